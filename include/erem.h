@@ -361,11 +361,11 @@ int erem_coupled_step_adjoint(erem_ctx* ctx, double h, const double* d_T, double
  * (constant fluid law), so G_p(T) = J_p T + g_p with constant J_p and the EREM
  * step (Eq. EERM) uses a fixed Gershgorin interval, substep count and set of
  * divided differences per problem (Sec. 4.2).  erem_batch_run advances all
- * problems by nsteps steps.  The problems are cut into 64 x rows tiles that
- * form one list; a run is a sequence of phases, and each phase is one work
+ * problems by nsteps steps.  The problems are cut into tiles (a strip of at
+ * most 64 columns by some rows) that form one list; a run is a sequence of phases, and each phase is one work
  * launch over the whole list - every problem that is not done takes one step
- * of its own schedule: a substep's start pass (q_0, p = d_0 q_0), four Newton
- * terms (Eq. newt) staged in LDS, or the last step's T update - followed by a
+ * of its own schedule: a substep's start pass (q_0, p = d_0 q_0), four or
+ * eight Newton terms (Eq. newt), or the last step's T update - followed by a
  * control launch that reduces each problem's tile partials in a fixed order
  * (so runs are bit-for-bit reproducible), applies the stop test of Sec. 4.2
  * and picks the problem's next phase.  With use_graph the whole sequence is
@@ -380,11 +380,10 @@ typedef struct {
     int64_t terms_total;   /* Newton-Leja terms summed over problems and steps */
     int32_t terms_min, terms_max;  /* per problem, over the run */
     int32_t failed;        /* problems that stopped on an error (see the return code) */
-    int32_t tile_shape;    /* 0: 64 x 8 tiles on 512 threads, 1: 64 x 16 on 1024 threads,
-                              2: 64 x 8 on 512 threads, 3: 64 x 16 on 512, 4: 64 x 32 on
-                              512, all with four Newton terms per pass; 5: 64 x 16 and
-                              6: 64 x 8 and 7: 64 x 32 on 512 threads with eight terms per
-                              pass; each XCD takes a contiguous range of tiles in 2-7.  The stop test is
+    int32_t tile_shape;    /* rows of a tile: 0: 16, 1: 8, 2: 32, 3: 64, 4: 128, all with
+                              four Newton terms per pass; 5: 32, 6: 16, 7: 64 with eight
+                              terms per pass; a tile is one wavefront's strip of at most
+                              64 columns.  The stop test is
                               evaluated term by term after each pass and all terms of the
                               pass are kept (the applied degree is the first multiple of
                               the pass width at which the test holds) */

@@ -8,15 +8,17 @@
 
 namespace erem {
 
-// Tile shapes of the work kernel: 64 x kBatchTileRows[shape] cells on 64 x
-// kBatchThreadRows[shape] threads, kBatchPassTerms[shape] Newton terms per
-// pass; shapes 2-7 place the tiles so that each XCD takes a contiguous range
-// of them.
+// Tile shapes of the work pass: a tile is a strip of columns (march.h) by
+// kBatchTileRows[shape] rows, advanced by kBatchPassTerms[shape] Newton terms
+// per pass by one wavefront.  Eight terms halve the bytes per term; short
+// tiles re-read more rows (2 NT per tile) but shorten a pass whose problems do
+// not fill the chip.  50 steps of 256 realisations (7.2 M cells, FP64): 95 ms
+// with 4 terms x 32 rows, 69.8 / 65.9 / 74.8 ms with 8 terms x 16 / 32 / 64
+// rows; 5 steps of 20 realisations (mixed): 2.60 ms with 4 x 8, 2.66 with
+// 4 x 16, 2.47 with 8 x 16, 2.99 with 8 x 32.
 constexpr int kNumTileShapes = 8;
-constexpr int kBatchTileRows[kNumTileShapes] = {8, 16, 8, 16, 32, 16, 8, 32};
-constexpr int kBatchThreadRows[kNumTileShapes] = {8, 16, 8, 8, 8, 8, 8, 8};
+constexpr int kBatchTileRows[kNumTileShapes] = {16, 8, 32, 64, 128, 32, 16, 64};
 constexpr int kBatchPassTerms[kNumTileShapes] = {4, 4, 4, 4, 4, 8, 8, 8};
-constexpr int kBatchTileX = 64;
 constexpr int kBatchPartStride = 8;  // partials per tile (one per term of a pass)
 
 // Static description of one problem of the batch.
@@ -29,14 +31,12 @@ struct BProb {
   double delta;   // substep length h / s
   double rootN;   // sqrt(nx ny)
   int tile0;      // first tile of the problem in the tile list
-  int ntiles;     // its tiles (tiles_x rows of 64 x rows cells)
-  int tiles_x;
-  int pad;
+  int ntiles;     // its tiles
 };
 
-// Tile list entry: the problem and the tile's first cell.
+// Tile list entry: the problem, the strip of columns and the first row.
 struct BTile {
-  int pid, x0, y0;
+  int pid, strip, y0;
   int done;  // set by the control kernel once the problem is done: the tile returns at entry
 };
 
@@ -92,17 +92,17 @@ struct BatchArgs {
   double* part;          // kBatchPartStride partials per tile
   long long ntot;
   int nprob, ntiles, nsteps, m_max;
-  int nt;                // Newton terms per pass of the tile shape
+  int nt, rows;          // Newton terms per pass and rows per tile of the tile shape
+  int pass;              // parity of the pass (the order in which the tiles are taken)
   double tol_a, tol_r, thresh;
 };
 
 hipError_t batch_pack(int nx, int ny, const double* coef, const double* F, const double* T0,
                       double* bcoef, double* g, long long ntot, long long off, hipStream_t s);
 hipError_t batch_reset(const BatchArgs& a, hipStream_t s);
-// One phase of every problem: the work pass over all tiles, then the control
-// kernel.  e0 / e1 (optional) time the work pass alone.
-hipError_t batch_phase(const BatchArgs& a, int shape, int fp32, hipStream_t s, hipEvent_t e0 = nullptr,
+// One phase of every problem: work pass number `pass` over all tiles, then the
+// control kernel.  e0 / e1 (optional) time the work pass alone.
+hipError_t batch_phase(BatchArgs a, long long pass, int fp32, hipStream_t s, hipEvent_t e0 = nullptr,
                        hipEvent_t e1 = nullptr);
-size_t batch_lds_bytes(int shape, int fp32);
 
 }  // namespace erem

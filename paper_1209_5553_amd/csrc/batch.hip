@@ -6,8 +6,9 @@
 // (Eq. EERM) with a Gershgorin interval, substep count and divided
 // differences fixed for the whole run (Sec. 4.2).
 //
-// MI355X mapping.  The problems are cut into 64 x rows tiles and all tiles
-// of all problems form one list.  A run is a sequence of phases; in each
+// MI355X mapping.  The problems are cut into tiles - strips of at most 64
+// columns by a chunk of rows, one wavefront each (march.h) - and all tiles of
+// all problems form one list.  A run is a sequence of phases; in each
 // phase ONE work launch covers the whole tile list and advances every
 // problem that is not done by one step of its own schedule:
 //
@@ -19,10 +20,10 @@
 //               q_k = ((J - cI)/gamma - xi_{k-1}) q_{k-1}, p += d_k q_k
 //               (Eq. newt) on the tile, computed over the tile plus the halo
 //               that NT stencil applications need; the intermediate terms
-//               never leave the CU;
+//               stay in registers;
 //   finish pass T += u + delta p of the last step.
 //
-// Each tile stores its block partial sums (sum q_k^2 per term, in FP64); a
+// Each tile stores its partial sums (sum q_k^2 per term, in FP64); a
 // control kernel then reduces each problem's partials in a fixed order (one
 // wavefront per problem), applies the scaled-norm stop test of Sec. 4.2 to
 // the pass's NT estimates in order, and sets the problem's next phase.
@@ -34,6 +35,7 @@
 // rewrites (T, u, p) are ping-ponged so that no tile reads a neighbour's
 // updated value.
 #include "batch.h"
+#include "march.h"
 
 #include <cmath>
 
@@ -41,262 +43,224 @@ namespace erem {
 
 namespace {
 
+// Rows loaded ahead: four keep 14 KB per wavefront in flight and still fit 256
+// registers with eight FP64 terms (two: 71.2 ms a run, four: 70.4).
+constexpr int kBatchAhead = 4;
+
 template <class V>
 __device__ inline V cv(double x) { return static_cast<V>(x); }
 
-// Two buffers in the frame of q_{k-1} (the tile plus a halo of NT): the
-// first holds q_{k-1}, then the odd intermediate terms; the second the even
-// ones.
-template <int TY, int NT, class V>
-constexpr size_t work_lds_bytes() {
-  return 2 * sizeof(V) * static_cast<size_t>(TY + 2 * NT) * (kBatchTileX + 2 * NT);
+// Maximum over the wavefront, valid in lane 0.
+__device__ inline double march_max(double v) {
+  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_down(v, off, 64));
+  return v;
 }
 
-// Sum (or max) over the workgroup of one double per thread; fixed order
-// (each wavefront by a shuffle tree, then the wavefronts in order); the
-// result is valid in thread 0.
-template <int NW, bool MAX>
-__device__ inline double block_reduce(double v, double* sh, int tid) {
-  for (int off = 32; off > 0; off >>= 1) {
-    const double o = __shfl_down(v, off, 64);
-    v = MAX ? fmax(v, o) : v + o;
+// Start pass of substep S.sub of step S.step on one strip's chunk of rows:
+// the vector w whose J w enters q_0 (T^n, or the substep sum u, both formed
+// here from the arrays the previous pass left), q_0 = v + J u or G = J T + g,
+// p = d_0 q_0.  Marches like the term pass (row r of w arrives, row r - 1 of
+// q_0 leaves); an array that this kind of pass does not read or write gets an
+// empty descriptor, so its loads give zero and its stores are dropped.
+template <class V>
+__device__ inline void batch_start(const BatchArgs& a, const BProb& P, const BState& S, MarchStrip st, int y0, int y1,
+                                   double* part) {
+  constexpr int PD = 6, U = 8;
+  const int nx = P.nx, ny = P.ny, lane = threadIdx.x & 63;
+  const int r0 = max(0, y0 - 1), rend = min(ny, y1 + 1);
+  const long long org = P.off + static_cast<long long>(nx) * r0;
+  const unsigned rb = static_cast<unsigned>(nx) * 8u, rv = static_cast<unsigned>(nx) * sizeof(V);
+  const unsigned bytes = rb * static_cast<unsigned>(rend - r0), bytv = rv * static_cast<unsigned>(rend - r0);
+  const bool first = S.kind == kInitFirst, sub = S.kind == kInitSub;
+  const bool use_u = sub ? S.sub > 1 : (!first && P.s > 1);
+  const double delta = first ? 0.0 : P.delta;
+  const __amdgpu_buffer_rsrc_t rT = march_rsrc((S.tpar ? a.T1 : a.T0) + org, sub ? 0u : bytes);
+  const __amdgpu_buffer_rsrc_t ru = march_rsrc((S.upar ? a.u1 : a.u0) + org, use_u ? bytes : 0u);
+  const __amdgpu_buffer_rsrc_t rp =
+      march_rsrc(reinterpret_cast<const V*>(S.ppar ? a.p1 : a.p0) + org, first ? 0u : bytv);
+  const __amdgpu_buffer_rsrc_t ra = march_rsrc((sub ? a.v : a.g) + org, bytes);
+  __amdgpu_buffer_rsrc_t rc[5];
+#pragma unroll
+  for (int d = 0; d < 5; ++d) rc[d] = march_rsrc(a.coef64 + d * a.ntot + org, bytes);
+  // outputs: the strip's own columns, rows y0 .. y1 - 1
+  const long long oout = P.off + static_cast<long long>(nx) * y0;
+  const unsigned rows = static_cast<unsigned>(y1 - y0);
+  double* wdst = sub ? (S.upar ? a.u0 : a.u1) : (S.tpar ? a.T0 : a.T1);
+  const __amdgpu_buffer_rsrc_t ow = march_rsrc(wdst + oout, first ? 0u : rb * rows);
+  const __amdgpu_buffer_rsrc_t ov = march_rsrc(a.v + oout, sub ? 0u : rb * rows);
+  const __amdgpu_buffer_rsrc_t oq = march_rsrc(reinterpret_cast<V*>(a.q0) + oout, rv * rows);
+  const __amdgpu_buffer_rsrc_t op = march_rsrc(reinterpret_cast<V*>(S.ppar ? a.p0 : a.p1) + oout, rv * rows);
+  const V d0 = cv<V>(a.dk[P.coef_off]);
+  const int gx = st.xs + lane;
+  const bool in = gx < nx, out = gx >= st.x0 && gx < st.x1;
+  const unsigned base = in ? static_cast<unsigned>(gx) * 8u : kMarchOut;
+  const unsigned basv = in ? static_cast<unsigned>(gx) * static_cast<unsigned>(sizeof(V)) : kMarchOut;
+  const unsigned bo = out ? static_cast<unsigned>(gx) * 8u : kMarchOut;
+  const unsigned bov = out ? static_cast<unsigned>(gx) * static_cast<unsigned>(sizeof(V)) : kMarchOut;
+  double T[U], uu[U], c[U][5], ad[U], w[2] = {0.0, 0.0};
+  V pp[U];
+#pragma unroll
+  for (int i = 0; i < U; ++i) {
+    T[i] = uu[i] = ad[i] = 0.0;
+    pp[i] = V(0);
+#pragma unroll
+    for (int d = 0; d < 5; ++d) c[i][d] = 0.0;
   }
-  if ((tid & 63) == 0) sh[tid >> 6] = v;
-  __syncthreads();
-  double r = 0.0;
-  if (tid == 0) {
-    r = sh[0];
-    for (int w = 1; w < NW; ++w) r = MAX ? fmax(r, sh[w]) : r + sh[w];
+#pragma unroll
+  for (int i = 0; i < PD; ++i) {
+    const unsigned o = base + static_cast<unsigned>(i) * rb;
+    march_load(rT, o, T[i]);
+    march_load(ru, o, uu[i]);
+    march_load(rp, basv + static_cast<unsigned>(i) * rv, pp[i]);
+    if (i + 1 < PD) {
+#pragma unroll
+      for (int d = 0; d < 5; ++d) march_load(rc[d], o, c[i][d]);
+      march_load(ra, o, ad[i]);
+    }
   }
-  __syncthreads();
-  return r;
+  double s0 = 0.0, mx = 0.0;
+  int r = r0;
+  unsigned offl = base + PD * rb, ofpl = basv + PD * rv;
+  unsigned offo = bo + static_cast<unsigned>(r0 - 1 - y0) * rb, ofvo = bov + static_cast<unsigned>(r0 - 1 - y0) * rv;
+  for (;;) {
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      march_load(rT, offl, T[(k + PD) % U]);
+      march_load(ru, offl, uu[(k + PD) % U]);
+      march_load(rp, ofpl, pp[(k + PD) % U]);
+#pragma unroll
+      for (int d = 0; d < 5; ++d) march_load(rc[d], offl - rb, c[(k + PD + U - 1) % U][d]);
+      march_load(ra, offl - rb, ad[(k + PD + U - 1) % U]);
+      __builtin_amdgcn_sched_barrier(0);
+      const double wn = T[k] + uu[k] + delta * static_cast<double>(pp[k]);  // row r
+      const double wc = w[(k + 1) & 1], ws = w[k & 1];                      // rows r - 1, r - 2
+      const int s = (k + U - 1) % U;
+      double jw = c[s][0] * wc;
+      jw += c[s][1] * west(wc);
+      jw += c[s][2] * east(wc);
+      jw += c[s][3] * ws;
+      jw += c[s][4] * wn;
+      const double q = jw + ad[s];
+      const V qv = cv<V>(q);
+      march_store(ow, offo, wc);
+      march_store(ov, offo, q);
+      march_store(oq, ofvo, qv);
+      march_store(op, ofvo, d0 * qv);
+      const bool row = r - 1 >= y0;
+      const double qm = march_mask(row, static_cast<double>(qv));
+      s0 += qm * qm;
+      mx = fmax(mx, row ? fabs(wc) : 0.0);
+      w[k & 1] = wn;
+      if (r == y1) goto done;
+      ++r;
+      offl += rb;
+      ofpl += rv;
+      offo += rb;
+      ofvo += rv;
+    }
+  }
+done:
+  s0 = march_sum(out ? s0 : 0.0);
+  mx = march_max(out && !sub ? mx : 0.0);
+  if (lane == 0) {
+    part[0] = s0;
+    part[1] = mx;
+  }
 }
 
-template <int TY, int BY, int NT, bool XCD, class V>
-__global__ __launch_bounds__(kBatchTileX* BY) void k_bt_work(BatchArgs a) {
-  static_assert(TY % BY == 0, "whole thread rows per tile");
-  static_assert(NT >= 2 && NT <= kBatchPartStride, "terms per pass");
-  constexpr int NTH = kBatchTileX * BY;  // threads
-  constexpr int NW = NTH / 64;
-  constexpr int R = TY / BY;             // tile rows per thread in the start and finish passes
-  constexpr int H = NT - 1;
-  constexpr int WQ = kBatchTileX + 2 * NT, HQ = TY + 2 * NT;  // q_{k-1}: halo NT
-  constexpr int WI = kBatchTileX + 2 * H, HI = TY + 2 * H;    // stencil, intermediates: halo NT - 1
-  extern __shared__ __align__(16) unsigned char smem[];
-  V(*sq)[WQ] = reinterpret_cast<V(*)[WQ]>(smem);  // q_{k-1}, then the odd terms
-  V(*sb)[WQ] = reinterpret_cast<V(*)[WQ]>(smem + sizeof(V) * HQ * WQ);  // the even terms
-  __shared__ double red[NT][NW];
+// Finish pass: T^N = T^{N-1} + u + delta p into the caller's array (a failed
+// problem keeps its last step's T).
+template <class V>
+__device__ inline void batch_finish(const BatchArgs& a, const BProb& P, const BState& S, MarchStrip st, int y0,
+                                    int y1) {
+  constexpr int U = 8;
+  const int nx = P.nx, lane = threadIdx.x & 63;
+  const long long org = P.off + static_cast<long long>(nx) * y0;
+  const unsigned rb = static_cast<unsigned>(nx) * 8u, rv = static_cast<unsigned>(nx) * sizeof(V);
+  const unsigned rows = static_cast<unsigned>(y1 - y0);
+  const bool ok = S.flags == 0;
+  const double delta = ok ? P.delta : 0.0;
+  const __amdgpu_buffer_rsrc_t rT = march_rsrc((S.tpar ? a.T1 : a.T0) + org, rb * rows);
+  const __amdgpu_buffer_rsrc_t ru = march_rsrc((S.upar ? a.u1 : a.u0) + org, ok && P.s > 1 ? rb * rows : 0u);
+  const __amdgpu_buffer_rsrc_t rp =
+      march_rsrc(reinterpret_cast<const V*>(S.ppar ? a.p1 : a.p0) + org, ok ? rv * rows : 0u);
+  const __amdgpu_buffer_rsrc_t ro = march_rsrc(a.T0 + org, rb * rows);
+  const int gx = st.xs + lane;
+  const bool out = gx >= st.x0 && gx < st.x1;
+  unsigned o = out ? static_cast<unsigned>(gx) * 8u : kMarchOut;
+  unsigned ov = out ? static_cast<unsigned>(gx) * static_cast<unsigned>(sizeof(V)) : kMarchOut;
+  for (int y = y0; y < y1; y += U, o += U * rb, ov += U * rv) {
+    double T[U], u[U];
+    V p[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      march_load(rT, o + k * rb, T[k]);
+      march_load(ru, o + k * rb, u[k]);
+      march_load(rp, ov + k * rv, p[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) march_store(ro, o + k * rb, T[k] + (u[k] + delta * static_cast<double>(p[k])));
+  }
+}
 
-  const int t = XCD ? xcd_tile_id() : static_cast<int>(blockIdx.x);
+// Tile of this workgroup: each XCD takes one contiguous range of the list (as
+// xcd_tile_id does), front to back on even passes and back to front on odd
+// ones, so that a pass begins with what the pass before left in the caches.
+__device__ inline int batch_tile(int back) {
+  const int n = gridDim.x, b = blockIdx.x;
+  const int q = n / kXcds, r = n % kXcds, x = b % kXcds, k = b / kXcds;
+  const int size = q + (x < r ? 1 : 0);
+  return x * q + (x < r ? x : r) + (back ? size - 1 - k : k);
+}
+
+// One phase of every unfinished problem: a wavefront per tile (a strip of
+// columns by a chunk of rows).  While most problems are unfinished the pass is
+// bound by memory: eight FP64 terms of 7.2 M cells read 544 MB (5 stencil
+// words, q and p, plus the halos that missed L2) and write 115 MB in about
+// 145 us, 4.5 TB/s where a large copy reaches 4.8; taking every second pass
+// back to front finds the end of the pass before in the Infinity Cache (a run
+// of 50 steps 70.4 -> 65.9 ms).  The 64 x 16 LDS tiles on 512 threads that
+// this replaces took 215 us for the same pass (two workgroups' loads per CU in
+// flight, then eight barriered terms) and 92 ms for the run.  When only the
+// longest problems are left, a pass costs what one wavefront takes to issue
+// its rows (about 500 cycles a row of eight terms).
+template <int NT, class V>
+__global__ __launch_bounds__(kMarchLanes) __attribute__((amdgpu_waves_per_eu(2))) void k_bt_work(BatchArgs a) {
+  static_assert(NT <= kBatchPartStride, "terms per pass");
+  const int t = batch_tile(a.pass & 1);
   const BTile tl = a.tile[t];
   if (tl.done) return;  // the tiles of a finished problem stop here, before its state is read
   const BState S = a.state[tl.pid];
   if (S.phase == kPhDone) return;
   const BProb P = a.prob[tl.pid];
-  const int nx = P.nx, ny = P.ny;
-  const long long o = P.off, Nt = a.ntot;
-  const int lx = threadIdx.x, ly = threadIdx.y;
-  const int tid = lx + kBatchTileX * ly;
-  const int x = tl.x0 + lx;
+  const MarchStrip st = march_strip(P.nx, NT, tl.strip);
+  const int y0 = tl.y0, y1 = min(tl.y0 + a.rows, P.ny);
   double* part = a.part + static_cast<long long>(kBatchPartStride) * t;
-
   if (S.phase == kPhFinish) {
-    // T^N = T^{N-1} + u + delta p (a failed problem keeps its last step's T)
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int y = tl.y0 + ly + r * BY;
-      if (x < nx && y < ny) {
-        const long long i = o + x + static_cast<long long>(nx) * y;
-        const double* Tc = S.tpar ? a.T1 : a.T0;
-        double Tn = Tc[i];
-        if (S.flags == 0) {
-          const V* pc = reinterpret_cast<const V*>(S.ppar ? a.p1 : a.p0);
-          const double* uc = S.upar ? a.u1 : a.u0;
-          Tn += (P.s > 1 ? uc[i] : 0.0) + P.delta * static_cast<double>(pc[i]);
-        }
-        a.T0[i] = Tn;
-      }
-    }
+    batch_finish<V>(a, P, S, st, y0, y1);
     return;
   }
-
   if (S.phase == kPhInit) {
-    // start of substep S.sub of step S.step
-    double s0 = 0.0, mx = 0.0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int y = tl.y0 + ly + r * BY;
-      if (!(x < nx && y < ny)) continue;
-      const long long i = o + x + static_cast<long long>(nx) * y;
-      const long long jw = x > 0 ? i - 1 : i, je = x + 1 < nx ? i + 1 : i;
-      const long long js = y > 0 ? i - nx : i, jn = y + 1 < ny ? i + nx : i;
-      const long long jj[5] = {i, jw, je, js, jn};
-      double c[5], w[5];
-#pragma unroll
-      for (int d = 0; d < 5; ++d) c[d] = a.coef64[d * Nt + i];  // 0 toward missing neighbours
-      const double* Tc = S.tpar ? a.T1 : a.T0;
-      const double* uc = S.upar ? a.u1 : a.u0;
-      const V* pc = reinterpret_cast<const V*>(S.ppar ? a.p1 : a.p0);
-      if (S.kind == kInitFirst) {
-#pragma unroll
-        for (int d = 0; d < 5; ++d) w[d] = Tc[jj[d]];
-      } else if (S.kind == kInitStep) {
-        // T^{n} = T^{n-1} + u + delta p at the cell and its neighbours
-        const bool use_u = P.s > 1;
-#pragma unroll
-        for (int d = 0; d < 5; ++d)
-          w[d] = Tc[jj[d]] + (use_u ? uc[jj[d]] : 0.0) + P.delta * static_cast<double>(pc[jj[d]]);
-      } else {
-        // u after substep S.sub - 1: u + delta p (u = 0 after the first)
-        const bool use_u = S.sub > 1;
-#pragma unroll
-        for (int d = 0; d < 5; ++d) w[d] = (use_u ? uc[jj[d]] : 0.0) + P.delta * static_cast<double>(pc[jj[d]]);
-      }
-      double jw_ = c[0] * w[0];
-#pragma unroll
-      for (int d = 1; d < 5; ++d) jw_ += c[d] * w[d];
-      double q;
-      if (S.kind == kInitSub) {
-        (S.upar ? a.u0 : a.u1)[i] = w[0];
-        q = a.v[i] + jw_;
-      } else {
-        if (S.kind == kInitStep) (S.tpar ? a.T0 : a.T1)[i] = w[0];
-        q = jw_ + a.g[i];
-        a.v[i] = q;
-        mx = fmax(mx, fabs(w[0]));
-      }
-      const V qv = cv<V>(q);
-      reinterpret_cast<V*>(a.q0)[i] = qv;
-      reinterpret_cast<V*>(S.ppar ? a.p0 : a.p1)[i] = cv<V>(a.dk[P.coef_off]) * qv;
-      s0 += static_cast<double>(qv) * static_cast<double>(qv);
-    }
-    const double S0 = block_reduce<NW, false>(s0, &red[0][0], tid);
-    const double M0 = block_reduce<NW, true>(mx, &red[1][0], tid);
-    if (tid == 0) {
-      part[0] = S0;
-      part[1] = M0;
-    }
+    batch_start<V>(a, P, S, st, y0, y1, part);
     return;
   }
-
-  // NT Newton terms S.k .. S.k + NT - 1 on the tile.  The tile plus its
-  // halo of NT - 1 (the "box", HI x WI cells) is cut into vertical strips of
-  // SH cells, one per thread, consecutive threads taking consecutive
-  // columns.  A thread keeps the stencil and the current term of its strip
-  // in registers and computes its cells in every term whose region (the box
-  // shrinking by one cell per term) holds them: the north and south
-  // neighbours come from its own registers (from LDS at the strip's ends),
-  // the west and east ones from LDS, where every term is written for the
-  // neighbouring strips.  p and the partial sums accumulate for the strip's
-  // cells in the tile.
   const int grp = (S.k - 1) / NT;
-  const V* __restrict__ qin = reinterpret_cast<const V*>((grp & 1) ? a.q1 : a.q0);
-  V* __restrict__ qout = reinterpret_cast<V*>((grp & 1) ? a.q0 : a.q1);
-  V* __restrict__ p = reinterpret_cast<V*>(S.ppar ? a.p1 : a.p0);
-  const V* __restrict__ coef = reinterpret_cast<const V*>(a.coef);
-  const int x0 = tl.x0, y0 = tl.y0;
-  constexpr int UQ = (HQ * WQ + NTH - 1) / NTH;  // q values staged per thread
-  constexpr int SROWS = NTH / WI;                // strip rows the threads can cover
-  static_assert(SROWS >= 1, "a thread per box column");
-  constexpr int SH = (HI + SROWS - 1) / SROWS;   // cells per strip
-  constexpr int NSR = (HI + SH - 1) / SH;        // strip rows used
-  const bool has_strip = tid < NSR * WI;
-  const int bx = has_strip ? tid % WI : 0;
-  const int by0 = has_strip ? (tid / WI) * SH : HI;  // first cell of the strip (box rows)
-  // every load of the tile is issued (into registers) before the first LDS
-  // store, so the tile waits for one memory latency
-  V rq[UQ];
+  const V* qin = reinterpret_cast<const V*>((grp & 1) ? a.q1 : a.q0) + P.off;
+  V* qout = reinterpret_cast<V*>((grp & 1) ? a.q0 : a.q1) + P.off;
+  V* p = reinterpret_cast<V*>(S.ppar ? a.p1 : a.p0) + P.off;
+  V shift[NT], dk[NT];
 #pragma unroll
-  for (int u = 0; u < UQ; ++u) {
-    const int e = tid + u * NTH;
-    const int ry = e / WQ, rx = e - ry * WQ;
-    const int gx = x0 - NT + rx, gy = y0 - NT + ry;
-    rq[u] = (e < HQ * WQ && gx >= 0 && gx < nx && gy >= 0 && gy < ny) ? qin[o + gx + nx * gy] : V(0);
+  for (int j = 0; j < NT; ++j) {
+    shift[j] = march_uniform(cv<V>(a.shift[P.coef_off + S.k + j]));
+    dk[j] = march_uniform(cv<V>(a.dk[P.coef_off + S.k + j]));
   }
-  const int gx = x0 - H + bx;
-  const bool col_in = has_strip && gx >= 0 && gx < nx;
-  const bool col_tile = has_strip && bx >= H && bx < H + kBatchTileX;
-  V rc[5][SH], acc[SH];
+  double sum[NT];
+  march_terms<NT, kBatchAhead, V>(reinterpret_cast<const V*>(a.coef) + P.off, a.ntot, qin, qout, p, P.nx, P.ny, st, y0, y1,
+                        cv<V>(P.inv_g), shift, dk, sum);
 #pragma unroll
-  for (int r = 0; r < SH; ++r) {
-    const int by = by0 + r, gy = y0 - H + by;
-    const bool in = col_in && by < HI && gy >= 0 && gy < ny;
-    const long long j = o + (in ? gx + static_cast<long long>(nx) * gy : 0);
-#pragma unroll
-    for (int d = 0; d < 5; ++d) rc[d][r] = in ? coef[d * Nt + j] : V(0);
-    const bool tile_cell = in && col_tile && by >= H && by < H + TY;
-    acc[r] = tile_cell ? p[j] : V(0);
-  }
-#pragma unroll
-  for (int u = 0; u < UQ; ++u) {
-    const int e = tid + u * NTH;
-    if (e < HQ * WQ) sq[e / WQ][e % WQ] = rq[u];
-  }
-  __syncthreads();
-  // the strip's q_{k-1} (rows up to HI: the halo of q_{k-1} above the box)
-  V cur[SH];
-#pragma unroll
-  for (int r = 0; r < SH; ++r) cur[r] = has_strip && by0 + r <= HI ? sq[by0 + r + 1][bx + 1] : V(0);
-  const V ig = cv<V>(P.inv_g);
-  const double* shf = a.shift + P.coef_off + S.k;
-  const double* dkp = a.dk + P.coef_off + S.k;
-#pragma unroll
-  for (int tt = 0; tt < NT; ++tt) {
-    const V sh = cv<V>(shf[tt]);
-    const V dkt = cv<V>(dkp[tt]);
-    const V(*src)[WQ] = (tt & 1) ? sb : sq;
-    V(*dst)[WQ] = (tt & 1) ? sq : sb;
-    double sum = 0.0;  // this thread's share of sum q_k^2 over the tile
-    // the cell below the strip, from LDS (the strip above computed it)
-    const V below = has_strip ? src[by0][bx + 1] : V(0);
-    const V above = has_strip && by0 + SH + 1 < HQ ? src[by0 + SH + 1][bx + 1] : V(0);
-    V nxt[SH];
-#pragma unroll
-    for (int r = 0; r < SH; ++r) {
-      const int by = by0 + r;
-      nxt[r] = cur[r];
-      // the region of term tt: the box less tt cells on every side
-      if (has_strip && by >= tt && by < HI - tt && bx >= tt && bx < WI - tt) {
-        const V qc = cur[r];
-        const V qw = src[by + 1][bx];
-        const V qe = src[by + 1][bx + 2];
-        const V qs = r > 0 ? cur[r - 1] : below;
-        const V qn = r + 1 < SH ? cur[r + 1] : above;
-        V jq = rc[0][r] * qc;
-        jq += rc[1][r] * qw;
-        jq += rc[2][r] * qe;
-        jq += rc[3][r] * qs;
-        jq += rc[4][r] * qn;
-        const V qo = jq * ig - sh * qc;  // zero outside the grid (stencil and q are)
-        nxt[r] = qo;
-        if (tt + 1 < NT) dst[by + 1][bx + 1] = qo;
-        if (col_tile && by >= H && by < H + TY) {
-          acc[r] += dkt * qo;
-          sum += static_cast<double>(qo) * static_cast<double>(qo);
-          if (tt + 1 == NT) {
-            // the last term: p and q_k of the tile go straight out
-            const int gy = y0 - H + by;
-            if (col_in && gy < ny) {
-              const long long j = o + gx + static_cast<long long>(nx) * gy;
-              p[j] = acc[r];
-              qout[j] = qo;
-            }
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < SH; ++r) cur[r] = nxt[r];
-    // the wavefront's share of the term's norm, to LDS in wavefront order
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
-    if ((tid & 63) == 0) red[tt][tid >> 6] = sum;
-    if (tt + 1 < NT) __syncthreads();
-  }
-  __syncthreads();
-  if (tid < NT) {
-    double v = red[tid][0];
-    for (int w = 1; w < NW; ++w) v += red[tid][w];
-    part[tid] = v;
+  for (int j = 0; j < NT; ++j) {
+    const double v = march_sum(sum[j]);
+    if ((threadIdx.x & 63) == 0) part[j] = v;
   }
 }
 
@@ -481,45 +445,16 @@ __global__ __launch_bounds__(256) void k_batch_pack(int nx, int ny, const double
   }
 }
 
-template <int TY, int BY, int NT, bool XCD, class V>
+template <class V>
 hipError_t launch_work(const BatchArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  const size_t bytes = work_lds_bytes<TY, NT, V>();
-  if (bytes > 65536) {
-    static bool granted = false;
-    if (!granted) {
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bt_work<TY, BY, NT, XCD, V>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes));
-      if (e != hipSuccess) return e;
-      granted = true;
-    }
-  }
-  launch_timed(k_bt_work<TY, BY, NT, XCD, V>, dim3(a.ntiles), dim3(kBatchTileX, BY), static_cast<unsigned>(bytes), s,
-               e0, e1, a);
+  if (a.nt == 8)
+    launch_timed(k_bt_work<8, V>, dim3(a.ntiles), dim3(kMarchLanes), 0, s, e0, e1, a);
+  else
+    launch_timed(k_bt_work<4, V>, dim3(a.ntiles), dim3(kMarchLanes), 0, s, e0, e1, a);
   return hipGetLastError();
 }
 
-template <class V>
-hipError_t launch_work_shape(const BatchArgs& a, int shape, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  switch (shape) {
-    case 0: return launch_work<8, 8, 4, false, V>(a, s, e0, e1);
-    case 1: return launch_work<16, 16, 4, false, V>(a, s, e0, e1);
-    case 2: return launch_work<8, 8, 4, true, V>(a, s, e0, e1);
-    case 3: return launch_work<16, 8, 4, true, V>(a, s, e0, e1);
-    case 4: return launch_work<32, 8, 4, true, V>(a, s, e0, e1);
-    case 5: return launch_work<16, 8, 8, true, V>(a, s, e0, e1);
-    case 6: return launch_work<8, 8, 8, true, V>(a, s, e0, e1);
-    case 7: return launch_work<32, 8, 8, true, V>(a, s, e0, e1);
-    default: return hipErrorInvalidValue;
-  }
-}
-
 }  // namespace
-
-size_t batch_lds_bytes(int shape, int fp32) {
-  const size_t vb = fp32 ? sizeof(float) : sizeof(double);
-  const size_t rows = kBatchTileRows[shape], nt = kBatchPassTerms[shape];
-  return 2 * vb * (rows + 2 * nt) * (kBatchTileX + 2 * nt);
-}
 
 hipError_t batch_pack(int nx, int ny, const double* coef, const double* F, const double* T0, double* bcoef,
                       double* g, long long ntot, long long off, hipStream_t s) {
@@ -536,8 +471,9 @@ hipError_t batch_reset(const BatchArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t batch_phase(const BatchArgs& a, int shape, int fp32, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  const hipError_t e = fp32 ? launch_work_shape<float>(a, shape, s, e0, e1) : launch_work_shape<double>(a, shape, s, e0, e1);
+hipError_t batch_phase(BatchArgs a, long long pass, int fp32, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  a.pass = static_cast<int>(pass & 1);
+  const hipError_t e = fp32 ? launch_work<float>(a, s, e0, e1) : launch_work<double>(a, s, e0, e1);
   if (e != hipSuccess) return e;
   const int per = kCtrlThreads / 64;
   hipLaunchKernelGGL(k_bt_ctrl, dim3((a.nprob + per - 1) / per), dim3(kCtrlThreads), 0, s, a);

@@ -19,6 +19,7 @@
 #include "device.h"
 #include "host_numerics.h"
 #include "leja.h"
+#include "march.h"
 
 using namespace erem;
 
@@ -110,8 +111,8 @@ void free_batch(erem_batch* b) {
   b->ctxs.clear();
 }
 
-// Tile list and per-problem tile ranges for the current shape (64 x rows
-// tiles, each problem's tiles row by row).  The work pass deals the tile
+// Tile list and per-problem tile ranges for the current shape (strips of
+// columns by chunks of rows, each problem's tiles chunk by chunk).  The work pass deals the tile
 // list to the XCDs in eight contiguous chunks, so the order of the problems
 // decides which XCD works on which problem.  Once the intervals are known
 // the problems go in order of their schedule length h (beta - alpha) (the
@@ -121,7 +122,7 @@ void free_batch(erem_batch* b) {
 // longest problems are left, run on all XCDs.  Each problem's own results do
 // not depend on the order.
 int build_tiles(erem_batch* b) {
-  const int rows = kBatchTileRows[b->shape];
+  const int rows = kBatchTileRows[b->shape], nt = kBatchPassTerms[b->shape];
   std::vector<BTile> tiles;
   std::vector<int> ord(b->nprob);
   std::vector<double> len(b->nprob, 0.0);
@@ -140,25 +141,25 @@ int build_tiles(erem_batch* b) {
   for (const auto& g : groups) ord.insert(ord.end(), g.begin(), g.end());
   for (const int i : ord) {
     BProb& P = b->hprob[i];
-    const int tx = static_cast<int>((b->grids[i].nx + kBatchTileX - 1) / kBatchTileX);
-    const int ty = static_cast<int>((b->grids[i].ny + rows - 1) / rows);
+    const int tx = march_strips(P.nx, nt), ty = (P.ny + rows - 1) / rows;
     P.tile0 = static_cast<int>(tiles.size());
     P.ntiles = tx * ty;
-    P.tiles_x = tx;
     for (int y = 0; y < ty; ++y)
-      for (int x = 0; x < tx; ++x) tiles.push_back(BTile{i, x * kBatchTileX, y * rows, 0});
+      for (int x = 0; x < tx; ++x) tiles.push_back(BTile{i, x, y * rows, 0});
   }
   if (tiles.size() > static_cast<size_t>(1 << 30)) return bfail(b, EREM_EINVAL, "too many tiles");
   b->ntiles = static_cast<int>(tiles.size());
   if (b->ntiles > b->tile_cap) {
-    // sized once for the largest tile count of any shape (the fewest rows),
-    // so that the arrays the graphs hold are never reallocated
-    long long cap = 0;
-    int rmin = kBatchTileRows[0];
-    for (int k = 1; k < kNumTileShapes; ++k) rmin = std::min(rmin, kBatchTileRows[k]);
-    for (int i = 0; i < b->nprob; ++i)
-      cap += ((b->grids[i].nx + kBatchTileX - 1) / kBatchTileX) * ((b->grids[i].ny + rmin - 1) / rmin);
-    cap = std::max<long long>(cap, b->ntiles);
+    // sized once for the largest tile count of any shape, so that the arrays
+    // the graphs hold are never reallocated
+    long long cap = b->ntiles;
+    for (int k = 0; k < kNumTileShapes; ++k) {
+      long long n = 0;
+      for (const BProb& P : b->hprob)
+        n += static_cast<long long>(march_strips(P.nx, kBatchPassTerms[k])) *
+             ((P.ny + kBatchTileRows[k] - 1) / kBatchTileRows[k]);
+      cap = std::max(cap, n);
+    }
     if (b->tile) (void)hipFree(b->tile);
     if (b->part) (void)hipFree(b->part);
     b->tile = nullptr;
@@ -202,6 +203,7 @@ BatchArgs make_args(erem_batch* b, double* T, int nsteps) {
   a.tol_r = b->tol_r;
   a.thresh = b->thresh;
   a.nt = kBatchPassTerms[b->shape];
+  a.rows = kBatchTileRows[b->shape];
   return a;
 }
 
@@ -263,7 +265,7 @@ int run_eager(erem_batch* b, const BatchArgs& a, long long start, long long* pas
     }
     for (int c = 0; c < kChunk && n < limit; ++c, ++n) {
       const bool time_it = !ev.empty() && n % b->prof_stride == 0;
-      const hipError_t le = batch_phase(a, b->shape, b->fp32, b->stream, time_it ? ev[2 * c] : nullptr,
+      const hipError_t le = batch_phase(a, n, b->fp32, b->stream, time_it ? ev[2 * c] : nullptr,
                                         time_it ? ev[2 * c + 1] : nullptr);
       if (le != hipSuccess) {
         drop();
@@ -283,7 +285,7 @@ int capture(erem_batch* b, const BatchArgs& a, int phases, erem_batch::Graph* g)
   hipGraph_t graph;
   BHIP(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
   hipError_t le = batch_reset(a, b->stream);
-  for (int n = 0; n < phases && le == hipSuccess; ++n) le = batch_phase(a, b->shape, b->fp32, b->stream);
+  for (int n = 0; n < phases && le == hipSuccess; ++n) le = batch_phase(a, n, b->fp32, b->stream);
   const hipError_t ce = hipStreamEndCapture(b->stream, &graph);
   if (le != hipSuccess || ce != hipSuccess) {
     (void)hipGetLastError();
@@ -402,17 +404,6 @@ int launch(erem_batch* b, double* T, int nsteps, bool use_graph, erem_batch_stat
 }
 
 // Switch the tile shape: the tile list changes, so the captured graphs go.
-// Whether a tile shape's dynamic LDS (at the batch's precision) fits the
-// device's limit per workgroup.
-bool shape_fits(const erem_batch* b, int shape) {
-  int max_lds = 0;
-  if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, b->device) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  return batch_lds_bytes(shape, b->fp32) + 1024 <= static_cast<size_t>(max_lds);  // + the static reduction arrays
-}
-
 int set_shape(erem_batch* b, int shape) {
   if (shape == b->shape) return EREM_OK;
   BHIP(b, hipStreamSynchronize(b->stream));
@@ -640,7 +631,6 @@ int erem_batch_autotune(erem_batch* b, const double* d_T, int32_t nsteps, int32_
   const int saved = b->prof_stride;
   b->prof_stride = 0;
   for (int s = 0; s < kNumTileShapes; ++s) {
-    if (!shape_fits(b, s)) continue;
     const int rc0 = set_shape(b, s);
     if (rc0) return rc0;
     BHIP(b, hipMemcpyAsync(b->tscratch, d_T, sizeof(double) * b->ntot, hipMemcpyDeviceToDevice, b->stream));
@@ -665,7 +655,6 @@ int erem_batch_autotune(erem_batch* b, const double* d_T, int32_t nsteps, int32_
 int erem_batch_set_tile_shape(erem_batch* b, int32_t shape) {
   if (!b) return EREM_EINVAL;
   if (shape < 0 || shape >= kNumTileShapes) return bfail(b, EREM_EINVAL, "tile shape index out of range");
-  if (!shape_fits(b, shape)) return bfail(b, EREM_EINVAL, "tile shape needs more LDS than the device has");
   return set_shape(b, shape);
 }
 

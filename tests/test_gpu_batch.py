@@ -283,6 +283,27 @@ def test_batch_degenerate_and_rectangular_problems_match_oracle(torch_mod, shape
         assert rel_inf(Tg - p.T0, Tref - p.T0) <= 1e-10, (shape, p.name)
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("shape", [0, 5, 7])
+def test_batch_strip_and_chunk_edges_match_oracle(torch_mod, shape, precision):
+    """Widths one below, at and one above the edges of the 64-lane strips
+    (64; 120 with four terms per pass, 112 with eight) and heights around the
+    16-, 32- and 64-row chunks: FP64 1e-10, FP32 1e-5 of the increment."""
+    from paper_1209_5553_amd.api import EremBatch, make_opts
+    sides = [(63, 15), (64, 16), (65, 17), (112, 33), (113, 31), (120, 63), (121, 65), (176, 7)]
+    probs = [_rect_problem(nx, ny, seed=60 + i) for i, (nx, ny) in enumerate(sides)]
+    b = EremBatch(probs, device="cuda:0")
+    b.prepare(probs[0].h, make_opts(m_max=256) if precision == 0 else
+              make_opts(m_max=256, precision=1, tol_r=1e-7))
+    b.set_tile_shape(shape)
+    T = b.pack([p.T0 for p in probs])
+    st = b.run(T, 2, use_graph=False)
+    _say(f"strip edges, shape {shape}, precision {precision}: {st}")
+    for p, Tg in zip(probs, b.unpack(T)):
+        Tref, _ = oerem.run_linear(p, nsteps=2, tier="taylor")
+        assert rel_inf(Tg - p.T0, Tref - p.T0) <= (1e-10 if precision == 0 else 1e-5), (shape, p.name)
+
+
 def test_batch_problem_over_the_term_budget_fails_alone(torch_mod):
     """Substeps capped at two: a stiff two-cell problem (h (beta - alpha)
     about 1200) cannot meet the tolerance within m_max terms of a substep of

@@ -152,7 +152,7 @@ int replay(erem_ctx* c, double h, const erem_tape* t, const Slots* store) {
       HIP_TRY(c, launch_leja_term<double>(d, c->cf, c->coef, cur, nxt, c->pacc, c->states, c->part, k, c->stream));
       cur = nxt;
     }
-    HIP_TRY(c, launch_substep_update<double>(d, c->u, c->pacc, delta, j == 0 ? 1 : 0, c->stream));
+    HIP_TRY(c, launch_substep_update<double>(d, c->u, c->pacc, delta, j == 0 ? 1 : 0, c->stream, c->states));
   }
   return EREM_OK;
 }

@@ -256,7 +256,7 @@ __global__ __launch_bounds__(kMarchLanes) __attribute__((amdgpu_waves_per_eu(2))
   }
   double sum[NT];
   march_terms<NT, kBatchAhead, V>(reinterpret_cast<const V*>(a.coef) + P.off, a.ntot, qin, qout, p, P.nx, P.ny, st, y0, y1,
-                        cv<V>(P.inv_g), shift, dk, sum);
+                        cv<V>(P.inv_g), shift, dk, sum, [] { return false; });
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     const double v = march_sum(sum[j]);

@@ -300,14 +300,6 @@ int read_reduce(erem_ctx* c) {
   return EREM_OK;
 }
 
-// Device buffers of the Newton passes in one precision: the stencil of J,
-// the two q buffers and the accumulated polynomial p.
-template <class V>
-struct LejaBufs {
-  const V* coef;
-  V *qa, *qb, *p;
-};
-
 int ensure_mixed(erem_ctx* c) {
   if (!c->coef32) {
     const size_t n = c->d.N;
@@ -325,14 +317,6 @@ int ensure_mixed(erem_ctx* c) {
   return EREM_OK;
 }
 
-// Newton terms computed by the launch that starts at term k of at most K:
-// four (2D, a whole stop-test group), else two, else one.
-int leja_terms_per_launch(const Dims& d, int k, int K) {
-  if (d.dim != 2) return 1;
-  if (k + 3 <= K) return 4;
-  return k + 1 <= K ? 2 : 1;
-}
-
 // One Newton-Leja evaluation over s substeps: its coefficient block, its s
 // stop-state slots, the vector that accumulates the substep increments and,
 // for the non-autonomous step, the time source g and the fixed phi2 term zt.
@@ -347,40 +331,18 @@ struct LejaPass {
 };
 
 template <class V>
-int leja_run(erem_ctx* c, const LejaBufs<V>& B, const LejaPass& P, const double* v, double delta, int s,
+int leja_run(erem_ctx* c, const LejaVecs<V>& B, const LejaPass& P, const double* v, double delta, int s,
              int K) {
   const Dims& d = c->d;
   for (int j = 0; j < s; ++j) {
-    LejaState* st = P.states + j;
     const double* src = v;
     if (j > 0) {
       HIP_TRY(c, launch_stencil_axpy(d, c->coef, v, P.out, c->w, c->stream, P.g, j * delta));
       src = c->w;
     }
-    HIP_TRY(c, launch_leja_init<V>(d, P.cf, src, B.qa, B.p, c->part, c->stream));
     hipEvent_t* evj = j < P.nprof ? &P.ev[static_cast<size_t>(j) * 2 * K] : nullptr;
-    int prev = -1;  // last term already checked
-    V* cur = B.qa;  // latest q
-    V* oth = B.qb;
-    // 2D grids take the terms in groups of four (one stop-test group per
-    // launch, so the stop test still follows every kCheckEvery terms)
-    for (int k = 1, launch = 0; k <= K; ++launch) {
-      const int nt = leja_terms_per_launch(d, k, K);
-      const bool timed = evj && launch % c->prof == 0;
-      hipEvent_t e0 = timed ? evj[2 * (k - 1)] : nullptr, e1 = timed ? evj[2 * (k - 1) + 1] : nullptr;
-      if (nt > 1)
-        HIP_TRY(c, launch_leja_terms<V>(d, P.cf, B.coef, cur, oth, B.p, st, c->part, k, nt, c->stream, e0, e1));
-      else
-        HIP_TRY(c, launch_leja_term<V>(d, P.cf, B.coef, cur, oth, B.p, st, c->part, k, c->stream, e0, e1));
-      std::swap(cur, oth);
-      k += nt;
-      const int last = k - 1;
-      if (last % kCheckEvery == 0 || last == K) {
-        HIP_TRY(c, launch_leja_check(d, P.cf, st, c->part, prev + 1, last, c->stream));
-        prev = last;
-      }
-    }
-    HIP_TRY(c, launch_substep_update<V>(d, P.out, B.p, delta, j == 0 ? 1 : 0, c->stream, P.zt));
+    HIP_TRY(c, leja_substep<V>(d, P.cf, B, src, P.states + j, c->part, K, P.out, delta, j == 0 ? 1 : 0, P.zt,
+                               c->stream, evj, c->prof));
   }
   return EREM_OK;
 }
@@ -496,11 +458,11 @@ int leja_hphi1(erem_ctx* c, double h, const double* v, const double* g, double s
   if (o->precision == EREM_PREC_MIXED) {
     rc = ensure_mixed(c);
     if (rc) return rc;
-    const LejaBufs<float> B{c->coef32, c->qa32, c->qb32, c->p32};
+    const LejaVecs<float> B{c->coef32, c->qa32, c->qb32, c->p32};
     if (na) rc = leja_run<float>(c, B, p2, g, delta * delta, 1, K);
     if (!rc) rc = leja_run<float>(c, B, p1, v, delta, s, K);
   } else {
-    const LejaBufs<double> B{c->coef, c->qa, c->qb, c->pacc};
+    const LejaVecs<double> B{c->coef, c->qa, c->qb, c->pacc};
     if (na) rc = leja_run<double>(c, B, p2, g, delta * delta, 1, K);
     if (!rc) rc = leja_run<double>(c, B, p1, v, delta, s, K);
   }
@@ -1021,7 +983,7 @@ int erem_create(const erem_grid* g, void* stream, erem_ctx** out) {
   rc |= dev_alloc(c, &c->pres_lo, n);
   rc |= dev_alloc(c, &c->pdelta, n);
   rc |= dev_alloc(c, &c->prhs, n);
-  rc |= dev_alloc(c, &c->part, static_cast<size_t>(kLejaRing) * leja_num_blocks(c->d));
+  rc |= dev_alloc(c, &c->part, leja_part_words(c->d));
   c->nstates = 64;
   rc |= dev_alloc(c, &c->cf, 2);  // phi1 and phi2 coefficient blocks
   rc |= dev_alloc(c, &c->states, c->nstates);

@@ -8,39 +8,71 @@
 namespace erem {
 
 constexpr int kLejaRing = 16;       // terms whose block partials are kept
-#ifndef EREM_LEJA_TILE_ROWS
-#define EREM_LEJA_TILE_ROWS 8
-#endif
-constexpr int kLejaTileRows = EREM_LEJA_TILE_ROWS;  // rows of the multi-term tile (64 wide)
-#ifndef EREM_LEJA_THREAD_ROWS
-#define EREM_LEJA_THREAD_ROWS 8
-#endif
-constexpr int kLejaThreadRows = EREM_LEJA_THREAD_ROWS;  // thread rows of its block (64 wide)
-constexpr int kCheckThreads = 1024;  // workgroup of the stop-test kernel
 constexpr int kCheckEvery = 4;      // terms between stop tests
+constexpr int kTermsPerPass2 = 4;   // terms per pass on 2D grids: one stop-test group
+// Rows per wavefront of the 2D pass: four while that gives at most kTermFew
+// workgroups (333 x 77: 188 us a phi1 action against 203 with eight), else
+// eight (512 x 512: 1.16 times the time with four, 1.09 times with sixteen),
+// more once the workgroups would pass kGateMax.
+constexpr int kTermRowsFew = 4, kTermRows = 8, kTermFew = 64;
+constexpr int kZmarchRows = 16;     // rows of the 3D pass's tile (64 wide)
+constexpr int kZmarchStrip = 2;     // cells per thread of its box
+constexpr int kZmarchThreads = 640;
+// Workgroups aimed at by the 3D pass: one per CU.  A chunk reads two planes of
+// the stencil and four of q more than it advances, so more, shorter chunks cost
+// what they hide (128^3: 3.50 ms a step against 4.33 with 512 workgroups; 256^3
+// 38.2 against 40.7 ms).
+constexpr int kZmarchBlocks = 256;
+constexpr int kInitBlocks = 2048;    // most workgroups of the start pass
+constexpr int kGateTerms = 5;       // most terms of one stop test (the first: terms 0 .. 4)
+constexpr int kGateMax = 2048;      // most partials per term that every workgroup adds up by itself
+constexpr int kFoldParts = 512;     // partials per term after a fold
 
-int leja_num_blocks(const Dims& d);
+// Stop test of terms k1 .. k2: the partials of term k1 + i are src[i][0 .. cnt[i]).
+struct LejaGate {
+  const double* src[kGateTerms];
+  int cnt[kGateTerms];
+  int k1, k2;
+};
+
+// Device vectors of the Newton passes in one precision: the stencil of J, the
+// two q buffers and the accumulated polynomial p.
+template <class V>
+struct LejaVecs {
+  const V* coef;
+  V *qa, *qb, *p;
+};
+
+// Newton terms computed by the launch that starts at term k of at most K.
+int leja_terms_per_launch(const Dims& d, int k, int K);
+// Partial slots of one term, and the words of a partial array.
+int leja_slots(const Dims& d);
+inline size_t leja_part_words(const Dims& d) {
+  return static_cast<size_t>(kLejaRing) * leja_slots(d) + kGateTerms * kFoldParts;
+}
 
 hipError_t launch_leja_reset(LejaState* st, int nslots, int nterms, hipStream_t s);
 template <class V>
 hipError_t launch_leja_init(const Dims& d, const LejaCoef* cf, const double* v, V* q0, V* p,
                             double* part, hipStream_t s);
+// One term, without a stop test (the adjoint's replay; the terms left over when
+// a budget is no multiple of a pass).
 template <class V>
 hipError_t launch_leja_term(const Dims& d, const LejaCoef* cf, const V* coef, const V* qin, V* qout,
                             V* p, const LejaState* st, double* part, int k, hipStream_t s,
                             hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
-// Terms k .. k + nterms - 1 in one launch (2D grids only, nterms 2 or 4):
-// the last q to qout, p updated, every term's partial sums in its ring slot.
+// One substep of at most K terms from src, with its stop tests into st:
+// out = (first ? 0 : out) + delta p (+ zt when zt is not null).  part:
+// leja_part_words(d).  ev, when not null: 2 K events, every prof-th launch
+// timed with the pair of its first term.
 template <class V>
-hipError_t launch_leja_terms(const Dims& d, const LejaCoef* cf, const V* coef, const V* qin, V* qout,
-                             V* p, const LejaState* st, double* part, int k, int nterms, hipStream_t s,
-                             hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
-hipError_t launch_leja_check(const Dims& d, const LejaCoef* cf, LejaState* st, const double* part,
-                             int k1, int k2, hipStream_t s);
-// u = (first ? 0 : u) + delta p (+ zt when zt is not null)
+hipError_t leja_substep(const Dims& d, const LejaCoef* cf, const LejaVecs<V>& B, const double* src, LejaState* st,
+                        double* part, int K, double* out, double delta, int first, const double* zt, hipStream_t s,
+                        hipEvent_t* ev, int prof);
+// u = (first ? 0 : u) + delta p
 template <class V>
 hipError_t launch_substep_update(const Dims& d, double* u, const V* p, double delta, int first,
-                                 hipStream_t s, const double* zt = nullptr);
+                                 hipStream_t s, LejaState* st);
 hipError_t launch_cast_f32(const double* a, float* b, long long n, hipStream_t s);
 
 // Coefficients of one Newton-Leja phi1 evaluation formed on the device from

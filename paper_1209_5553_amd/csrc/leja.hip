@@ -3,20 +3,24 @@
 //   q_0 = v,  p_0 = d_0 q_0,
 //   q_k = ((J - c I)/gamma - xi_{k-1} I) q_{k-1},  p_k = p_{k-1} + d_k q_k   (Eq. newt)
 //
-// One fused pass per term reads the stencil of J and q_{k-1}, updates p and
-// writes q_k; each block also stores its partial sum of q_k^2 (in FP64 in
-// both precisions).  A one-workgroup check kernel, launched after every few
-// terms, reduces those partials in a fixed order (so results are
-// reproducible bit for bit), forms the scaled error estimates
-// ||delta d_k q_k|| = |delta d_k| ||q_k||_2 / (sqrt(N) scal) and applies the
-// stop test 10^p * mean(last five estimates) < 1 (Sec. 4.2).  Once it holds,
-// later term launches return at entry.
+// One pass advances four terms (2D, k_leja_terms) or two (3D, k_leja_zmarch):
+// it reads the stencil of J, q_{k-1} and p, and writes p and the last q; every
+// workgroup also stores its partial sums of q_k^2 (in FP64 in both
+// precisions).  The stop test of the terms so far is made at the start of the
+// next pass by every workgroup alike, while its first loads are in flight
+// (leja_gate): the partials are added in a fixed order (so results are
+// reproducible bit for bit), the scaled error estimates ||delta d_k q_k|| =
+// |delta d_k| ||q_k||_2 / (sqrt(N) scal) formed, and 10^p * mean(last five
+// estimates) < 1 tested (Sec. 4.2), after every kCheckEvery terms.  Once it
+// holds, the first workgroup records it and later passes return at entry.
 //
 // Value type V is double (FP64 path) or float (mixed path: FP32 stencil,
 // vectors and accumulation; FP64 divided differences, norms and update).
 #include "device.h"
 #include "leja.h"
+#include "march.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace erem {
@@ -50,23 +54,73 @@ __global__ void k_leja_reset(LejaState* st, int nslots, int nterms) {
   }
 }
 
+// q_0 = v, p_0 = d_0 q_0: a copy, at most kInitBlocks workgroups so that term
+// 0 has few partials.
 template <class V>
-__global__ __launch_bounds__(kThreads) void k_leja_init(Dims d, const LejaCoef* __restrict__ cf,
+__global__ __launch_bounds__(kThreads) void k_leja_init(int N, const LejaCoef* __restrict__ cf,
                                               const double* __restrict__ v, V* __restrict__ q0,
                                               V* __restrict__ p, double* __restrict__ part) {
-  const int x = blockIdx.x * kBX + threadIdx.x;
-  const int y = blockIdx.y * kBY + threadIdx.y;
-  const int z = blockIdx.z;
+  const V d0 = to_v<V>(cf->dk[0]);
   double s = 0.0;
-  if (x < d.nx && y < d.ny) {
-    const int i = x + d.nx * (y + d.ny * z);
+  for (int i = blockIdx.x * kThreads + threadIdx.x; i < N; i += gridDim.x * kThreads) {
     const V vi = to_v<V>(v[i]);
     q0[i] = vi;
-    p[i] = to_v<V>(cf->dk[0]) * vi;
-    s = static_cast<double>(vi) * static_cast<double>(vi);
+    p[i] = d0 * vi;
+    s += static_cast<double>(vi) * static_cast<double>(vi);
   }
   s = block_sum256(s);
-  if (threadIdx.x == 0 && threadIdx.y == 0) part[block_id()] = s;  // ring slot 0
+  if (threadIdx.x == 0) part[blockIdx.x] = s;  // ring slot 0
+}
+
+// The stop test of terms g.k1 .. g.k2 (none when g.k2 < g.k1), made by the
+// whole workgroup (NW wavefronts): true when the evaluation has stopped, now or
+// before.  Wavefront w adds the partials of the terms k1 + w, k1 + w + NW, ...;
+// the estimates of the last nine terms are formed one per lane.  The leading
+// workgroup records the sums and the outcome; another workgroup of the same
+// launch that already reads the new flag comes to the same outcome by itself.
+template <int NW>
+__device__ inline bool leja_gate(const LejaCoef* __restrict__ cf, LejaState* st, const LejaGate& g, bool lead) {
+  const bool was = *(volatile const int*)&st->stopped >= 0;
+  if (g.k2 < g.k1) return was;
+  __shared__ double sh[kGateTerms];
+  const int tid = threadIdx.x + threadIdx.y * blockDim.x;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = g.k2 - g.k1 + 1;
+  const int j = g.k1 - 4 + lane;  // the lane's term (lanes 0 .. n + 3)
+  double old = 0.0, ef = 0.0;
+  if (lane < n + 4 && j >= 0) {
+    ef = cf->estf[j];
+    if (j < g.k1) old = st->sums[j];
+  }
+  for (int i = wave; i < n; i += NW) {
+    const double s = wave_part_sum(g.src[i], g.cnt[i]);
+    if (lane == 0) sh[i] = s;
+  }
+  __syncthreads();
+  if (was) return true;
+  // lanes 0 .. 3: the terms before k1; lanes 4 .. n + 3: the new ones, each
+  // testing the mean of its own and the four lanes below
+  const bool mine = lane >= 4 && lane < n + 4;
+  const double S = mine ? sh[lane - 4] : old;
+  const double est = ef * sqrt(S);
+  double mean = __shfl_up(est, 4, 64);
+  mean += __shfl_up(est, 3, 64);
+  mean += __shfl_up(est, 2, 64);
+  mean += __shfl_up(est, 1, 64);
+  mean += est;
+  const bool bad = mine && !isfinite(S);
+  const unsigned long long hit = __ballot(bad || (mine && j >= 4 && 0.2 * mean < cf->thresh));
+  const int stop = hit ? g.k1 - 4 + __ffsll(hit) - 1 : -1;  // the first term that passes
+  if (lead && tid < 64) {
+    const int last = stop >= 0 ? stop : g.k2;
+    if (mine && j <= last) st->sums[j] = S;
+    if (bad && j == stop) st->nonfinite = 1;
+    if (lane == 0) {
+      st->checked = last;
+      if (stop >= 0) st->stopped = stop;
+    }
+  }
+  return stop >= 0;
 }
 
 template <int DIM, class V>
@@ -111,209 +165,296 @@ __global__ __launch_bounds__(kThreads) void k_leja_term(Dims d, const LejaCoef* 
   if (threadIdx.x == 0 && threadIdx.y == 0) part[(k % kLejaRing) * nb + tile] = s;  // slot of the tile
 }
 
-// NT Newton terms in one pass (2D), NT = 2 or 4: q_{k-1} is staged in LDS on
-// the block's 64 x TY tile plus a halo of NT cells and the stencil on the
-// tile plus a halo of NT - 1; term k + t is then computed on the tile plus a
-// halo of NT - 1 - t, so the last one lands on the tile.  p gets d_k q_k,
-// then d_{k+1} q_{k+1}, ... (the order of single passes); the intermediate
-// q's never go to memory.  Each thread owns TY / 4 cells of the tile (rows
-// threadIdx.y, threadIdx.y + 4, ...).  The per-block partial sums of every
-// term's q^2 go to the term's ring slot in the slot layout of the one-term
-// kernel (one slot per 64 x 4 band): the block's sum in the slot of its first
-// band, zeros in the slots of its other bands, so the check kernel reduces
-// the same number of slots in the same order.
-template <int NT, int TY, int BY, class V>
-__global__ __launch_bounds__(kBX * BY) void k_leja_terms(Dims d, const LejaCoef* __restrict__ cf,
+// Four Newton terms in one pass on 2D grids (march.h): a workgroup's four
+// wavefronts take four consecutive chunks of rows of one strip, and leave one
+// partial per term.  On grids of up to 512 x 512 the pass is a chain of
+// latencies: launch, first rows, stop test, some 16 rows; 10 us with its stop
+// test, where a pass with LDS tiles (9 us) and a stop-test launch (6.6 us) took
+// 16 and two launch gaps.
+template <int NT, class V>
+__global__ __launch_bounds__(kThreads) void k_leja_terms(Dims d, const LejaCoef* __restrict__ cf,
                                                const V* __restrict__ coef, const V* __restrict__ qin,
-                                               V* __restrict__ qout, V* __restrict__ p,
-                                               const LejaState* __restrict__ st, double* __restrict__ part, int nb,
-                                               int k) {
-  static_assert(TY % BY == 0 && TY % kBY == 0, "whole thread rows and 64 x 4 bands per tile");
-  constexpr int NTH = kBX * BY;                     // threads
-  constexpr int R = TY / BY;                        // own cells per thread
-  constexpr int H = NT - 1;                         // halo of the stencil / intermediates
-  constexpr int WQ = kBX + 2 * NT, HQ = TY + 2 * NT;
-  constexpr int WI = kBX + 2 * H, HI = TY + 2 * H;
-  __shared__ V sq[HQ][WQ];           // q_{k-1}, halo NT
-  __shared__ V sc[5][HI][WI];        // stencil, halo NT - 1
-  __shared__ V sb[2][HI][WI];        // intermediates, halo NT - 1
-  const bool stopped = *(volatile const int*)&st->stopped >= 0;
-  const int nx = d.nx, ny = d.ny, N = d.N;
-  // plain placement: the eight XCDs take interleaved tile columns, each
-  // column's vertical halos stay in one L2 (measured slightly faster here
-  // than contiguous tile ranges per XCD)
-  const int bx = blockIdx.x, by = blockIdx.y;
-  const int x0 = bx * kBX, y0 = by * TY;
-  const int tid = threadIdx.x + threadIdx.y * kBX;
-  // every load of the tile is issued (into registers) before the first LDS
-  // store, so the tile waits for one memory latency instead of one per trip
-  constexpr int UQ = (HQ * WQ + NTH - 1) / NTH, UI = (HI * WI + NTH - 1) / NTH;
-  V rq[UQ], rc[5][UI];
-#pragma unroll
-  for (int u = 0; u < UQ; ++u) {
-    const int e = tid + u * NTH;
-    const int ly = e / WQ, lx = e - ly * WQ;
-    const int gx = x0 - NT + lx, gy = y0 - NT + ly;
-    rq[u] = (e < HQ * WQ && gx >= 0 && gx < nx && gy >= 0 && gy < ny) ? qin[gx + nx * gy] : V(0);
-  }
-#pragma unroll
-  for (int u = 0; u < UI; ++u) {
-    const int e = tid + u * NTH;
-    const int ly = e / WI, lx = e - ly * WI;
-    const int gx = x0 - H + lx, gy = y0 - H + ly;
-    const bool in = e < HI * WI && gx >= 0 && gx < nx && gy >= 0 && gy < ny;
-    const int j = gx + nx * gy;
-#pragma unroll
-    for (int c = 0; c < 5; ++c) rc[c][u] = in ? coef[c * N + j] : V(0);
-  }
-  const int gx = x0 + threadIdx.x;
-  V acc[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int gy = y0 + threadIdx.y + BY * r;
-    acc[r] = (gx < nx && gy < ny) ? p[gx + nx * gy] : V(0);
-  }
-#pragma unroll
-  for (int u = 0; u < UQ; ++u) {
-    const int e = tid + u * NTH;
-    if (e < HQ * WQ) sq[e / WQ][e % WQ] = rq[u];
-  }
-#pragma unroll
-  for (int u = 0; u < UI; ++u) {
-    const int e = tid + u * NTH;
-    if (e < HI * WI) {
-#pragma unroll
-      for (int c = 0; c < 5; ++c) sc[c][e / WI][e % WI] = rc[c][u];
-    }
-  }
-  if (stopped) return;  // stop test already passed
-  __syncthreads();
-  const V ig = to_v<V>(cf->inv_g);
-  double a[NT];
-  V last[R];
+                                               V* __restrict__ qout, V* __restrict__ p, LejaState* st,
+                                               double* __restrict__ part, LejaGate g, int stride, int rows, int k) {
+  constexpr int NW = kThreads / 64;
+  const int tile = xcd_tile_id();
+  const int strips = march_strips(d.nx, NT);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int y0 = ((tile / strips) * NW + wave) * rows, y1 = min(y0 + rows, d.ny);
+  V shift[NT], dk[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    const int h = H - t;  // halo of the region computed in this phase
-    const V sh = to_v<V>(cf->shift[k + t]);
-    const int w = kBX + 2 * h, hh = TY + 2 * h;
-    V(*out)[WI] = sb[t & 1];
-    for (int e = tid; e < w * hh; e += NTH) {
-      const int ry = e / w, rx = e - ry * w;
-      const int iy = ry + t, ix = rx + t;  // position in the halo-H buffers
-      V qc, qw, qe, qs, qn;
-      if (t == 0) {
-        qc = sq[iy + 1][ix + 1];
-        qw = sq[iy + 1][ix];
-        qe = sq[iy + 1][ix + 2];
-        qs = sq[iy][ix + 1];
-        qn = sq[iy + 2][ix + 1];
-      } else {
-        const V(*prev)[WI] = sb[(t - 1) & 1];
-        qc = prev[iy][ix];
-        qw = prev[iy][ix - 1];
-        qe = prev[iy][ix + 1];
-        qs = prev[iy - 1][ix];
-        qn = prev[iy + 1][ix];
-      }
-      V jq = sc[0][iy][ix] * qc;
-      jq += sc[1][iy][ix] * qw;
-      jq += sc[2][iy][ix] * qe;
-      jq += sc[3][iy][ix] * qs;
-      jq += sc[4][iy][ix] * qn;
-      out[iy][ix] = jq * ig - sh * qc;  // zero outside the grid (stencil and q are)
-    }
-    __syncthreads();
-    const V dk = to_v<V>(cf->dk[k + t]);
-    double sq2 = 0.0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int ly = threadIdx.y + BY * r;
-      const V qo = out[ly + H][threadIdx.x + H];
-      acc[r] += dk * qo;
-      if (gx < nx && y0 + ly < ny) sq2 += static_cast<double>(qo) * static_cast<double>(qo);
-      last[r] = qo;
-    }
-    a[t] = sq2;
+    shift[t] = march_uniform(to_v<V>(cf->shift[k + t]));
+    dk[t] = march_uniform(to_v<V>(cf->dk[k + t]));
   }
+  double sum[NT];
+  bool stop;
+  if (y0 < d.ny) {
+    stop = !march_terms<NT, 4, V>(coef, d.N, qin, qout, p, d.nx, d.ny, march_strip(d.nx, NT, tile % strips), y0, y1,
+                                  to_v<V>(cf->inv_g), shift, dk, sum, [&] { return leja_gate<NW>(cf, st, g, tile == 0); });
+  } else {
+    stop = leja_gate<NW>(cf, st, g, false);
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int gy = y0 + threadIdx.y + BY * r;
-    if (gx < nx && gy < ny) {
-      p[gx + nx * gy] = acc[r];
-      qout[gx + nx * gy] = last[r];
-    }
+    for (int t = 0; t < NT; ++t) sum[t] = 0.0;
   }
-  __shared__ double red[NT][BY];
+  if (stop) return;  // every wavefront of the workgroup alike
+  __shared__ double red[NT][NW];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    double v = a[t];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    if ((tid & 63) == 0) red[t][tid >> 6] = v;
+    const double v = march_sum(sum[t]);
+    if (lane == 0) red[t][wave] = v;
   }
   __syncthreads();
-  // slot layout of the one-term kernel: band b of this tile is global band
-  // by * NB + b, slot bx + gridDim.x * band
-  constexpr int NB = TY / kBY;  // 64 x 4 bands per tile
-  const int nbands = (ny + kBY - 1) / kBY;
-  for (int e = tid; e < NT * NB; e += NTH) {
-    const int t = e / NB, b = e - t * NB;
-    const int band = by * NB + b;
-    if (band < nbands) {
-      double sum = 0.0;
-      if (b == 0)
-        for (int w = 0; w < BY; ++w) sum += red[t][w];
-      part[((k + t) % kLejaRing) * nb + bx + gridDim.x * band] = sum;
-    }
+  if (threadIdx.x < NT) {
+    const int t = threadIdx.x;
+    part[((k + t) % kLejaRing) * stride + tile] = red[t][0] + red[t][1] + red[t][2] + red[t][3];
   }
 }
 
-// Reduce the partials of terms k1..k2 (in order), record their sums and
-// apply the stop test.  One workgroup of kCheckThreads threads.
-__global__ __launch_bounds__(kCheckThreads) void k_leja_check(const LejaCoef* __restrict__ cf, LejaState* st,
-                                                    const double* __restrict__ part, int nb, int k1, int k2) {
-  if (st->stopped >= 0) return;
-  __shared__ double sh[kCheckThreads / 64];
-  __shared__ int stop_sh;
-  for (int k = k1; k <= k2; ++k) {
-    const double* pk = part + (k % kLejaRing) * nb;
-    double v = 0.0;
-    for (int b = threadIdx.x; b < nb; b += kCheckThreads) v += pk[b];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double S = 0.0;
-      for (int w = 0; w < kCheckThreads / 64; ++w) S += sh[w];
-      st->sums[k] = S;
-      int stop = 0;
-      if (!isfinite(S)) {
-        st->nonfinite = 1;
-        stop = 1;
-      } else if (k >= 4) {
-        double mean = 0.0;
-        for (int j = k - 4; j <= k; ++j) mean += cf->estf[j] * sqrt(st->sums[j]);
-        mean *= 0.2;
-        stop = mean < cf->thresh;
+// Two Newton terms in one pass on 3D grids.  A workgroup holds a tile of 64 x
+// TY columns plus a halo of one (the box) and marches through a chunk of
+// planes: on the step that has plane z + 1 of q_{k-1}, term k is formed on
+// plane z of the box and term k + 1 on plane z - 1 of the tile.  A thread owns
+// SH cells of one box column and keeps their q, term-k values and stencil of
+// the planes it needs in registers; the x and y neighbours come from LDS (one
+// plane of q_{k-1} with a further halo, one plane of term k, each double
+// buffered, so a step has one barrier).  Loads of a plane are issued one step
+// ahead.  The multiply-adds are spelled out so that the terms round as in the
+// one-term pass whatever the compiler contracts.
+//
+// Bound by memory: per cell and pair of terms the seven stencil words, q_{k-1},
+// p in and out and the last q, 88 B where two one-term passes move 176.  On
+// 256^3 (FP64, 1.5 GB a pass, six times the Infinity Cache) 248 -> 133 us per
+// term, 5.5 TB/s; on 128^3 28 -> 19 us; on 50^3, where a launch costs more than
+// its bytes, 4.4 us and a stop-test launch per four terms -> 3.7 us.
+template <int TY, int SH, int NTH, class V>
+__global__ __launch_bounds__(NTH) void k_leja_zmarch(Dims d, const LejaCoef* __restrict__ cf,
+                                           const V* __restrict__ coef, const V* __restrict__ qin,
+                                           V* __restrict__ qout, V* __restrict__ p, LejaState* st,
+                                           double* __restrict__ part, LejaGate g, int stride, int zc, int k) {
+  constexpr int WB = kBX + 2, HB = TY + 2;   // box
+  constexpr int NW = NTH / 64;
+  constexpr int NS = (HB + SH - 1) / SH;     // strips of SH cells per box column
+  static_assert(NS * WB <= NTH && 2 * (WB + HB) <= NTH, "a thread per strip, a thread per ring cell");
+  constexpr int WQ = WB + 2, HQ = NS * SH + 2;  // q_{k-1}: one more cell around (strips may pass the box's top)
+  __shared__ V sq[2][HQ][WQ], s1[2][HQ][WQ];
+  const int tid = threadIdx.x;
+  const int nx = d.nx, ny = d.ny, nz = d.nz, N = d.N;
+  const int pl = nx * ny;
+  const int tx = (nx + kBX - 1) / kBX, ty = (ny + TY - 1) / TY;
+  const int tile = xcd_tile_id();
+  const int x0 = (tile % tx) * kBX, y0 = ((tile / tx) % ty) * TY;
+  const int z0 = (tile / (tx * ty)) * zc, z1 = min(z0 + zc, nz);
+  const bool act = tid < NS * WB;
+  const int bx = act ? tid % WB : 0, b0 = act ? (tid / WB) * SH : 0;  // box column, first box row
+  const int gx = x0 - 1 + bx;
+  const bool xin = act && gx >= 0 && gx < nx, xout = xin && bx >= 1 && bx <= kBX;
+  int cell[SH];          // clamped plane offset of each cell: every load is valid
+  bool in[SH], out[SH];  // in the grid; an output
+#pragma unroll
+  for (int r = 0; r < SH; ++r) {
+    const int by = b0 + r, gy = y0 - 1 + by;
+    in[r] = xin && by < HB && gy >= 0 && gy < ny;
+    out[r] = in[r] && xout && by >= 1 && by <= TY;
+    cell[r] = min(max(gx, 0), nx - 1) + nx * min(max(gy, 0), ny - 1);
+  }
+  // the ring around the box, one cell per thread: bottom, top, left, right
+  int rx = 0, ry = 0;
+  bool ring = false;
+  {
+    int e = tid;
+    if (e < 2 * WB) {
+      rx = e % WB + 1;
+      ry = e < WB ? 0 : HB + 1;
+      ring = true;
+    } else if (e < 2 * (WB + HB)) {
+      e -= 2 * WB;
+      ry = e % HB + 1;
+      rx = e < HB ? 0 : WB + 1;
+      ring = true;
+    }
+  }
+  const int rgx = x0 - 2 + rx, rgy = y0 - 2 + ry;
+  const bool rin = ring && rgx >= 0 && rgx < nx && rgy >= 0 && rgy < ny;
+  const int rcell = min(max(rgx, 0), nx - 1) + nx * min(max(rgy, 0), ny - 1);
+  auto plane = [&](int z) { return static_cast<long long>(min(max(z, 0), nz - 1)) * pl; };
+
+  V c0[SH][7], c1[SH][7];              // stencil of planes z - 1 and z (then z + 1)
+  V qm[SH], qc[SH], qp[SH], qr;        // q_{k-1} on planes z - 1, z, z + 1; the ring cell of z + 1
+  V tm[SH], tc[SH];                    // term k on planes z - 2, z - 1
+  V pc[SH], pn[SH];                    // p on planes z - 1, z
+  const int zs = z0 - 1;               // first plane of term k
+  {
+    const long long o0 = plane(zs - 1), o1 = plane(zs), o2 = plane(zs + 1);
+#pragma unroll
+    for (int r = 0; r < SH; ++r) {
+      qm[r] = qin[o0 + cell[r]];
+      qc[r] = qin[o1 + cell[r]];
+      qp[r] = qin[o2 + cell[r]];
+#pragma unroll
+      for (int e = 0; e < 7; ++e) c1[r][e] = coef[static_cast<long long>(e) * N + o1 + cell[r]];
+      pn[r] = tm[r] = tc[r] = pc[r] = V(0);  // plane z0 - 1 has no outputs
+#pragma unroll
+      for (int e = 0; e < 7; ++e) c0[r][e] = V(0);
+    }
+    const V q1 = rin ? qin[o1 + rcell] : V(0);
+    qr = rin ? qin[o2 + rcell] : V(0);
+#pragma unroll
+    for (int r = 0; r < SH; ++r) {
+      qm[r] = in[r] && zs >= 1 ? qm[r] : V(0);
+      qc[r] = in[r] && zs >= 0 ? qc[r] : V(0);
+      qp[r] = in[r] ? qp[r] : V(0);
+    }
+    if (leja_gate<NW>(cf, st, g, tile == 0)) return;
+    if (act) {
+#pragma unroll
+      for (int r = 0; r < SH; ++r) {
+        sq[zs & 1][b0 + r + 1][bx + 1] = qc[r];
+        s1[(zs & 1) ^ 1][b0 + r + 1][bx + 1] = V(0);
       }
-      if (stop) st->stopped = k;
-      st->checked = k;
-      stop_sh = stop;
+    }
+    if (ring) {
+      sq[zs & 1][ry][rx] = zs >= 0 ? q1 : V(0);
+      s1[0][ry][rx] = s1[1][ry][rx] = V(0);
     }
     __syncthreads();
-    if (stop_sh) return;
   }
+  const V ig = to_v<V>(cf->inv_g);
+  const V sh0 = to_v<V>(cf->shift[k]), sh1 = to_v<V>(cf->shift[k + 1]);
+  const V d0 = to_v<V>(cf->dk[k]), d1 = to_v<V>(cf->dk[k + 1]);
+  double a0 = 0.0, a1 = 0.0;
+  for (int z = zs; z <= z1; ++z) {
+    const int par = z & 1;
+    // the next plane's loads
+    V cn[SH][7], qn[SH], pf[SH], qrn = V(0);
+    const long long oq = plane(z + 2), oc = plane(z + 1);
+#pragma unroll
+    for (int r = 0; r < SH; ++r) {
+      qn[r] = pf[r] = V(0);
+#pragma unroll
+      for (int e = 0; e < 7; ++e) cn[r][e] = V(0);
+    }
+    if (z < z1) {
+#pragma unroll
+      for (int r = 0; r < SH; ++r) {
+        qn[r] = qin[oq + cell[r]];
+#pragma unroll
+        for (int e = 0; e < 7; ++e) cn[r][e] = coef[static_cast<long long>(e) * N + oc + cell[r]];
+        if (out[r] && z + 1 < z1) pf[r] = p[oc + cell[r]];
+      }
+      qrn = qin[oq + rcell];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const bool zin = z >= 0 && z < nz, wr = z - 1 >= z0;
+    V t1[SH];
+#pragma unroll
+    for (int r = 0; r < SH; ++r) {
+      // term k on plane z
+      const int ly = b0 + r + 1, lx = bx + 1;
+      V jq = c1[r][0] * qc[r];
+      jq = fma(c1[r][1], sq[par][ly][lx - 1], jq);
+      jq = fma(c1[r][2], sq[par][ly][lx + 1], jq);
+      jq = fma(c1[r][3], (r > 0 ? qc[r > 0 ? r - 1 : 0] : sq[par][ly - 1][lx]), jq);
+      jq = fma(c1[r][4], (r + 1 < SH ? qc[r + 1 < SH ? r + 1 : 0] : sq[par][ly + 1][lx]), jq);
+      jq = fma(c1[r][5], qm[r], jq);
+      jq = fma(c1[r][6], qp[r], jq);
+      const V v = fma(jq, ig, -(sh0 * qc[r]));
+      t1[r] = in[r] && zin ? v : V(0);
+    }
+    if (wr) {
+#pragma unroll
+      for (int r = 0; r < SH; ++r) {
+        // term k + 1 on plane z - 1
+        const int ly = b0 + r + 1, lx = bx + 1;
+        V jq = c0[r][0] * tc[r];
+        jq = fma(c0[r][1], s1[par ^ 1][ly][lx - 1], jq);
+        jq = fma(c0[r][2], s1[par ^ 1][ly][lx + 1], jq);
+        jq = fma(c0[r][3], (r > 0 ? tc[r > 0 ? r - 1 : 0] : s1[par ^ 1][ly - 1][lx]), jq);
+        jq = fma(c0[r][4], (r + 1 < SH ? tc[r + 1 < SH ? r + 1 : 0] : s1[par ^ 1][ly + 1][lx]), jq);
+        jq = fma(c0[r][5], tm[r], jq);
+        jq = fma(c0[r][6], t1[r], jq);
+        const V v = fma(jq, ig, -(sh1 * tc[r]));
+        if (out[r]) {
+          const long long o = static_cast<long long>(z - 1) * pl + cell[r];
+          p[o] = fma(d1, v, fma(d0, tc[r], pc[r]));
+          qout[o] = v;
+          a0 += static_cast<double>(tc[r]) * static_cast<double>(tc[r]);
+          a1 += static_cast<double>(v) * static_cast<double>(v);
+        }
+      }
+    }
+    if (act) {
+#pragma unroll
+      for (int r = 0; r < SH; ++r) {
+        s1[par][b0 + r + 1][bx + 1] = t1[r];
+        sq[par ^ 1][b0 + r + 1][bx + 1] = qp[r];
+      }
+    }
+    if (ring) sq[par ^ 1][ry][rx] = qr;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < SH; ++r) {
+      qm[r] = qc[r];
+      qc[r] = qp[r];
+      qp[r] = in[r] && z + 2 < nz ? qn[r] : V(0);
+      tm[r] = tc[r];
+      tc[r] = t1[r];
+      pc[r] = pn[r];
+      pn[r] = pf[r];
+#pragma unroll
+      for (int e = 0; e < 7; ++e) {
+        c0[r][e] = c1[r][e];
+        c1[r][e] = cn[r][e];
+      }
+    }
+    qr = rin && z + 2 < nz ? qrn : V(0);
+  }
+  __shared__ double red[2][NW];
+  for (int off = 32; off > 0; off >>= 1) {
+    a0 += __shfl_down(a0, off, 64);
+    a1 += __shfl_down(a1, off, 64);
+  }
+  if ((tid & 63) == 0) {
+    red[0][tid >> 6] = a0;
+    red[1][tid >> 6] = a1;
+  }
+  __syncthreads();
+  if (tid < 2) {
+    double s = red[tid][0];
+    for (int w = 1; w < NW; ++w) s += red[tid][w];
+    part[((k + tid) % kLejaRing) * stride + tile] = s;
+  }
+}
+
+// Partials of up to kGateTerms terms folded to kFoldParts each, for launches
+// with more workgroups than the gate should add up.
+__global__ __launch_bounds__(64) void k_leja_fold(const LejaState* st, LejaGate g, double* __restrict__ dst) {
+  if (*(volatile const int*)&st->stopped >= 0) return;
+  const int i = blockIdx.y, n = g.cnt[i];
+  const int per = (n + kFoldParts - 1) / kFoldParts;
+  const int b0 = min(n, static_cast<int>(blockIdx.x) * per);
+  const double s = wave_part_sum(g.src[i] + b0, min(per, n - b0));
+  if (threadIdx.x == 0) dst[i * kFoldParts + blockIdx.x] = s;
+}
+
+// The stop test on its own (one workgroup), where no pass follows that makes it.
+__global__ __launch_bounds__(kThreads) void k_leja_check(const LejaCoef* __restrict__ cf, LejaState* st, LejaGate g) {
+  (void)leja_gate<kThreads / 64>(cf, st, g, true);
 }
 
 // u = (first ? 0 : u) + delta * p (+ zt)  (FP64 update of the substep
-// increment; zt, when not null, is a fixed vector added on every substep)
+// increment; zt, when not null, is a fixed vector added on every substep).  The
+// last workgroup makes the stop test of the substep's last terms instead.
 template <class V>
-__global__ __launch_bounds__(kThreads) void k_substep_update(Dims d, double* __restrict__ u, const V* __restrict__ p,
-                                                   double delta, int first, const double* __restrict__ zt) {
-  const int x = blockIdx.x * kBX + threadIdx.x;
-  const int y = blockIdx.y * kBY + threadIdx.y;
-  const int z = blockIdx.z;
-  if (x >= d.nx || y >= d.ny) return;
-  const int i = x + d.nx * (y + d.ny * z);
+__global__ __launch_bounds__(kThreads) void k_substep_update(int N, double* __restrict__ u, const V* __restrict__ p,
+                                                   double delta, int first, const double* __restrict__ zt,
+                                                   const LejaCoef* __restrict__ cf, LejaState* st, LejaGate g) {
+  if (blockIdx.x + 1 == gridDim.x) {
+    (void)leja_gate<kThreads / 64>(cf, st, g, true);
+    return;
+  }
+  const int i = blockIdx.x * kThreads + threadIdx.x;
+  if (i >= N) return;
   const double pi = static_cast<double>(p[i]);
   double r = first ? delta * pi : u[i] + delta * pi;
   if (zt) r += zt[i];
@@ -530,10 +671,51 @@ __global__ __launch_bounds__(kCoefThreads) void k_leja_coef(LejaCoefArgs a) {
 
 }  // namespace
 
-int leja_num_blocks(const Dims& d) {
-  const dim3 g = cell_grid(d);
-  return static_cast<int>(g.x * g.y * g.z);
+namespace {
+
+// Rows per chunk of the 2D pass: short chunks while the grid leaves wavefront
+// slots idle, longer ones once the workgroups (and so the partials that every
+// workgroup adds up) would pass kGateMax.
+int terms_rows(const Dims& d) {
+  const long long strips = march_strips(d.nx, kTermsPerPass2);
+  if (strips * ((d.ny + 4 * kTermRowsFew - 1) / (4 * kTermRowsFew)) <= kTermFew) return kTermRowsFew;
+  int rows = kTermRows;
+  while (strips * ((d.ny + 4ll * rows - 1) / (4ll * rows)) > kGateMax && rows < d.ny &&
+         static_cast<long long>(d.nx) * (2 * rows + 2 * kTermsPerPass2) < (1ll << 27))
+    rows *= 2;
+  return rows;
 }
+
+// Planes per chunk of the 3D pass: about kZmarchBlocks workgroups.
+int zmarch_planes(const Dims& d) {
+  const long long xy = static_cast<long long>((d.nx + kBX - 1) / kBX) * ((d.ny + kZmarchRows - 1) / kZmarchRows);
+  const long long chunks = std::max(1ll, std::min<long long>(d.nz, kZmarchBlocks / xy));
+  return static_cast<int>((d.nz + chunks - 1) / chunks);
+}
+
+int terms_blocks(const Dims& d) {
+  if (d.dim == 2) {
+    const long long rows = terms_rows(d);
+    return static_cast<int>(march_strips(d.nx, kTermsPerPass2) * ((d.ny + 4 * rows - 1) / (4 * rows)));
+  }
+  const int zc = zmarch_planes(d);
+  return static_cast<int>(((d.nx + kBX - 1) / kBX) * ((d.ny + kZmarchRows - 1) / kZmarchRows) *
+                          ((d.nz + zc - 1) / zc));
+}
+
+int init_blocks(const Dims& d) { return std::min(kInitBlocks, (d.N + kThreads - 1) / kThreads); }
+
+}  // namespace
+
+int leja_terms_per_launch(const Dims& d, int k, int K) {
+  if (d.dim == 2) {
+    // the 2D pass addresses a chunk's rows with 31-bit byte offsets
+    return k + kTermsPerPass2 - 1 <= K && d.nx <= (1 << 22) ? kTermsPerPass2 : 1;
+  }
+  return k + 1 <= K ? 2 : 1;
+}
+
+int leja_slots(const Dims& d) { return std::max(cell_bands(d), std::max(terms_blocks(d), kInitBlocks)); }
 
 hipError_t launch_leja_reset(LejaState* st, int nslots, int nterms, hipStream_t s) {
   hipLaunchKernelGGL(k_leja_reset, dim3(nslots < 64 ? nslots : 64), dim3(256), 0, s, st, nslots, nterms);
@@ -543,14 +725,14 @@ hipError_t launch_leja_reset(LejaState* st, int nslots, int nterms, hipStream_t 
 template <class V>
 hipError_t launch_leja_init(const Dims& d, const LejaCoef* cf, const double* v, V* q0, V* p, double* part,
                             hipStream_t s) {
-  hipLaunchKernelGGL(k_leja_init<V>, cell_grid(d), cell_block(), 0, s, d, cf, v, q0, p, part);
+  hipLaunchKernelGGL(k_leja_init<V>, dim3(init_blocks(d)), dim3(kThreads), 0, s, d.N, cf, v, q0, p, part);
   return hipGetLastError();
 }
 
 template <class V>
 hipError_t launch_leja_term(const Dims& d, const LejaCoef* cf, const V* coef, const V* qin, V* qout, V* p,
                             const LejaState* st, double* part, int k, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  const int nb = leja_num_blocks(d);
+  const int nb = leja_slots(d);
   if (d.dim == 3)
     launch_timed(k_leja_term<3, V>, cell_grid(d), cell_block(), 0, s, e0, e1, d, cf, coef, qin, qout, p, st, part,
                  nb, k);
@@ -560,34 +742,101 @@ hipError_t launch_leja_term(const Dims& d, const LejaCoef* cf, const V* coef, co
   return hipGetLastError();
 }
 
+namespace {
+
 template <class V>
-hipError_t launch_leja_terms(const Dims& d, const LejaCoef* cf, const V* coef, const V* qin, V* qout, V* p,
-                             const LejaState* st, double* part, int k, int nterms, hipStream_t s, hipEvent_t e0,
-                             hipEvent_t e1) {
-  if (d.dim != 2) return hipErrorInvalidValue;
-  const dim3 g((d.nx + kBX - 1) / kBX, (d.ny + kLejaTileRows - 1) / kLejaTileRows, 1);
-  const dim3 blk(kBX, kLejaThreadRows, 1);
-  if (nterms == 4)
-    launch_timed(k_leja_terms<4, kLejaTileRows, kLejaThreadRows, V>, g, blk, 0, s, e0, e1, d, cf, coef, qin, qout, p,
-                 st, part, leja_num_blocks(d), k);
-  else if (nterms == 2)
-    launch_timed(k_leja_terms<2, kLejaTileRows, kLejaThreadRows, V>, g, blk, 0, s, e0, e1, d, cf, coef, qin, qout, p,
-                 st, part, leja_num_blocks(d), k);
+hipError_t launch_terms(const Dims& d, const LejaCoef* cf, const V* coef, const V* qin, V* qout, V* p, LejaState* st,
+                        double* part, const LejaGate& g, int k, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  const int nb = leja_slots(d);
+  if (d.dim == 2)
+    launch_timed(k_leja_terms<kTermsPerPass2, V>, dim3(terms_blocks(d)), dim3(kThreads), 0, s, e0, e1, d, cf, coef,
+                 qin, qout, p, st, part, g, nb, terms_rows(d), k);
   else
-    return hipErrorInvalidValue;
+    launch_timed(k_leja_zmarch<kZmarchRows, kZmarchStrip, kZmarchThreads, V>, dim3(terms_blocks(d)),
+                 dim3(kZmarchThreads), 0, s, e0, e1, d, cf, coef, qin, qout, p, st, part, g, nb, zmarch_planes(d), k);
   return hipGetLastError();
 }
 
-hipError_t launch_leja_check(const Dims& d, const LejaCoef* cf, LejaState* st, const double* part, int k1, int k2,
-                             hipStream_t s) {
-  hipLaunchKernelGGL(k_leja_check, dim3(1), dim3(kCheckThreads), 0, s, cf, st, part, leja_num_blocks(d), k1, k2);
+// Gate of terms k1 .. k2 whose partials the launches of leja_substep left; a
+// fold first when they are too many to be added by every workgroup.
+hipError_t make_gate(const Dims& d, LejaState* st, double* part, int k1, int k2, const int* cnt, LejaGate* g,
+                     hipStream_t s) {
+  const int nb = leja_slots(d);
+  g->k1 = k1;
+  g->k2 = k2;
+  int most = 0;
+  for (int i = 0; i <= k2 - k1; ++i) {
+    const int k = k1 + i;
+    g->src[i] = part + static_cast<size_t>(k % kLejaRing) * nb;
+    g->cnt[i] = cnt[k % kLejaRing];
+    most = std::max(most, g->cnt[i]);
+  }
+  if (most <= kGateMax) return hipSuccess;
+  double* dst = part + static_cast<size_t>(kLejaRing) * nb;
+  hipLaunchKernelGGL(k_leja_fold, dim3(kFoldParts, k2 - k1 + 1), dim3(64), 0, s, st, *g, dst);
+  for (int i = 0; i <= k2 - k1; ++i) {
+    g->src[i] = dst + i * kFoldParts;
+    g->cnt[i] = kFoldParts;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace
+
+template <class V>
+hipError_t leja_substep(const Dims& d, const LejaCoef* cf, const LejaVecs<V>& B, const double* src, LejaState* st,
+                        double* part, int K, double* out, double delta, int first, const double* zt, hipStream_t s,
+                        hipEvent_t* ev, int prof) {
+  hipError_t e = launch_leja_init<V>(d, cf, src, B.qa, B.p, part, s);
+  if (e != hipSuccess) return e;
+  int cnt[kLejaRing] = {};  // partials of the terms in the ring
+  cnt[0] = init_blocks(d);
+  const int nterms = terms_blocks(d), nterm = cell_bands(d);
+  V* cur = B.qa;
+  V* oth = B.qb;
+  int prev = -1;  // last term already tested
+  for (int k = 1, launch = 0; k <= K; ++launch) {
+    const int nt = leja_terms_per_launch(d, k, K);
+    const bool timed = ev && launch % prof == 0;
+    hipEvent_t e0 = timed ? ev[2 * (k - 1)] : nullptr, e1 = timed ? ev[2 * (k - 1) + 1] : nullptr;
+    LejaGate g{};
+    g.k1 = 0;
+    g.k2 = -1;
+    if (k > 1 && (k - 1) % kCheckEvery == 0) {
+      e = make_gate(d, st, part, prev + 1, k - 1, cnt, &g, s);
+      if (e != hipSuccess) return e;
+      prev = k - 1;
+    }
+    if (nt > 1) {
+      e = launch_terms<V>(d, cf, B.coef, cur, oth, B.p, st, part, g, k, s, e0, e1);
+    } else {
+      // the one-term pass only reads the flag: the test is made before it
+      if (g.k2 >= g.k1) {
+        hipLaunchKernelGGL(k_leja_check, dim3(1), dim3(kThreads), 0, s, cf, st, g);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+      }
+      e = launch_leja_term<V>(d, cf, B.coef, cur, oth, B.p, st, part, k, s, e0, e1);
+    }
+    if (e != hipSuccess) return e;
+    for (int t = 0; t < nt; ++t) cnt[(k + t) % kLejaRing] = nt > 1 ? nterms : nterm;
+    std::swap(cur, oth);
+    k += nt;
+  }
+  LejaGate g{};
+  e = make_gate(d, st, part, prev + 1, K, cnt, &g, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_substep_update<V>, dim3((d.N + kThreads - 1) / kThreads + 1), dim3(kThreads), 0, s, d.N, out,
+                     B.p, delta, first, zt, cf, st, g);
   return hipGetLastError();
 }
 
 template <class V>
 hipError_t launch_substep_update(const Dims& d, double* u, const V* p, double delta, int first, hipStream_t s,
-                                 const double* zt) {
-  hipLaunchKernelGGL(k_substep_update<V>, cell_grid(d), cell_block(), 0, s, d, u, p, delta, first, zt);
+                                 LejaState* st) {
+  LejaGate g{};
+  g.k2 = -1;
+  hipLaunchKernelGGL(k_substep_update<V>, dim3((d.N + kThreads - 1) / kThreads + 1), dim3(kThreads), 0, s, d.N, u, p,
+                     delta, first, nullptr, nullptr, st, g);
   return hipGetLastError();
 }
 
@@ -618,14 +867,12 @@ template hipError_t launch_leja_term<double>(const Dims&, const LejaCoef*, const
 template hipError_t launch_leja_term<float>(const Dims&, const LejaCoef*, const float*, const float*, float*, float*,
                                             const LejaState*, double*, int, hipStream_t, hipEvent_t, hipEvent_t);
 template hipError_t launch_substep_update<double>(const Dims&, double*, const double*, double, int, hipStream_t,
-                                                  const double*);
-template hipError_t launch_substep_update<float>(const Dims&, double*, const float*, double, int, hipStream_t,
-                                                 const double*);
-
-template hipError_t launch_leja_terms<double>(const Dims&, const LejaCoef*, const double*, const double*, double*,
-                                              double*, const LejaState*, double*, int, int, hipStream_t, hipEvent_t,
-                                              hipEvent_t);
-template hipError_t launch_leja_terms<float>(const Dims&, const LejaCoef*, const float*, const float*, float*, float*,
-                                             const LejaState*, double*, int, int, hipStream_t, hipEvent_t, hipEvent_t);
+                                                  LejaState*);
+template hipError_t leja_substep<double>(const Dims&, const LejaCoef*, const LejaVecs<double>&, const double*,
+                                         LejaState*, double*, int, double*, double, int, const double*, hipStream_t,
+                                         hipEvent_t*, int);
+template hipError_t leja_substep<float>(const Dims&, const LejaCoef*, const LejaVecs<float>&, const double*,
+                                        LejaState*, double*, int, double*, double, int, const double*, hipStream_t,
+                                        hipEvent_t*, int);
 
 }  // namespace erem

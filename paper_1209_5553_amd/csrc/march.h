@@ -108,11 +108,12 @@ __device__ inline double march_sum(double v) {
 // One strip's chunk of rows [y0, y1) by NT terms.  coef (five arrays, stride
 // cs), qin, qout and p start at the grid's first cell; shift[t], dk[t] belong
 // to term t + 1 of the pass.  sum[t] gets the lane's share of sum q^2 over the
-// outputs.
-template <int NT, int PD, class V>
-__device__ inline void march_terms(const V* __restrict__ coef, long long cs, const V* __restrict__ qin,
+// outputs.  gate() runs once the first rows' loads are in flight; when it
+// returns true the pass ends there, with nothing written.
+template <int NT, int PD, class V, class Gate>
+__device__ inline bool march_terms(const V* __restrict__ coef, long long cs, const V* __restrict__ qin,
                                    V* __restrict__ qout, V* __restrict__ p, int nx, int ny, MarchStrip st, int y0,
-                                   int y1, V ig, const V (&shift)[NT], const V (&dk)[NT], double (&sum)[NT]) {
+                                   int y1, V ig, const V (&shift)[NT], const V (&dk)[NT], double (&sum)[NT], Gate&& gate) {
   constexpr int U = (NT + PD + 1) / 2 * 2;  // ring rows (even: the terms keep their last two rows by row parity)
   static_assert(PD >= 2 && NT >= 2, "rows ahead, terms");
   const int lane = threadIdx.x & 63;
@@ -160,6 +161,7 @@ __device__ inline void march_terms(const V* __restrict__ coef, long long cs, con
       march_load(rp, bo + static_cast<unsigned>(i) * rowb, pr[i]);
     }
   }
+  if (gate()) return false;
   int r = r0;
   const int rlast = r0 + steps - 1;
   for (;;) {
@@ -183,14 +185,14 @@ __device__ inline void march_terms(const V* __restrict__ coef, long long cs, con
         const V qc = t == 1 ? q0[(u + U - 1) % U] : Q[t - 2][(u + 1) & 1];
         const V qs = t == 1 ? q0[(u + U - 2) % U] : Q[t - 2][u & 1];
         const V qn = t == 1 ? q0[u] : nv[t - 2];
-        V jq = c[s][0] * qc;
-        jq += c[s][1] * west(qc);
-        jq += c[s][2] * east(qc);
-        jq += c[s][3] * qs;
-        jq += c[s][4] * qn;
-        const V qo = jq * ig - shift[t - 1] * qc;
+        V jq = c[s][1] * west(qc);
+        jq = fma(c[s][0], qc, jq);
+        jq = fma(c[s][2], east(qc), jq);
+        jq = fma(c[s][3], qs, jq);
+        jq = fma(c[s][4], qn, jq);
+        const V qo = fma(jq, ig, -(shift[t - 1] * qc));
         nv[t - 1] = qo;
-        pr[s] += dk[t - 1] * qo;
+        pr[s] = fma(dk[t - 1], qo, pr[s]);
         const int row = r - t;
         const double qm = march_mask(row >= y0 && row < y1, static_cast<double>(qo));
         sum[t - 1] += qm * qm;
@@ -208,6 +210,7 @@ __device__ inline void march_terms(const V* __restrict__ coef, long long cs, con
 done:
 #pragma unroll
   for (int t = 0; t < NT; ++t) sum[t] = out ? sum[t] : 0.0;
+  return true;
 }
 
 }  // namespace erem

@@ -33,7 +33,7 @@ constexpr int kNaSubsteps = 64;               // stop-state slots (max substeps)
 // the term partials (kLejaRing slots per block), the Newton coefficients, the
 // stop states, the reduction targets.
 constexpr size_t kNaVec = static_cast<size_t>(kNaMaxCells);
-constexpr size_t kNaPart = static_cast<size_t>(kLejaRing) * kNaMaxBlocks;
+constexpr size_t kNaPart = static_cast<size_t>(kLejaRing) * kNaMaxBlocks + kGateTerms * kFoldParts;
 constexpr size_t kNaCoefWords = (sizeof(LejaCoef) + 255) / 256 * 32;
 constexpr size_t kNaStateWords = (sizeof(LejaState) * kNaSubsteps + 255) / 256 * 32;
 constexpr size_t kNaRedWords = (sizeof(AsmReduce) + 255) / 256 * 32;
@@ -100,12 +100,6 @@ NaBufs carve(double* base) {
     if ((expr) != hipSuccess) return EREM_EDEVICE; \
   } while (0)
 
-int terms_per_launch(const Dims& d, int k, int K) {
-  if (d.dim != 2) return 1;
-  if (k + 3 <= K) return 4;
-  return k + 1 <= K ? 2 : 1;
-}
-
 // u <- h phi1(h J) v by s substeps of delta = h / s, at most K Newton terms
 // each: u_{j+1} = u_j + delta phi1(delta J)(v + J u_j).  EREM_ENOCONV when a
 // substep did not stop within K terms.
@@ -129,32 +123,15 @@ int leja_eval(const Dims& d, const NaBufs& B, const double* coef, const double* 
   }
   NA_TRY(hipMemcpyAsync(B.cf, &hc, sizeof(LejaCoef), hipMemcpyHostToDevice, st));
   NA_TRY(launch_leja_reset(B.states, s, K, st));
+  const LejaVecs<double> vecs{coef, B.qa, B.qb, B.p};
   for (int j = 0; j < s; ++j) {
-    LejaState* sj = B.states + j;
     const double* src = v;
     if (j > 0) {
       NA_TRY(launch_stencil_axpy(d, coef, v, B.u, B.w, st));
       src = B.w;
     }
-    NA_TRY(launch_leja_init<double>(d, B.cf, src, B.qa, B.p, B.part, st));
-    int prev = -1;
-    double* cur = B.qa;
-    double* oth = B.qb;
-    for (int k = 1; k <= K;) {
-      const int nt = terms_per_launch(d, k, K);
-      if (nt > 1)
-        NA_TRY(launch_leja_terms<double>(d, B.cf, coef, cur, oth, B.p, sj, B.part, k, nt, st));
-      else
-        NA_TRY(launch_leja_term<double>(d, B.cf, coef, cur, oth, B.p, sj, B.part, k, st));
-      std::swap(cur, oth);
-      k += nt;
-      const int last = k - 1;
-      if (last % kCheckEvery == 0 || last == K) {
-        NA_TRY(launch_leja_check(d, B.cf, sj, B.part, prev + 1, last, st));
-        prev = last;
-      }
-    }
-    NA_TRY(launch_substep_update<double>(d, B.u, B.p, delta, j == 0 ? 1 : 0, st));
+    NA_TRY(leja_substep<double>(d, B.cf, vecs, src, B.states + j, B.part, K, B.u, delta, j == 0 ? 1 : 0, nullptr, st,
+                                nullptr, 0));
   }
   // the hc copy must outlive the transfer; the stop states come back here
   NA_TRY(hipStreamSynchronize(st));
@@ -203,7 +180,7 @@ extern "C" int erem_phi1_apply_noalloc(const erem_grid* g, const double* d_coef,
   d.dx = g->dx;
   d.dy = g->dy;
   d.dz = g->dz;
-  if (leja_num_blocks(d) > kNaMaxBlocks) return EREM_EINVAL;
+  if (cell_bands(d) > kNaMaxBlocks || leja_slots(d) > kNaMaxBlocks) return EREM_EINVAL;
   double* base = nullptr;
   int rc = setup(&base);
   if (rc) return rc;

@@ -394,6 +394,53 @@ def test_ragged_and_degenerate_shapes(torch_mod, shape):
     assert rel_inf(T_gpu - prob.T0, T_ref - prob.T0) <= TOL
 
 
+@pytest.mark.parametrize("shape", [(64, 33, 1), (65, 17, 1), (120, 16, 1), (121, 31, 1), (65, 17, 3), (64, 16, 5),
+                                   (3, 33, 9), (66, 2, 18), (17, 18, 40)])
+@pytest.mark.parametrize("opts", [{}, {"m_max": 27}, {"precision": 1, "tol_r": 1e-7}])
+def test_newton_pass_edges_match_oracle(torch_mod, shape, opts):
+    """Grids at and beside the edges of the Newton passes' tiles (2D: strips
+    of 64 lanes, 56 of them new, by 4- and 8-row chunks; 3D: 64 x 16 columns by a
+    chunk of planes), with a term budget that is a multiple of a pass, one that is
+    not (27: the last terms go one at a time), and in FP32."""
+    from paper_1209_5553_amd.api import make_opts
+    nx, ny, nz = shape
+    rng = np.random.default_rng(nx * 1000 + ny * 10 + nz)
+    n = nx * ny * nz
+    logk = (inputs.layered_field(rng, nx, ny, nz) if nz > 1 else
+            np.log(1e-12) + 0.7 * rng.standard_normal(n))
+    prob = inputs.Problem(name=f"edges{shape}", nx=nx, ny=ny, nz=nz, logk=logk, poro=np.full(n, 0.2),
+                          T0=20.0 + 60.0 * rng.random(n), nsteps=2)
+    _say(f"edges {shape} {opts}")
+    # 1 MPa over a few cells is stiff: 64 substeps, the most allowed, of 27
+    # terms hold a sixteenth of the step
+    h = prob.h / 16 if "m_max" in opts else prob.h
+    T_gpu, _ = _run_gpu_linear(torch_mod, prob, 2, h=h, opts=make_opts(**opts))
+    T_ref, _ = oerem.run_linear(prob, nsteps=2, h=h, layered=nz > 1, tier="taylor")
+    assert rel_inf(T_gpu - prob.T0, T_ref - prob.T0) <= (1e-5 if "precision" in opts else TOL)
+
+
+def test_phi1_with_folded_stop_partials_matches_oracle(torch_mod):
+    """A single row of 116 000 cells is 2071 strips: more partials per term than
+    a pass adds up by itself, so they are folded first."""
+    torch = torch_mod
+    from paper_1209_5553_amd.api import EremContext, make_opts
+    n = 116000
+    rng = np.random.default_rng(3)
+    coef = np.zeros((5, n))
+    coef[1, 1:] = 1.0 + 0.3 * rng.random(n - 1)
+    coef[2, :-1] = 1.2 + 0.3 * rng.random(n - 1)
+    coef[0] = -2.9
+    v = rng.standard_normal(n)
+    ctx = EremContext(n, 1, device="cuda:0")
+    ctx.set_jacobian(_dev(torch, coef), torch.zeros(n, dtype=torch.float64, device="cuda:0"))
+    _say("phi1 on 116000 x 1")
+    h = 7.0
+    out, st = ctx.phi1_apply(h, _dev(torch, v), opts=make_opts())
+    _say(f"  {st}")
+    ref = ophi.hphi1_action_taylor(stencil_to_sparse(coef, n, 1, 1), v, h) / h
+    assert rel_inf(out.cpu().numpy(), ref) <= TOL
+
+
 def test_small_layered_3d(torch_mod):
     torch = torch_mod
     prob = inputs.layered3d_problem(10, seed=1, nsteps=2)

@@ -220,7 +220,7 @@ int build_mg(erem_ctx* c) {
       }
     }
     const size_t bytes = mg_lds_layout(h, lc, nullptr) * sizeof(double);
-    if (mg_set_lds_limit(static_cast<int>(bytes)) == hipSuccess) break;
+    if (mg_set_lds_limit(static_cast<int>(bytes), false) == hipSuccess) break;
     (void)hipGetLastError();
     if (attempt == 1) return fail(c, EREM_EDEVICE, "cannot reserve LDS for the coarse multigrid solve");
   }
@@ -248,6 +248,21 @@ int build_mg(erem_ctx* c) {
   h.lds_bytes = mg_lds_layout(h, lc, &a) * sizeof(double);
   for (int k = 0; k < a.nlev; ++k) a.lev[k] = h.lev[lc + k];
   h.coarse_threads = std::min(1024, ((a.n0 + 63) / 64) * 64);
+  // 2D hierarchies with two smoothed LDS levels keep them in registers, with
+  // the grid level above when it has at most kMgTopCells cells and is not the
+  // finest (whose legs carry the conjugate-gradient update)
+  h.lt = lc;
+  if (c->d.nz == 1 && a.nlev == 3) {
+    const bool top = lc >= 2 && static_cast<size_t>(h.lev[lc - 1].nx) * h.lev[lc - 1].ny <= kMgTopCells;
+    const size_t bytes = mg_coarse_2d_words(top) * sizeof(double);
+    if (bytes + 1024 <= static_cast<size_t>(max_lds) && mg_set_lds_limit(static_cast<int>(bytes), true) == hipSuccess) {
+      h.reg2d = true;
+      h.lds_bytes = bytes;
+      if (top) h.lt = lc - 1;
+    } else {
+      (void)hipGetLastError();
+    }
+  }
   // the coarse kernel gives each thread at most one cell of its first level
   if (h.coarse_threads < a.n0) return fail(c, EREM_EDEVICE, "coarse multigrid level larger than one workgroup");
   return EREM_OK;

@@ -21,6 +21,8 @@
 #include "device.h"
 #include "mg.h"
 
+#include <mutex>
+
 namespace erem {
 
 namespace {
@@ -988,6 +990,314 @@ __global__ __launch_bounds__(1024) void k_mg_coarse_lds(MgCoarseArgs a, const do
   }
 }
 
+// ---------------------------------------------------------------------------
+// The coarse solve of 2D hierarchies with two smoothed LDS levels above the
+// bottom (every grid that is not a thin strip): the same cycles as
+// k_mg_coarse_lds with the operands in registers.  A thread owns cell t of
+// each level and keeps the four transmissibilities scaled by 1/D (zero toward a
+// missing neighbour), D, the scaled right-hand side and its iterate; only the
+// iterates that neighbours read go through LDS, so a sweep is four LDS reads,
+// four multiply-adds, one LDS write and a barrier.  With TOP the level above
+// (at most 4 x 1024 cells, four per thread, smoothed by the grid levels' NU
+// weighted sweeps) is handled here too, which spares its two launches.
+//
+// Bound by its chain of about 60 barriered phases, 0.2 us each, and 3 us of
+// launch and loads: 17.3 us with a 64 x 64 top level, where k_mg_coarse_lds
+// (operands from LDS and a division of the cell index in every phase) took 24.1
+// us for the levels below it and the top level's two legs 14 us and two launch
+// gaps more.
+// ---------------------------------------------------------------------------
+struct CoarseCell {
+  double tw, te, ts, tn;   // transmissibility / D, zero toward a missing neighbour
+  double D, bp, e;         // diagonal, right-hand side / D, iterate
+};
+
+// Cell c of a level (a cell past its end: all zero, D = 1).
+__device__ inline void coarse_load(const MgLevelDev& L, int c, CoarseCell& q) {
+  const int nx = L.nx, ny = L.ny;
+  const bool in = c < nx * ny;
+  const int cc = in ? c : 0;
+  const int y = cc / nx, x = cc - y * nx;
+  const double tw = L.tx[fxi(nx, ny, x, y, 0)], te = L.tx[fxi(nx, ny, x + 1, y, 0)];
+  const double ts = L.ty[fyi(nx, ny, x, y, 0)], tn = L.ty[fyi(nx, ny, x, y + 1, 0)];
+  const double D = L.diag[cc];
+  q.D = in ? D : 1.0;
+  q.tw = in && x > 0 ? tw : 0.0;
+  q.te = in && x + 1 < nx ? te : 0.0;
+  q.ts = in && y > 0 ? ts : 0.0;
+  q.tn = in && y + 1 < ny ? tn : 0.0;
+  q.bp = q.e = 0.0;
+}
+
+__device__ inline int coarse_parent(const MgLevelDev& F, const MgLevelDev& C, int c) {
+  const int y = c / F.nx, x = c - y * F.nx;
+  return (x >> 1) + C.nx * (y >> 1);
+}
+
+__device__ inline void coarse_scale(CoarseCell& q) {
+  const double di = 1.0 / q.D;
+  q.tw *= di;
+  q.te *= di;
+  q.ts *= di;
+  q.tn *= di;
+}
+
+// (B + sum t v_nb) / D, v at the cell in a padded LDS array: a missing
+// neighbour reads some other entry or the padding and multiplies it by zero.
+__device__ inline double coarse_nb(const CoarseCell& q, const double* v, int nx) {
+  double s = fma(q.tw, v[-1], q.bp);
+  s = fma(q.te, v[1], s);
+  s = fma(q.ts, v[-nx], s);
+  return fma(q.tn, v[nx], s);
+}
+
+// Sum of the residuals of the (up to) 2 x 2 children of coarse cell (X, Y).
+__device__ inline double coarse_children(const double* r, int fnx, int fny, int X, int Y) {
+  const int x0 = 2 * X, y0 = 2 * Y;
+  const bool hx = x0 + 1 < fnx, hy = y0 + 1 < fny;
+  const int i = x0 + fnx * y0;
+  const double r00 = r[i], r10 = r[hx ? i + 1 : i], r01 = r[hy ? i + fnx : i], r11 = r[hx && hy ? i + fnx + 1 : i];
+  return r00 + (hx ? r10 : 0.0) + (hy ? r01 : 0.0) + (hx && hy ? r11 : 0.0);
+}
+
+// Sum over the 16 lanes of a DPP row; every lane gets it.
+template <int CTRL>
+__device__ inline double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return v + __hiloint2double(hi, lo);
+}
+__device__ inline double row_sum16(double v) {
+  v = dpp_add<0xB1>(v);   // quad_perm: lane ^ 1
+  v = dpp_add<0x4E>(v);   // quad_perm: lane ^ 2
+  v = dpp_add<0x141>(v);  // half mirror: the other quad of eight
+  return dpp_add<0x140>(v);  // mirror: the other eight of sixteen
+}
+
+// One double-buffered iterate of a level in LDS: a phase reads cur and writes
+// oth; turn() makes the written one current.
+struct CoarseBuf {
+  double *cur, *oth;
+  __device__ inline void turn() {
+    __syncthreads();
+    double* t = cur;
+    cur = oth;
+    oth = t;
+  }
+};
+
+template <int NU, bool TOP>
+__global__ __launch_bounds__(kMgLdsCells) void k_mg_coarse_2d(MgCoarseArgs a, MgLevelDev top,
+                                                              const double* __restrict__ bglob,
+                                                              const double* __restrict__ binv,
+                                                              double* __restrict__ out, PcgState* st, int rz_slot) {
+  constexpr int NT = TOP ? kMgTopCells / kMgLdsCells : 1;  // top cells per thread
+  constexpr int S = kMgLdsCells;
+  const bool stop = pcg_done(st);
+  extern __shared__ double smem[];
+  const int t = threadIdx.x;
+  const MgLevelDev &L0 = a.lev[0], &L1 = a.lev[1], &L2 = a.lev[2];
+  const int n0 = L0.nx * L0.ny, n1 = L1.nx * L1.ny, n2 = L2.nx * L2.ny;
+  const bool on0 = t < n0, on1 = t < n1, on2 = t < n2;
+  const int nxt = TOP ? top.nx : 0, nx0 = L0.nx, nx1 = L1.nx;
+  // LDS: the buffers (pointers to the thread's own cell), level 0's and then
+  // level 1's residuals, the bottom vectors
+  CoarseBuf b0, b1, bt;
+  double* p = smem;
+  auto take = [&](int cells, int pad) {
+    double* r = p + pad + t;
+    p += cells + 2 * pad;
+    return r;
+  };
+  b0.cur = take(S, kMgPad0);
+  b0.oth = take(S, kMgPad0);
+  b1.cur = take(S, kMgPad0);
+  b1.oth = take(S, kMgPad0);
+  bt.cur = bt.oth = nullptr;
+  if (TOP) {
+    bt.cur = take(kMgTopCells, kMgPadTop);
+    bt.oth = take(kMgTopCells, kMgPadTop);
+  }
+  double* rc = take(S, 0) - t;
+  double* bc = take(kMgBottomCells, 0) - t;
+  double* ebot = take(kMgBottomCells, 0) - t;
+  // loads first; with TOP those of the levels below go out behind the top
+  // level's first sweep (the registers do not hold everything in flight)
+  CoarseCell ct[NT], c0, c1;
+  if (TOP) {
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      coarse_load(top, t + k * S, ct[k]);
+      ct[k].bp = t + k * S < top.nx * top.ny ? bglob[t + k * S] : 0.0;
+    }
+  }
+  // bottom inverse: thread (row t / 16, columns 4 (t % 16) .. + 3)
+  const int br = t >> 4, bj = (t & 15) * 4;
+  double inv[4];
+  auto load_below = [&] {
+    coarse_load(L0, t, c0);
+    coarse_load(L1, t, c1);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) inv[k] = br < n2 && bj + k < n2 ? binv[br * n2 + bj + k] : 0.0;
+  };
+  if (!TOP) load_below();
+  const double bin = !TOP && on0 ? bglob[t] : 0.0;
+  const int par0 = on0 ? coarse_parent(L0, L1, t) : 0, par1 = on1 ? coarse_parent(L1, L2, t) : 0;
+  for (double* q = smem + t; q < p; q += S) *q = 0.0;  // padding and cells past a level's end
+  if (stop) return;
+  __syncthreads();
+  double B0 = bin;
+  if (TOP) {
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      coarse_scale(ct[k]);
+      ct[k].bp /= ct[k].D;
+      ct[k].e = sweep_weight<NU>(0) * ct[k].bp;
+      bt.oth[k * S] = ct[k].e;
+    }
+    bt.turn();
+    load_below();
+#pragma unroll
+    for (int s = 1; s < NU; ++s) {
+      const double w = sweep_weight<NU>(s);
+#pragma unroll
+      for (int k = 0; k < NT; ++k) {
+        ct[k].e += w * (coarse_nb(ct[k], bt.cur + k * S, nxt) - ct[k].e);
+        bt.oth[k * S] = ct[k].e;
+      }
+      bt.turn();
+    }
+#pragma unroll
+    for (int k = 0; k < NT; ++k)
+      bt.oth[k * S] = (coarse_nb(ct[k], bt.cur + k * S, nxt) - ct[k].e) * ct[k].D;  // residuals
+    bt.turn();
+    B0 = on0 ? coarse_children(bt.cur - t, top.nx, top.ny, t % nx0, t / nx0) : 0.0;
+    __syncthreads();
+    // the top level's right-hand side waits in LDS (its iterate is in bt.oth)
+#pragma unroll
+    for (int k = 0; k < NT; ++k) bt.cur[k * S] = ct[k].bp;
+  }
+  coarse_scale(c0);
+  coarse_scale(c1);
+  c0.bp = B0 / c0.D;
+  double x0 = 0.0;
+#pragma unroll 1
+  for (int cyc = 0; cyc < a.ncyc; ++cyc) {
+    if (cyc > 0) {  // continue from the residual the cycle before left
+      x0 += c0.e;
+      c0.bp = coarse_nb(c0, b0.cur, nx0) - c0.e;
+    }
+    c0.e = kOmega * c0.bp;
+    *b0.oth = c0.e;
+    b0.turn();
+    c0.e += kOmega * (coarse_nb(c0, b0.cur, nx0) - c0.e);
+    *b0.oth = c0.e;
+    b0.turn();
+    rc[t] = (coarse_nb(c0, b0.cur, nx0) - c0.e) * c0.D;
+    __syncthreads();
+    double x1 = 0.0;
+#pragma unroll 1
+    for (int v = 0; v < a.ncyc1; ++v) {
+      if (on1) {
+        if (v == 0) {
+          c1.bp = coarse_children(rc, L0.nx, L0.ny, t % nx1, t / nx1) / c1.D;
+        } else {
+          x1 += c1.e;
+          c1.bp = coarse_nb(c1, b1.cur, nx1) - c1.e;
+        }
+        c1.e = kOmega * c1.bp;
+        *b1.oth = c1.e;
+      }
+      b1.turn();
+      if (on1) {
+        c1.e += kOmega * (coarse_nb(c1, b1.cur, nx1) - c1.e);
+        *b1.oth = c1.e;
+      }
+      b1.turn();
+      if (on1) rc[t] = (coarse_nb(c1, b1.cur, nx1) - c1.e) * c1.D;
+      __syncthreads();
+      if (on2) bc[t] = coarse_children(rc, L1.nx, L1.ny, t % L2.nx, t / L2.nx);
+      __syncthreads();
+      {
+        double s = inv[0] * bc[bj];
+        s = fma(inv[1], bc[bj + 1], s);
+        s = fma(inv[2], bc[bj + 2], s);
+        s = fma(inv[3], bc[bj + 3], s);
+        s = row_sum16(s);
+        if ((t & 15) == 0) ebot[br] = s;
+      }
+      __syncthreads();
+      if (on1) {
+        c1.e = fma(a.omega_c, ebot[par1], c1.e);
+        *b1.oth = c1.e;
+      }
+      b1.turn();
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        if (on1) {
+          c1.e += kOmega * (coarse_nb(c1, b1.cur, nx1) - c1.e);
+          // the last value is the level's whole correction, for level 0
+          *b1.oth = s == 1 && v + 1 == a.ncyc1 ? c1.e + x1 : c1.e;
+        }
+        b1.turn();
+      }
+    }
+    c0.e = fma(a.omega_c, (b1.cur - t)[par0], c0.e);
+    *b0.oth = c0.e;
+    b0.turn();
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      c0.e += kOmega * (coarse_nb(c0, b0.cur, nx0) - c0.e);
+      *b0.oth = s == 1 && cyc + 1 == a.ncyc ? c0.e + x0 : c0.e;
+      b0.turn();
+    }
+  }
+  if (TOP) {
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      const int c = t + k * S;
+      const int pk = c < top.nx * top.ny ? coarse_parent(top, L0, c) : 0;
+      ct[k].bp = bt.cur[k * S];
+      ct[k].e = fma(a.omega_c, (b0.cur - t)[pk], bt.oth[k * S]);
+      bt.oth[k * S] = ct[k].e;
+    }
+    bt.turn();
+#pragma unroll
+    for (int s = 1; s <= NU; ++s) {
+      const double w = sweep_weight<NU>(NU - s);
+#pragma unroll
+      for (int k = 0; k < NT; ++k) {
+        const int c = t + k * S;
+        ct[k].e += w * (coarse_nb(ct[k], bt.cur + k * S, nxt) - ct[k].e);
+        if (s < NU)
+          bt.oth[k * S] = ct[k].e;
+        else if (c < top.nx * top.ny)
+          out[c] = ct[k].e;
+      }
+      if (s < NU) bt.turn();
+    }
+    return;
+  }
+  double part = 0.0;
+  if (on0) {
+    const double v = c0.e + x0;
+    out[t] = v;
+    part = bin * v;
+  }
+  if (rz_slot < 0) return;
+  for (int off = 32; off > 0; off >>= 1) part += __shfl_down(part, off, 64);
+  __shared__ double sh[kMgLdsCells / 64];
+  if ((t & 63) == 0) sh[t >> 6] = part;
+  __syncthreads();
+  double* slots = st->rz + rz_slot * st->nb;
+  for (int k = t + 1; k < st->nb; k += kMgLdsCells) slots[k] = 0.0;
+  if (t == 0) {
+    double s = 0.0;
+    for (int w = 0; w < kMgLdsCells / 64; ++w) s += sh[w];
+    slots[0] = s;
+  }
+}
+
 }  // namespace
 
 hipError_t mg_setup(const MgHierarchy& h, hipStream_t s) {
@@ -1006,7 +1316,7 @@ hipError_t mg_setup(const MgHierarchy& h, hipStream_t s) {
 hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* st, int rz_slot, hipStream_t s,
                     const CgFuse* cg) {
   if (cg && !mg_fuses_cg(h)) return hipErrorInvalidValue;
-  const int lc = h.lc;
+  const int lc = h.lt;  // the first level of the one-workgroup solve
   auto grid_of = [](const MgLevelDev& L) {
     return dim3((L.nx + kBX - 1) / kBX, (L.ny + kBY - 1) / kBY, L.nz);
   };
@@ -1030,8 +1340,16 @@ hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* 
   {
     const double* b = lc == 0 ? r : h.lev[lc].b;
     double* out = lc == 0 ? z : h.lev[lc].x;
-    hipLaunchKernelGGL(k_mg_coarse_lds, dim3(1), dim3(h.coarse_threads), h.lds_bytes, s, h.coarse, b, h.binv,
-                       out, st, lc == 0 ? rz_slot : -1);
+    const int slot = lc == 0 ? rz_slot : -1;
+    if (h.reg2d && h.lt < h.lc)
+      hipLaunchKernelGGL((k_mg_coarse_2d<kMgSweeps, true>), dim3(1), dim3(kMgLdsCells), h.lds_bytes, s, h.coarse,
+                         h.lev[lc], b, h.binv, out, st, slot);
+    else if (h.reg2d)
+      hipLaunchKernelGGL((k_mg_coarse_2d<kMgSweeps, false>), dim3(1), dim3(kMgLdsCells), h.lds_bytes, s, h.coarse,
+                         h.lev[lc], b, h.binv, out, st, slot);
+    else
+      hipLaunchKernelGGL(k_mg_coarse_lds, dim3(1), dim3(h.coarse_threads), h.lds_bytes, s, h.coarse, b, h.binv,
+                         out, st, slot);
   }
   // The up leg reads its level's x at the neighbours, so it writes its result
   // to y (z on the finest level); the LDS solve leaves its result in x.
@@ -1059,13 +1377,21 @@ hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* 
 
 // The attribute belongs to the kernel, not to a context: keep the largest
 // size any context asked for.
-hipError_t mg_set_lds_limit(int bytes) {
-  static int granted = 0;
-  if (bytes <= granted) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mg_coarse_lds),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e == hipSuccess) granted = bytes;
-  return e;
+hipError_t mg_set_lds_limit(int bytes, bool reg2d) {
+  static std::mutex mu;
+  static int granted[2] = {0, 0};
+  std::lock_guard<std::mutex> lock(mu);
+  if (bytes <= granted[reg2d]) return hipSuccess;
+  const void* fn[2] = {reg2d ? reinterpret_cast<const void*>(&k_mg_coarse_2d<kMgSweeps, true>)
+                             : reinterpret_cast<const void*>(&k_mg_coarse_lds),
+                       reg2d ? reinterpret_cast<const void*>(&k_mg_coarse_2d<kMgSweeps, false>) : nullptr};
+  for (const void* f : fn) {
+    if (!f) continue;
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e != hipSuccess) return e;
+  }
+  granted[reg2d] = bytes;
+  return hipSuccess;
 }
 
 }  // namespace erem

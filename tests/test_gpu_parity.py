@@ -127,6 +127,14 @@ def test_multigrid_pressure_ragged_shapes(torch_mod, shape):
     assert st["est_err"] <= 1e-14
 
 
+@pytest.mark.parametrize("shape", [(32, 32), (64, 64), (128, 128), (130, 126), (97, 41), (257, 129), (116, 21)])
+def test_multigrid_pressure_level_edges(torch_mod, shape):
+    """Hierarchies whose one-workgroup solve starts on the finest level (32 x 32),
+    right under it (64 x 64), or takes in the grid level above its LDS levels (at
+    4096, 1056, 1029 and 2145 cells, the last level's threads partly idle)."""
+    test_multigrid_pressure_ragged_shapes(torch_mod, shape)
+
+
 def test_multigrid_pressure_3d_layered_is_analytic(torch_mod):
     torch = torch_mod
     prob = inputs.layered3d_problem(24, seed=3)

@@ -1007,7 +1007,10 @@ int erem_create(const erem_grid* g, void* stream, erem_ctx** out) {
   rc |= dev_alloc(c, &c->xi_dev, kMaxTerms + 1);
   rc |= dev_alloc(c, &c->ddc, 1);
   c->pcg_nb = cell_bands(c->d);
-  rc |= dev_alloc(c, &c->pcg_parts, pcg_parts_words(c->pcg_nb));
+  int nd = 0, nu = 0;
+  mg_cg_tiles(c->d.nx, c->d.ny, &nd, &nu);
+  if (c->d.nz != 1) nd = nu = 0;
+  rc |= dev_alloc(c, &c->pcg_parts, pcg_parts_words(c->pcg_nb, nd, nu));
   if (rc == EREM_OK) {
     if (hipHostMalloc(reinterpret_cast<void**>(&c->h_cf), 2 * sizeof(LejaCoef), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&c->h_states), sizeof(LejaState) * c->nstates, hipHostMallocDefault) != hipSuccess ||
@@ -1020,7 +1023,7 @@ int erem_create(const erem_grid* g, void* stream, erem_ctx** out) {
   if (rc == EREM_OK) {
     // the state's pointers into the partial slots, set once
     PcgState init{};
-    pcg_bind_parts(&init, c->pcg_parts, c->pcg_nb);
+    pcg_bind_parts(&init, c->pcg_parts, c->pcg_nb, nd, nu);
     if (hipMemcpy(c->pcg, &init, sizeof(PcgState), hipMemcpyHostToDevice) != hipSuccess) rc = EREM_EDEVICE;
   }
   if (rc != EREM_OK) {

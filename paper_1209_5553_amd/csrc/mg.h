@@ -85,6 +85,8 @@ struct CgFuse {
 };
 
 hipError_t mg_setup(const MgHierarchy& h, hipStream_t s);
+// Workgroups of the finest 2D legs (the partial slots of their sums).
+void mg_cg_tiles(int nx, int ny, int* nd, int* nu);
 // z = M^{-1} r.  With cg (only where mg_fuses_cg): see CgFuse; with
 // cg->update, r is the residual before the update and z = M^{-1} r_new.
 hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* st, int rz_slot,

@@ -275,385 +275,260 @@ __global__ __launch_bounds__(kThreads) void k_mg_up_smooth(MgLevelDev F, MgLevel
 }
 
 // ---------------------------------------------------------------------------
-// 2D forms of the two legs.  A block of 64 x 4 threads owns a tile of 64 x 8
-// cells (two rows per thread, so each thread holds a whole y pair of
-// aggregates).  Every global operand of the tile and its halo (two cells for
-// the first sweep, one for the second) is loaded into LDS in one phase, so the
-// chain of dependent memory latencies is a single one; the sweeps then run
-// from LDS.  Same arithmetic, in the same order, as the generic forms above.
-// ---------------------------------------------------------------------------
-constexpr int kTY = 8;           // tile rows (two per thread)
-
-// A 64 x kTY tile covers the 64 x 4 bands (bx, 2 by) and (bx, 2 by + 1) of
-// the finest grid: its partial goes to the first, zero to the second.
-__device__ inline void tile_band_store(double* slots, int nx, int ny, double v) {
-  const int gx = (nx + kBX - 1) / kBX, gyb = (ny + kBY - 1) / kBY;
-  const int b0 = blockIdx.x + gx * (2 * blockIdx.y);
-  slots[b0] = v;
-  if (2 * static_cast<int>(blockIdx.y) + 1 < gyb) slots[b0 + gx] = 0.0;
-}
-
-// Faces of the halo-H region: x faces of its rows (face gx of cell gx is its
-// -x face) and y faces of its columns.
-template <int H>
-struct TileFacesH {
-  double tx[kTY + 2 * H][kBX + 2 * H + 1];
-  double ty[kTY + 2 * H + 1][kBX + 2 * H];
-};
-using TileFaces = TileFacesH<1>;
-
-// Faces of a tile staged through registers: fetch issues every load (a
-// fixed number per thread), store writes them to LDS, so the loads of all
-// the tile's operands are in flight together instead of one loop trip after
-// another.
-template <int H>
-struct FaceRegs {
-  static constexpr int W = kBX + 2 * H, HH = kTY + 2 * H;
-  static constexpr int NX = HH * (W + 1), NY = (HH + 1) * W;
-  static constexpr int UX = (NX + kThreads - 1) / kThreads, UY = (NY + kThreads - 1) / kThreads;
-  double tx[UX], ty[UY];
-  __device__ inline void fetch(const MgLevelDev& L, int x0, int y0, int tid) {
-    const int nx = L.nx, ny = L.ny;
-#pragma unroll
-    for (int u = 0; u < UX; ++u) {
-      const int k = tid + u * kThreads;
-      const int ly = k / (W + 1), lx = k - ly * (W + 1);
-      const int gx = x0 - H + lx, gy = y0 - H + ly;
-      tx[u] = (k < NX && gx >= 0 && gx <= nx && gy >= 0 && gy < ny) ? L.tx[fxi(nx, ny, gx, gy, 0)] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < UY; ++u) {
-      const int k = tid + u * kThreads;
-      const int ly = k / W, lx = k - ly * W;
-      const int gx = x0 - H + lx, gy = y0 - H + ly;
-      ty[u] = (k < NY && gx >= 0 && gx < nx && gy >= 0 && gy <= ny) ? L.ty[fyi(nx, ny, gx, gy, 0)] : 0.0;
-    }
-  }
-  __device__ inline void store(TileFacesH<H>& F, int tid) const {
-#pragma unroll
-    for (int u = 0; u < UX; ++u) {
-      const int k = tid + u * kThreads;
-      if (k < NX) F.tx[k / (W + 1)][k % (W + 1)] = tx[u];
-    }
-#pragma unroll
-    for (int u = 0; u < UY; ++u) {
-      const int k = tid + u * kThreads;
-      if (k < NY) F.ty[k / W][k % W] = ty[u];
-    }
-  }
-};
-
-// Neighbour sum of the halo-H cell (lx, ly) at (gx, gy), values v in a
-// region whose element (sy, sx) is that cell.
-template <int W, int H>
-__device__ inline double nb_sum_tile(const TileFacesH<H>& F, int nx, int ny, int gx, int gy, int lx, int ly,
-                                     const double (*v)[W], int sy, int sx) {
-  double s = 0.0;
-  if (gx > 0) s += F.tx[ly][lx] * v[sy][sx - 1];
-  if (gx + 1 < nx) s += F.tx[ly][lx + 1] * v[sy][sx + 1];
-  if (gy > 0) s += F.ty[ly][lx] * v[sy - 1][sx];
-  if (gy + 1 < ny) s += F.ty[ly + 1][lx] * v[sy + 1][sx];
-  return s;
-}
-
-// Tile arrays of the 2D legs: the 64 x 8 tile plus a halo of H cells.
-template <int H>
-struct Halo {
-  static constexpr int W = kBX + 2 * H;
-  static constexpr int R = kTY + 2 * H;
-};
-
-// One damped-Jacobi sweep, out = x + w (B - D x + sum t x_nb) / D, on the
-// tile plus a halo of h (cells outside the grid get zero); arrays in
-// halo-HA coordinates, faces of the halo-HF region (HF >= h, HA > h).
-template <int HA, int HF>
-__device__ inline void tile_sweep(int h, const TileFacesH<HF>& tf, const MgLevelDev& F, int x0, int y0, int tid,
-                                  const double (*sb)[Halo<HA>::W], const double (*sd)[Halo<HA>::W],
-                                  const double (*xin)[Halo<HA>::W], double (*xo)[Halo<HA>::W], double om) {
-  constexpr int W = Halo<HA>::W;
-  const int w = kBX + 2 * h, hh = kTY + 2 * h;
-  for (int k = tid; k < w * hh; k += kThreads) {
-    const int ry = k / w, rx = k - ry * w;
-    const int ly = ry + HA - h, lx = rx + HA - h;
-    const int gx = x0 - HA + lx, gy = y0 - HA + ly;
-    double v = 0.0;
-    if (gx >= 0 && gx < F.nx && gy >= 0 && gy < F.ny) {
-      const double D = sd[ly][lx];
-      const double xi = xin[ly][lx];
-      v = xi + om * (sb[ly][lx] - D * xi +
-                     nb_sum_tile<W>(tf, F.nx, F.ny, gx, gy, lx - (HA - HF), ly - (HA - HF), xin, ly, lx)) / D;
-    }
-    xo[ly][lx] = v;
-  }
-}
-
-// Down leg of a 2D level, fused: NU damped-Jacobi sweeps from zero (the
-// first, x1 = w B / D, needs no neighbours; sweep k runs on the tile plus a
-// halo of NU - k + 1 so that the neighbours' values are recomputed instead of
-// exchanged), then the restricted residual of the tile's aggregates.
+// 2D forms of the two legs.  A workgroup of 1024 threads holds a box of 64 x 16
+// cells, one per thread, a wavefront per row; the box is the workgroup's tile
+// plus a halo of H cells, so that every sweep needs only what the box holds
+// (each sweep's outer ring goes wrong by one cell).  A thread keeps its cell's
+// four transmissibilities scaled by 1/D, D, the scaled right-hand side and the
+// iterate in registers; the x neighbours come from the next lanes by DPP, the y
+// neighbours from LDS (double buffered: a barrier per sweep).
 //
-// With CG, iteration it of Chronopoulos-Gear conjugate gradients (one
-// reduction phase per iteration) is folded in front of the leg.  From the
-// slot sums of the previous leg pair: the stop test on ||r_it||, then
-// beta = g_it / g_{it-1}, alpha = g_it / (d_it - beta g_it / alpha_{it-1})
-// with g = r.z, d = w.z, w = A z (alpha = g_0 / d_0, beta = 0 at it = 0);
-// s = w + beta s_old and r_new = r - alpha s on the tile and its halo (the
-// halo values recomputed, the tile's written); p = z + beta p and
-// x += alpha p on the tile; the partial sums of r_new . r_new.
-template <int NU, bool CG>
-__global__ __launch_bounds__(kThreads) void k_mg_down_restrict_2d(MgLevelDev F, MgLevelDev C,
-                                                        const double* __restrict__ b, double* __restrict__ xout,
-                                                        double* __restrict__ bc, PcgState* st, CgFuse cg) {
-  static_assert(NU >= 2, "two sweeps at least");
-  constexpr int HA = NU;  // b, D (and the CG vectors) on the tile plus NU
-  constexpr int W = Halo<HA>::W, R = Halo<HA>::R;
-  const bool stop = pcg_done(st);
-  __shared__ double sb[R][W], sd[R][W], sx[2][R][W];
-  __shared__ double sw[CG ? R : 1][CG ? W : 1], ss[CG ? R : 1][CG ? W : 1];
-  __shared__ double alpha_sh, beta_sh;
-  __shared__ int stop_sh;
-  __shared__ TileFacesH<NU - 1> tf;
-  const int nx = F.nx, ny = F.ny;
-  const int tile = xcd_tile_id();  // 2D grid: tile = bx + gridDim.x * by
-  const int x0 = (tile % gridDim.x) * kBX, y0 = (tile / gridDim.x) * kTY;
-  const int tid = threadIdx.x + threadIdx.y * kBX;
-  const int it = cg.it;
-  // every load of the tile is issued (into registers) before the first LDS
-  // store: the cells' b, D (and w, s) on the tile plus NU, the faces, the
-  // tile's own x, z, p
-  constexpr int U = (R * W + kThreads - 1) / kThreads;
-  double rb[U], rd[U], rw[CG ? U : 1], rs[CG ? U : 1];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int k = tid + u * kThreads;
-    const int ly = k / W, lx = k - ly * W;
-    const int gx = x0 - HA + lx, gy = y0 - HA + ly;
-    const bool in = k < R * W && gx >= 0 && gx < nx && gy >= 0 && gy < ny;
-    const int j = gx + nx * gy;
-    rb[u] = in ? b[j] : 0.0;
-    rd[u] = in ? F.diag[j] : 1.0;
-    if (CG) {
-      rw[u] = in ? cg.w[j] : 0.0;
-      rs[u] = (in && it > 0) ? cg.s_old[j] : 0.0;
-    }
-  }
-  FaceRegs<NU - 1> fr;
-  fr.fetch(F, x0, y0, tid);
-  // the tile's own cells (two rows per thread) for the p and x updates
-  const int ox = x0 + threadIdx.x;
-  double xo[2] = {0.0, 0.0}, po[2] = {0.0, 0.0}, zo[2] = {0.0, 0.0};
-  if (CG) {
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int oy = y0 + 2 * threadIdx.y + r;
-      if (ox < nx && oy < ny) {
-        xo[r] = cg.x[ox + nx * oy];
-        zo[r] = cg.z[ox + nx * oy];
-        if (it > 0) po[r] = cg.p[ox + nx * oy];
-      }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int k = tid + u * kThreads;
-    if (k >= R * W) continue;
-    const int ly = k / W, lx = k - ly * W;
-    sb[ly][lx] = rb[u];
-    sd[ly][lx] = rd[u];
-    if (CG) {
-      sw[ly][lx] = rw[u];
-      ss[ly][lx] = rs[u];
-    } else {
-      sx[0][ly][lx] = sweep_weight<NU>(0) * rb[u] / rd[u];  // first sweep from zero
-    }
-  }
-  fr.store(tf, tid);
-  if (CG && tid < 64) {  // the first wavefront decides for the block
-    int halt = stop ? 1 : 0;
-    double alpha = 0.0, beta = 0.0;
-    const int nb = st->nb;
-    const double rr = wave_part_sum(st->rr + (it & 3) * nb, nb);
-    const double bb = wave_part_sum(st->bb_sl, nb);
-    const double g1 = wave_part_sum(st->rz + (it & 3) * nb, nb);
-    const double d1 = wave_part_sum(st->wz + (it & 3) * nb, nb);
-    const double g0 = it > 0 ? wave_part_sum(st->rz + ((it - 1) & 3) * nb, nb) : 1.0;
-    const bool lead = tile == 0;
-    if (halt) {
-      // an earlier iteration converged
-    } else if (!isfinite(rr)) {
-      halt = 1;
-      if (lead && tid == 0) { st->nonfinite = 1; st->done = 1; st->it_done = it; }
-    } else if (rr <= st->tol2 * bb) {
-      halt = 1;
-      if (lead && tid == 0) { st->done = 1; st->it_done = it; st->bb = bb; }
-    } else if (it > 0) {
-      beta = g1 / g0;
-      alpha = g1 / (d1 - beta * g1 / st->alpha[(it - 1) & 3]);
-    } else {
-      alpha = g1 / d1;
-    }
-    if (tid == 0) {
-      stop_sh = halt;
-      alpha_sh = alpha;
-      beta_sh = beta;
-    }
-    if (!halt && lead && tid == 0) st->alpha[it & 3] = alpha;
-  }
-  if (CG) {
-    // block (0, 0) may set the stop flag while this kernel runs, so every
-    // wavefront follows the first one's decision, not its own read
-    __syncthreads();
-    if (stop_sh) return;
-    const double alpha = alpha_sh, beta = beta_sh;
-    for (int k = tid; k < R * W; k += kThreads) {
-      const int ly = k / W, lx = k - ly * W;
-      const double sv = sw[ly][lx] + beta * ss[ly][lx];  // zero outside the grid stays zero
-      const double rn = sb[ly][lx] - alpha * sv;
-      ss[ly][lx] = sv;
-      sb[ly][lx] = rn;
-      sx[0][ly][lx] = sweep_weight<NU>(0) * rn / sd[ly][lx];  // first sweep from zero
-    }
-    __syncthreads();
-    double rr = 0.0;
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int ly = 2 * threadIdx.y + r, oy = y0 + ly;
-      if (ox < nx && oy < ny) {
-        const int j = ox + nx * oy;
-        const double rn = sb[ly + HA][threadIdx.x + HA];
-        const double pn = zo[r] + beta * po[r];
-        cg.r_new[j] = rn;
-        cg.s_new[j] = ss[ly + HA][threadIdx.x + HA];
-        cg.p[j] = pn;
-        cg.x[j] = xo[r] + alpha * pn;
-        rr += rn * rn;
-      }
-    }
-    for (int off = 32; off > 0; off >>= 1) rr += __shfl_down(rr, off, 64);
-    __shared__ double sh[kThreads / 64];
-    if ((tid & 63) == 0) sh[tid >> 6] = rr;
-    __syncthreads();
-    if (tid == 0) tile_band_store(st->rr + ((it + 1) & 3) * st->nb, nx, ny, sh[0] + sh[1] + sh[2] + sh[3]);
-  } else {
-    if (stop) return;
-    __syncthreads();
-  }
-#pragma unroll
-  for (int k = 2; k <= NU; ++k) {
-    tile_sweep<HA, NU - 1>(NU - k + 1, tf, F, x0, y0, tid, sb, sd, sx[(k - 2) & 1], sx[(k - 1) & 1],
-                           sweep_weight<NU>(k - 1));
-    __syncthreads();
-  }
-  const double(*fin)[W] = sx[(NU - 1) & 1];
-  const int gx = x0 + threadIdx.x;
-  double acc = 0.0;
-  for (int r = 0; r < 2; ++r) {
-    const int ly = 2 * threadIdx.y + r;
-    const int gy = y0 + ly;
-    if (gx < nx && gy < ny) {
-      const int sy = ly + HA, sxx = threadIdx.x + HA;
-      const double xi = fin[sy][sxx];
-      xout[gx + nx * gy] = xi;
-      acc += sb[sy][sxx] - sd[sy][sxx] * xi +
-             nb_sum_tile<W>(tf, nx, ny, gx, gy, sxx - (HA - (NU - 1)), sy - (HA - (NU - 1)), fin, sy, sxx);
-    }
-  }
-  acc += __shfl_xor(acc, 1, 64);
-  const int gy = y0 + 2 * threadIdx.y;
-  if ((threadIdx.x & 1) == 0 && gx < nx && gy < ny) bc[(gx >> 1) + C.nx * (gy >> 1)] = acc;
+// On grids of up to 512 x 512 the legs are chains of latencies (launch, one
+// round of loads, a barrier per sweep), which is why a sweep is as short as this;
+// the loads of a halo come from L2.  A down / up leg of 256 x 256 and 128 x 128
+// takes 3.9 / 4.1 us (6.9 / 7.4 with tiles of 64 x 8 on 256 threads, four cells a
+// thread, operands in LDS), the finest legs of 512 x 512 with their CG work 9.6 /
+// 9.6 us (15.8 / 11.3, the five sums of the CG step on one wavefront).
+// ---------------------------------------------------------------------------
+constexpr int kBoxR = 16;                 // box rows (64 columns wide)
+constexpr int kBoxT = kBX * kBoxR;        // threads
+
+// West / east neighbour's value (0 past the wavefront's ends).
+__device__ inline double box_w(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, true));
+}
+__device__ inline double box_e(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, true));
 }
 
-// Up leg of a 2D level, fused: the coarse correction v = x + w_c e[parent]
-// on the tile plus a halo of HU, then NU damped-Jacobi sweeps on shrinking
-// halos; the last lands on the tile (out = z) and, with rz_slot >= 0, b . z
-// goes to the CG ring.  With CG (the finest level of the Chronopoulos-Gear
-// form) every halo is one larger, so that the last sweep also covers the
-// halo-one ring and w = A z follows on the tile (w_out); the partial sums of
-// r.z and w.z go to the ring slot.
+// Operator of the thread's cell, scaled by 1/D; everything zero (D = 1) outside
+// the grid.  D is the sum of the cell's faces, as in the level's diagonal.
+struct BoxCell {
+  double tw, te, ts, tn, D, di;
+  __device__ inline void load(const MgLevelDev& L, int gx, int gy, bool in) {
+    const int nx = L.nx, ny = L.ny;
+    tw = in ? L.tx[fxi(nx, ny, gx, gy, 0)] : 0.0;
+    te = in ? L.tx[fxi(nx, ny, gx + 1, gy, 0)] : 0.0;
+    ts = in ? L.ty[fyi(nx, ny, gx, gy, 0)] : 0.0;
+    tn = in ? L.ty[fyi(nx, ny, gx, gy + 1, 0)] : 0.0;
+  }
+  __device__ inline void scale(const MgLevelDev& L, int gx, int gy, bool in) {
+    D = in ? tw + te + ts + tn : 1.0;
+    di = 1.0 / D;
+    tw = gx > 0 ? tw * di : 0.0;
+    te = gx + 1 < L.nx ? te * di : 0.0;
+    ts = gy > 0 ? ts * di : 0.0;
+    tn = gy + 1 < L.ny ? tn * di : 0.0;
+  }
+  // (b + sum t v_nb) / D for the scaled right-hand side bp; col: the thread's
+  // column of the LDS rows
+  __device__ inline double nb(double bp, double v, const double (*col)[kBX], int row, int lane) const {
+    double s = fma(tw, box_w(v), bp);
+    s = fma(te, box_e(v), s);
+    s = fma(ts, col[row][lane], s);         // rows are stored one down
+    return fma(tn, col[row + 2][lane], s);
+  }
+};
+
+// Down leg of a 2D level, fused: NU weighted Jacobi sweeps from zero (the first,
+// x1 = w b / D, needs no neighbours), then the restricted residual of the tile's
+// aggregates.
+//
+// With CG, iteration it of Chronopoulos-Gear conjugate gradients (one reduction
+// phase per iteration) is folded in front of the leg.  From the partial sums of
+// the previous leg pair (a wavefront per sum): the stop test on ||r_it||, then
+// beta = g_it / g_{it-1}, alpha = g_it / (d_it - beta g_it / alpha_{it-1}) with
+// g = r.z, d = w.z, w = A z (alpha = g_0 / d_0, beta = 0 at it = 0); s = w + beta
+// s_old and r_new = r - alpha s on the box (the halo values recomputed, the
+// tile's written); p = z + beta p and x += alpha p on the tile; the partial sum
+// of r_new . r_new.
 template <int NU, bool CG>
-__global__ __launch_bounds__(kThreads) void k_mg_up_smooth_2d(MgLevelDev F, MgLevelDev C, const double* __restrict__ b,
-                                                     const double* __restrict__ xv, const double* __restrict__ ec,
-                                                     double omega_c, double* __restrict__ out,
-                                                     double* __restrict__ w_out, PcgState* st, int rz_slot) {
-  constexpr int HU = NU + (CG ? 1 : 0);
-  constexpr int W = Halo<HU>::W, R = Halo<HU>::R;
+__global__ __launch_bounds__(kBoxT) __attribute__((amdgpu_waves_per_eu(8))) void k_mg_down_restrict_2d(
+    MgLevelDev F, MgLevelDev C, const double* __restrict__ b, double* __restrict__ xout, double* __restrict__ bc,
+    PcgState* st, CgFuse cg) {
+  static_assert(NU >= 2, "two sweeps at least");
+  constexpr int H = NU, TX = kBX - 2 * H, TR = kBoxR - 2 * H;
   const bool stop = pcg_done(st);
-  __shared__ double sxc[R][W], sb[R][W], sd[R][W], sy[2][R][W];
-  __shared__ TileFacesH<HU - 1> tf;
+  __shared__ double e[2][kBoxR + 2][kBX];
+  __shared__ double sums[5];
+  __shared__ double rrs[kBoxR];
   const int nx = F.nx, ny = F.ny;
-  const int tile = xcd_tile_id();  // 2D grid: tile = bx + gridDim.x * by
-  const int x0 = (tile % gridDim.x) * kBX, y0 = (tile / gridDim.x) * kTY;
-  const int tid = threadIdx.x + threadIdx.y * kBX;
-  // every load of the tile is issued (into registers) before the first LDS store
-  constexpr int U = (R * W + kThreads - 1) / kThreads;
-  double rx[U], re[U], rb[U], rd[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int k = tid + u * kThreads;
-    const int ly = k / W, lx = k - ly * W;
-    const int gx = x0 - HU + lx, gy = y0 - HU + ly;
-    const bool in = k < R * W && gx >= 0 && gx < nx && gy >= 0 && gy < ny;
-    const int j = gx + nx * gy;
-    rx[u] = in ? xv[j] : 0.0;
-    re[u] = in ? ec[(gx >> 1) + C.nx * (gy >> 1)] : 0.0;
-    rb[u] = in ? b[j] : 0.0;
-    rd[u] = in ? F.diag[j] : 1.0;
+  const int lane = threadIdx.x & 63, row = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tiles_x = (nx + TX - 1) / TX;
+  const int tile = xcd_tile_id();
+  const int gx = (tile % tiles_x) * TX - H + lane, gy = (tile / tiles_x) * TR - H + row;
+  const bool in = gx >= 0 && gx < nx && gy >= 0 && gy < ny;
+  const bool own = in && lane >= H && lane < H + TX && row >= H && row < H + TR;
+  const int j = gx + nx * gy;
+  const int it = cg.it;
+  // every load first
+  double bp = in ? b[j] : 0.0, w = 0.0, s = 0.0, xo = 0.0, zo = 0.0, po = 0.0;
+  if (CG) {
+    w = in ? cg.w[j] : 0.0;
+    s = in && it > 0 ? cg.s_old[j] : 0.0;
+    if (own) {
+      xo = cg.x[j];
+      zo = cg.z[j];
+      po = it > 0 ? cg.p[j] : 0.0;
+    }
   }
-  FaceRegs<HU - 1> fr;
-  fr.fetch(F, x0, y0, tid);
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int k = tid + u * kThreads;
-    if (k >= R * W) continue;
-    const int ly = k / W, lx = k - ly * W;
-    const int gx = x0 - HU + lx, gy = y0 - HU + ly;
-    const bool in = gx >= 0 && gx < nx && gy >= 0 && gy < ny;
-    sxc[ly][lx] = in ? rx[u] + omega_c * re[u] : 0.0;
-    sb[ly][lx] = rb[u];
-    sd[ly][lx] = rd[u];
+  BoxCell q;
+  q.load(F, gx, gy, in);
+  if (row == 0 || row == kBoxR - 1) {  // rows beside the box
+    const int r = row == 0 ? 0 : kBoxR + 1;
+    e[0][r][lane] = e[1][r][lane] = 0.0;
   }
-  fr.store(tf, tid);
+  if (CG) {
+    if (row < 5) {
+      const double* src = row == 0   ? (it > 0 ? st->frr + (it & 3) * st->nd : st->rr)
+                          : row == 1 ? st->bb_sl
+                          : row == 2 ? st->frz + (it & 3) * st->nu
+                          : row == 3 ? st->fwz + (it & 3) * st->nu
+                                     : st->frz + ((it - 1) & 3) * st->nu;
+      const int n = row == 0 ? (it > 0 ? st->nd : st->nb) : row == 1 ? st->nb : st->nu;
+      const double v = row == 4 && it == 0 ? 1.0 : wave_part_sum(src, n);
+      if (lane == 0) sums[row] = v;
+    }
+    // every wavefront must take the same decision, so none uses its own reading
+    // of the flag, which workgroup 0 may set meanwhile
+    const double alpha_old = it > 0 ? st->alpha[(it - 1) & 3] : 1.0;
+    if (threadIdx.x == 0) rrs[0] = stop ? 1.0 : 0.0;
+    __syncthreads();
+    const bool was = rrs[0] != 0.0;
+    const double rr = sums[0], bb = sums[1], g1 = sums[2], d1 = sums[3], g0 = sums[4];
+    const bool bad = !isfinite(rr), conv = rr <= st->tol2 * bb;
+    if (was || bad || conv) {
+      if (!was && tile == 0 && threadIdx.x == 0) {
+        if (bad) st->nonfinite = 1;
+        else st->bb = bb;
+        st->it_done = it;
+        st->done = 1;
+      }
+      return;
+    }
+    const double beta = it > 0 ? g1 / g0 : 0.0;
+    const double alpha = it > 0 ? g1 / (d1 - beta * g1 / alpha_old) : g1 / d1;
+    if (tile == 0 && threadIdx.x == 0) st->alpha[it & 3] = alpha;
+    s = w + beta * s;  // zero outside the grid
+    bp = bp - alpha * s;
+    double rr2 = 0.0;
+    if (own) {
+      const double pn = zo + beta * po;
+      cg.r_new[j] = bp;
+      cg.s_new[j] = s;
+      cg.p[j] = pn;
+      cg.x[j] = xo + alpha * pn;
+      rr2 = bp * bp;
+    }
+    for (int off = 32; off > 0; off >>= 1) rr2 += __shfl_down(rr2, off, 64);
+    if (lane == 0) w = rr2;  // stored after the next barrier (rrs[0] is still being read)
+  } else if (stop) {
+    return;
+  }
+  q.scale(F, gx, gy, in);
+  bp *= q.di;
+  double x = sweep_weight<NU>(0) * bp;  // first sweep from zero
+  e[0][row + 1][lane] = x;
+  __syncthreads();
+  if (CG && lane == 0) rrs[row] = w;
+#pragma unroll
+  for (int k = 1; k < NU; ++k) {
+    x += sweep_weight<NU>(k) * (q.nb(bp, x, e[(k - 1) & 1], row, lane) - x);
+    e[k & 1][row + 1][lane] = x;
+    __syncthreads();
+  }
+  const double res = (q.nb(bp, x, e[(NU - 1) & 1], row, lane) - x) * q.D;
+  if (own) xout[j] = x;
+  const double pair = (own ? res : 0.0) + box_e(own ? res : 0.0);
+  e[NU & 1][row + 1][lane] = pair;
+  __syncthreads();
+  // aggregates start at even cells: lanes and rows at an even distance from H
+  if (own && ((lane - H) & 1) == 0 && ((row - H) & 1) == 0)
+    bc[(gx >> 1) + C.nx * (gy >> 1)] = pair + e[NU & 1][row + 2][lane];
+  if (CG && threadIdx.x == 0) {
+    double v = rrs[0];
+    for (int k = 1; k < kBoxR; ++k) v += rrs[k];
+    st->frr[((it + 1) & 3) * st->nd + tile] = v;
+  }
+}
+
+// Up leg of a 2D level, fused: the coarse correction v = x + w_c e[parent] on
+// the box, then NU weighted Jacobi sweeps; the last lands on the tile (out = z).
+// With CG (the finest level of the Chronopoulos-Gear form) the halo is one
+// larger, so that the last sweep also covers the ring around the tile and w = A z
+// follows on the tile (w_out); the partial sums of r.z and w.z go to the ring
+// slot.
+template <int NU, bool CG>
+__global__ __launch_bounds__(kBoxT) __attribute__((amdgpu_waves_per_eu(8))) void k_mg_up_smooth_2d(
+    MgLevelDev F, MgLevelDev C, const double* __restrict__ b, const double* __restrict__ xv,
+    const double* __restrict__ ec, double omega_c, double* __restrict__ out, double* __restrict__ w_out, PcgState* st,
+    int rz_slot) {
+  constexpr int H = NU + (CG ? 1 : 0), TX = kBX - 2 * H, TR = kBoxR - 2 * H;
+  const bool stop = pcg_done(st);
+  __shared__ double e[2][kBoxR + 2][kBX];
+  __shared__ double sh[2][kBoxR];
+  const int nx = F.nx, ny = F.ny;
+  const int lane = threadIdx.x & 63, row = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tiles_x = (nx + TX - 1) / TX;
+  const int tile = xcd_tile_id();
+  const int gx = (tile % tiles_x) * TX - H + lane, gy = (tile / tiles_x) * TR - H + row;
+  const bool in = gx >= 0 && gx < nx && gy >= 0 && gy < ny;
+  const bool own = in && lane >= H && lane < H + TX && row >= H && row < H + TR;
+  const int j = gx + nx * gy;
+  const double xi = in ? xv[j] : 0.0, ei = in ? ec[(gx >> 1) + C.nx * (gy >> 1)] : 0.0;
+  const double bi = in ? b[j] : 0.0;
+  BoxCell q;
+  q.load(F, gx, gy, in);
+  if (row == 0 || row == kBoxR - 1) {
+    const int r = row == 0 ? 0 : kBoxR + 1;
+    e[0][r][lane] = e[1][r][lane] = 0.0;
+  }
+  double x = xi + omega_c * ei;
+  e[0][row + 1][lane] = x;
   if (stop) return;
+  q.scale(F, gx, gy, in);
+  const double bp = bi * q.di;
   __syncthreads();
 #pragma unroll
   for (int k = 1; k <= NU; ++k) {
-    tile_sweep<HU, HU - 1>(HU - k, tf, F, x0, y0, tid, sb, sd, k == 1 ? sxc : sy[(k - 2) & 1], sy[(k - 1) & 1],
-                           sweep_weight<NU>(NU - k));
-    __syncthreads();
-  }
-  const double(*fin)[W] = sy[(NU - 1) & 1];
-  const int gx = x0 + threadIdx.x;
-  double g = 0.0, dz = 0.0;
-  for (int r = 0; r < 2; ++r) {
-    const int ly = 2 * threadIdx.y + r;
-    const int gy = y0 + ly;
-    if (gx < nx && gy < ny) {
-      const int syy = ly + HU, sxx = threadIdx.x + HU;
-      const double z = fin[syy][sxx];
-      out[gx + nx * gy] = z;
-      g += sb[syy][sxx] * z;
-      if (CG) {
-        const double w = sd[syy][sxx] * z - nb_sum_tile<W>(tf, nx, ny, gx, gy, sxx - 1, syy - 1, fin, syy, sxx);
-        w_out[gx + nx * gy] = w;
-        dz += w * z;
-      }
+    x += sweep_weight<NU>(NU - k) * (q.nb(bp, x, e[(k - 1) & 1], row, lane) - x);
+    if (k < NU || CG) {
+      e[k & 1][row + 1][lane] = x;
+      __syncthreads();
     }
   }
-  if (rz_slot < 0) return;
+  if (own) out[j] = x;
+  if (!CG) return;
+  double g = 0.0, dz = 0.0;
+  const double w = (x - q.nb(0.0, x, e[NU & 1], row, lane)) * q.D;
+  if (own) {
+    w_out[j] = w;
+    g = bi * x;
+    dz = w * x;
+  }
   for (int off = 32; off > 0; off >>= 1) {
     g += __shfl_down(g, off, 64);
-    if (CG) dz += __shfl_down(dz, off, 64);
+    dz += __shfl_down(dz, off, 64);
   }
-  __shared__ double sh[2][kThreads / 64];
-  if ((tid & 63) == 0) {
-    sh[0][tid >> 6] = g;
-    sh[1][tid >> 6] = dz;
+  if (lane == 0) {
+    sh[0][row] = g;
+    sh[1][row] = dz;
   }
   __syncthreads();
-  if (tid == 0) {
-    tile_band_store(st->rz + rz_slot * st->nb, nx, ny, sh[0][0] + sh[0][1] + sh[0][2] + sh[0][3]);
-    if (CG) tile_band_store(st->wz + rz_slot * st->nb, nx, ny, sh[1][0] + sh[1][1] + sh[1][2] + sh[1][3]);
+  if (threadIdx.x < 2) {
+    const int k = threadIdx.x;
+    double v = sh[k][0];
+    for (int r = 1; r < kBoxR; ++r) v += sh[k][r];
+    (k == 0 ? st->frz : st->fwz)[rz_slot * st->nu + tile] = v;
   }
+}
+
+// Tiles of the legs on a level (the boxes less their halo).
+int leg_tiles(int nx, int ny, int halo) {
+  const int tx = kBX - 2 * halo, tr = kBoxR - 2 * halo;
+  return ((nx + tx - 1) / tx) * ((ny + tr - 1) / tr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1311,6 +1186,11 @@ hipError_t mg_setup(const MgHierarchy& h, hipStream_t s) {
   return hipGetLastError();
 }
 
+void mg_cg_tiles(int nx, int ny, int* nd, int* nu) {
+  *nd = leg_tiles(nx, ny, kMgSweeps);
+  *nu = leg_tiles(nx, ny, kMgSweeps + 1);
+}
+
 // z = M^{-1} r on the finest level; with rz_slot >= 0 also accumulates r . z
 // into the CG ring.
 hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* st, int rz_slot, hipStream_t s,
@@ -1325,12 +1205,11 @@ hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* 
     const MgLevelDev& C = h.lev[l + 1];
     const double* b = l == 0 ? r : F.b;
     if (F.nz == 1) {
-      const dim3 g((F.nx + kBX - 1) / kBX, (F.ny + kTY - 1) / kTY, 1);
+      const dim3 g(leg_tiles(F.nx, F.ny, kMgSweeps));
       if (l == 0 && cg && cg->update)
-        hipLaunchKernelGGL((k_mg_down_restrict_2d<kMgSweeps, true>), g, cell_block(), 0, s, F, C, b, F.x, C.b, st,
-                           *cg);
+        hipLaunchKernelGGL((k_mg_down_restrict_2d<kMgSweeps, true>), g, dim3(kBoxT), 0, s, F, C, b, F.x, C.b, st, *cg);
       else
-        hipLaunchKernelGGL((k_mg_down_restrict_2d<kMgSweeps, false>), g, cell_block(), 0, s, F, C, b, F.x, C.b, st,
+        hipLaunchKernelGGL((k_mg_down_restrict_2d<kMgSweeps, false>), g, dim3(kBoxT), 0, s, F, C, b, F.x, C.b, st,
                            CgFuse{});
     } else {
       const dim3 g((F.nx + kBX - 1) / kBX, (F.ny + kBY - 1) / kBY, C.nz);
@@ -1360,13 +1239,12 @@ hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* 
     const double* ec = l + 1 == lc ? C.x : C.y;
     double* out = l == 0 ? z : F.y;
     if (F.nz == 1) {
-      const dim3 g((F.nx + kBX - 1) / kBX, (F.ny + kTY - 1) / kTY, 1);
       if (l == 0 && cg)
-        hipLaunchKernelGGL((k_mg_up_smooth_2d<kMgSweeps, true>), g, cell_block(), 0, s, F, C, b, F.x, ec, h.omega_c,
-                           out, cg->w_out, st, rz_slot);
+        hipLaunchKernelGGL((k_mg_up_smooth_2d<kMgSweeps, true>), dim3(leg_tiles(F.nx, F.ny, kMgSweeps + 1)),
+                           dim3(kBoxT), 0, s, F, C, b, F.x, ec, h.omega_c, out, cg->w_out, st, rz_slot);
       else
-        hipLaunchKernelGGL((k_mg_up_smooth_2d<kMgSweeps, false>), g, cell_block(), 0, s, F, C, b, F.x, ec, h.omega_c,
-                           out, nullptr, st, l == 0 ? rz_slot : -1);
+        hipLaunchKernelGGL((k_mg_up_smooth_2d<kMgSweeps, false>), dim3(leg_tiles(F.nx, F.ny, kMgSweeps)), dim3(kBoxT),
+                           0, s, F, C, b, F.x, ec, h.omega_c, out, nullptr, st, -1);
     } else {
       hipLaunchKernelGGL(k_mg_up_smooth, grid_of(F), cell_block(), 0, s, F, C, b, F.x, ec, h.omega_c, out, st,
                          l == 0 ? rz_slot : -1);

@@ -59,10 +59,10 @@ struct erem_ctx {
   float *coef32 = nullptr, *qa32 = nullptr, *qb32 = nullptr, *p32 = nullptr;
   bool coef32_valid = false;
   // Krylov basis (m+1 vectors), work vector, Hessenberg matrix, norm, coefficients
-  double *kV = nullptr, *kw = nullptr, *kH = nullptr, *kbeta = nullptr, *kc = nullptr, *kg = nullptr,
+  double *kV = nullptr, *kw = nullptr, *kH = nullptr, *kg = nullptr,
          *kpart = nullptr;
   int kry_m = 0;
-  std::vector<double> hH;
+  double* h_kH = nullptr;  // pinned: H and beta
   size_t nfx = 0, nfy = 0, nfz = 0;
 
   // device control blocks

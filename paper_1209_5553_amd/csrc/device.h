@@ -223,6 +223,29 @@ __device__ inline double wave_part_sum(const double* __restrict__ base, int n) {
   return __shfl(s, 0, 64);
 }
 
+// v of another lane of the wavefront by a DPP control word (0 past its ends).
+template <int CTRL>
+__device__ inline double dpp(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
+}
+
+// Sum over the lanes that agree in lane & 3; every such lane gets it.
+__device__ inline double sum_quads(double v) {
+  v += dpp<0x128>(v);  // row rotated by eight
+  v += dpp<0x124>(v);  // and by four
+  v += __shfl_xor(v, 16, 64);
+  return v + __shfl_xor(v, 32, 64);
+}
+
+// Wavefront sums of four values at once: lane l gets that of value l & 3.
+__device__ inline double sum4(const double (&v)[4], int lane) {
+  const bool b0 = lane & 1, b1 = lane & 2;
+  const double lo = (b0 ? v[1] : v[0]) + dpp<0xB1>(b0 ? v[0] : v[1]);  // lane ^ 1
+  const double hi = (b0 ? v[3] : v[2]) + dpp<0xB1>(b0 ? v[2] : v[3]);
+  return sum_quads((b1 ? hi : lo) + dpp<0x4E>(b1 ? lo : hi));          // lane ^ 2
+}
+
 // Ordered encoding of doubles for atomic min/max on 64-bit unsigned integers.
 __host__ __device__ inline unsigned long long ord_encode(double v) {
   union { double d; unsigned long long u; } c;

@@ -103,9 +103,11 @@ void free_all(erem_ctx* c) {
   float** fbufs[] = {&c->coef32, &c->qa32, &c->qb32, &c->p32};
   for (float** b : fbufs)
     if (*b) { (void)hipFree(*b); *b = nullptr; }
-  double** kbufs[] = {&c->kV, &c->kw, &c->kH, &c->kbeta, &c->kc, &c->kg, &c->kpart};
+  double** kbufs[] = {&c->kV, &c->kw, &c->kH, &c->kg, &c->kpart};
   for (double** b : kbufs)
     if (*b) { (void)hipFree(*b); *b = nullptr; }
+  if (c->h_kH) (void)hipHostFree(c->h_kH);
+  c->h_kH = nullptr;
   double** abufs[] = {&c->adj_q, &c->adj_u, &c->adj_seg, &c->adj_block};
   for (double** b : abufs)
     if (*b) { (void)hipFree(*b); *b = nullptr; }
@@ -546,25 +548,30 @@ int krylov_hphi1(erem_ctx* c, double h, const double* v, double scal, const erem
   if (m < 1 || m > kMaxKrylov) return fail(c, EREM_EINVAL, "krylov_m must be in [1, 64]");
   const size_t N = c->d.N;
   if (c->kry_m < m) {
-    double** kbufs[] = {&c->kV, &c->kw, &c->kH, &c->kbeta, &c->kc, &c->kg, &c->kpart};
+    double** kbufs[] = {&c->kV, &c->kw, &c->kH, &c->kg, &c->kpart};
     for (double** b : kbufs)
       if (*b) { (void)hipFree(*b); *b = nullptr; }
     int rc = EREM_OK;
-    rc |= dev_alloc(c, &c->kV, N * (m + 1));
+    rc |= dev_alloc(c, &c->kV, N * m);
     rc |= dev_alloc(c, &c->kw, 2 * N);
-    rc |= dev_alloc(c, &c->kH, static_cast<size_t>(m + 1) * m);
-    rc |= dev_alloc(c, &c->kbeta, 1);
-    rc |= dev_alloc(c, &c->kc, m + 1);
+    // H, and beta behind it: one copy brings both to the host
+    rc |= dev_alloc(c, &c->kH, static_cast<size_t>(m + 1) * m + 1);
     rc |= dev_alloc(c, &c->kg, m + 1);
-    rc |= dev_alloc(c, &c->kpart, static_cast<size_t>(m + 1) * kry_num_blocks(c->d));
-    if (rc) return EREM_ENOMEM;
+    rc |= dev_alloc(c, &c->kpart, kry_part_words(c->d, m));
+    if (rc || hipHostMalloc(reinterpret_cast<void**>(&c->h_kH), sizeof(double) * (static_cast<size_t>(m + 1) * m + 1),
+                            hipHostMallocDefault) != hipSuccess)
+      return fail(c, EREM_ENOMEM, "no memory for the Krylov basis");
     c->kry_m = m;
   }
   const Dims& d = c->d;
   const double thresh = std::pow(10.0, -o->p_order);
   const double rootN = std::sqrt(static_cast<double>(N));
   const int max_halvings = 60;
-  c->hH.assign(static_cast<size_t>(m + 1) * m + 1, 0.0);
+    if (c->h_kH) (void)hipHostFree(c->h_kH);
+    c->h_kH = nullptr;
+    c->kry_m = 0;
+  const size_t nH = static_cast<size_t>(m + 1) * m;
+  const double* H = c->h_kH;
   double t = 0.0, delta = h;
   int nsub = 0, msum = 0;
   double last_est = 0.0;
@@ -573,15 +580,11 @@ int krylov_hphi1(erem_ctx* c, double h, const double* v, double scal, const erem
     if (nsub >= o->max_substeps)
       return fail(c, EREM_ENOCONV, "Krylov phi1 needs more than max_substeps substeps");
     // start vector v + J u (u = 0 on the first substep) into the first half of kw
-    if (first) HIP_TRY(c, hipMemcpyAsync(c->kw, v, N * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
-    else HIP_TRY(c, launch_stencil_axpy(d, c->coef, v, c->u, c->kw, c->stream));
-    HIP_TRY(c, arnoldi_cgs2(d, c->coef, c->kV, c->kw, c->kH, c->kbeta, c->kg, c->kpart, m, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(c->hH.data(), c->kH, sizeof(double) * (m + 1) * m, hipMemcpyDeviceToHost, c->stream));
-    double beta = 0.0;
-    HIP_TRY(c, hipMemcpyAsync(&beta, c->kbeta, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, krylov_start(d, c->coef, v, first ? nullptr : c->u, c->kw, c->kpart, m, c->stream));
+    HIP_TRY(c, arnoldi_cgs2(d, c->coef, c->kV, c->kw, c->kH, c->kH + nH, c->kg, c->kpart, m, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(c->h_kH, c->kH, sizeof(double) * (nH + 1), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     if (!std::isfinite(beta)) return fail(c, EREM_ENONFINITE, "non-finite Krylov vector norm");
-    const std::vector<double>& H = c->hH;
     if (beta == 0.0) {
       // w = 0: u is a steady state of u' = J u + v, nothing changes any more
       if (first) HIP_TRY(c, launch_axpby(d, c->u, 0.0, v, 0.0, c->stream));
@@ -595,6 +598,7 @@ int krylov_hphi1(erem_ctx* c, double h, const double* v, double scal, const erem
     int me = m;
     bool exact = false;
     for (int j = 0; j < m; ++j) {
+    const double beta = H[nH];
       for (int i = 0; i <= j; ++i) {
         const double e = H[i * m + j];
         if (!std::isfinite(e)) return fail(c, EREM_ENONFINITE, "non-finite Hessenberg entry");
@@ -631,12 +635,13 @@ int krylov_hphi1(erem_ctx* c, double h, const double* v, double scal, const erem
       dl *= 0.5;
     }
     if (!ok) return fail(c, EREM_ENOCONV, "Krylov substep could not meet the tolerance");
-    std::vector<double> coeffs(n);
-    for (int i = 0; i < n; ++i) coeffs[i] = dl * beta * y[i];
-    HIP_TRY(c, hipMemcpyAsync(c->kc, coeffs.data(), sizeof(double) * n, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, krylov_combine(d, c->kV, n, c->kc, c->u, first ? 1 : 0, c->stream));
-    // the coefficient upload reuses a host vector: wait before it goes out of scope
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    // v_m (the last of m + 1) is still unnormalised in kw
+    KryCoef kc{};
+    kc.nv = std::min(n, m);
+    for (int i = 0; i < kc.nv; ++i) kc.c[i] = dl * beta * y[i];
+    kc.last = n > m ? 1 : 0;
+    if (kc.last) kc.clast = dl * beta * y[m] / H[static_cast<size_t>(m) * m + m - 1];
+    HIP_TRY(c, krylov_combine(d, c->kV, c->kw + (m & 1) * N, kc, c->u, first ? 1 : 0, c->stream));
     t += dl;
     delta = dl;
     first = false;

@@ -210,22 +210,26 @@ void dense_expm(int n, const double* A, double* E) {
   for (size_t i = 0; i < X.size(); ++i) X[i] = A[i] * scale;
   for (int i = 0; i < n; ++i)
     for (int j = 0; j < n; ++j) P[i * n + j] = (i == j) ? 1.0 : 0.0;
-  for (int k = 20; k >= 1; --k) {
+  // Q = L R, row by row over contiguous rows of R (each entry's terms still in
+  // the order of the inner index)
+  auto product = [&](const std::vector<double>& L, const std::vector<double>& R) {
+    std::fill(Q.begin(), Q.end(), 0.0);
     for (int i = 0; i < n; ++i)
-      for (int j = 0; j < n; ++j) {
-        double acc = 0.0;
-        for (int l = 0; l < n; ++l) acc += X[i * n + l] * P[l * n + j];
-        Q[i * n + j] = acc / k + (i == j ? 1.0 : 0.0);
+      for (int l = 0; l < n; ++l) {
+        const double a = L[i * n + l];
+        const double* r = &R[l * n];
+        double* q = &Q[i * n];
+        for (int j = 0; j < n; ++j) q[j] += a * r[j];
       }
+  };
+  for (int k = 20; k >= 1; --k) {
+    product(X, P);
+    for (int i = 0; i < n; ++i)
+      for (int j = 0; j < n; ++j) Q[i * n + j] = Q[i * n + j] / k + (i == j ? 1.0 : 0.0);
     std::swap(P, Q);
   }
   for (int q = 0; q < s; ++q) {
-    for (int i = 0; i < n; ++i)
-      for (int j = 0; j < n; ++j) {
-        double acc = 0.0;
-        for (int l = 0; l < n; ++l) acc += P[i * n + l] * P[l * n + j];
-        Q[i * n + j] = acc;
-      }
+    product(P, P);
     std::swap(P, Q);
   }
   for (size_t i = 0; i < P.size(); ++i) E[i] = P[i];

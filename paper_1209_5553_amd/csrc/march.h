@@ -22,6 +22,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "device.h"
+
 namespace erem {
 
 constexpr int kMarchLanes = 64;
@@ -76,12 +78,8 @@ __device__ inline int dpp_west(int v) { return __builtin_amdgcn_update_dpp(0, v,
 __device__ inline int dpp_east(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, true); }
 __device__ inline float west(float v) { return __int_as_float(dpp_west(__float_as_int(v))); }
 __device__ inline float east(float v) { return __int_as_float(dpp_east(__float_as_int(v))); }
-__device__ inline double west(double v) {
-  return __hiloint2double(dpp_west(__double2hiint(v)), dpp_west(__double2loint(v)));
-}
-__device__ inline double east(double v) {
-  return __hiloint2double(dpp_east(__double2hiint(v)), dpp_east(__double2loint(v)));
-}
+__device__ inline double west(double v) { return dpp<0x138>(v); }
+__device__ inline double east(double v) { return dpp<0x130>(v); }
 
 // A value every lane holds alike, in scalar registers.
 __device__ inline double march_uniform(double v) {

@@ -293,15 +293,9 @@ __global__ __launch_bounds__(kThreads) void k_mg_up_smooth(MgLevelDev F, MgLevel
 constexpr int kBoxR = 16;                 // box rows (64 columns wide)
 constexpr int kBoxT = kBX * kBoxR;        // threads
 
-// West / east neighbour's value (0 past the wavefront's ends).
-__device__ inline double box_w(double v) {
-  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, true),
-                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, true));
-}
-__device__ inline double box_e(double v) {
-  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, true),
-                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, true));
-}
+// West / east neighbour's value (0 past the wavefront's ends): wavefront shifts.
+__device__ inline double box_w(double v) { return dpp<0x138>(v); }
+__device__ inline double box_e(double v) { return dpp<0x130>(v); }
 
 // Operator of the thread's cell, scaled by 1/D; everything zero (D = 1) outside
 // the grid.  D is the sum of the cell's faces, as in the level's diagonal.
@@ -936,17 +930,11 @@ __device__ inline double coarse_children(const double* r, int fnx, int fny, int 
 }
 
 // Sum over the 16 lanes of a DPP row; every lane gets it.
-template <int CTRL>
-__device__ inline double dpp_add(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
-  return v + __hiloint2double(hi, lo);
-}
 __device__ inline double row_sum16(double v) {
-  v = dpp_add<0xB1>(v);   // quad_perm: lane ^ 1
-  v = dpp_add<0x4E>(v);   // quad_perm: lane ^ 2
-  v = dpp_add<0x141>(v);  // half mirror: the other quad of eight
-  return dpp_add<0x140>(v);  // mirror: the other eight of sixteen
+  v += dpp<0xB1>(v);            // quad_perm: lane ^ 1
+  v += dpp<0x4E>(v);            // quad_perm: lane ^ 2
+  v += dpp<0x141>(v);           // half mirror: the other quad of eight
+  return v + dpp<0x140>(v);     // mirror: the other eight of sixteen
 }
 
 // One double-buffered iterate of a level in LDS: a phase reads cur and writes

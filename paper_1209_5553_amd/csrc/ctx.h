@@ -41,7 +41,7 @@ struct erem_ctx {
   // (allocated on first use): solver vectors, stage vectors k_1..k_3, the
   // stage state Y, G(Y), the right-hand side, and a scratch stencil
   double *bc_r = nullptr, *bc_rhat = nullptr, *bc_p0 = nullptr, *bc_p1 = nullptr, *bc_v0 = nullptr,
-         *bc_v1 = nullptr, *bc_s = nullptr, *bc_t = nullptr;
+         *bc_v1 = nullptr, *bc_s = nullptr, *bc_t = nullptr, *bc_d = nullptr;
   double *rs_k0 = nullptr, *rs_k1 = nullptr, *rs_k2 = nullptr, *rs_y = nullptr, *rs_g = nullptr,
          *rs_rhs = nullptr, *rs_coef = nullptr;
   erem::BicgState* bicg = nullptr;

@@ -69,11 +69,11 @@ int ensure_bicg(erem_ctx* c) {
   if (c->bicg) return EREM_OK;
   const size_t n = c->d.N;
   int rc = EREM_OK;
-  double** v[] = {&c->bc_r, &c->bc_rhat, &c->bc_p0, &c->bc_p1, &c->bc_v0, &c->bc_v1, &c->bc_s, &c->bc_t,
+  double** v[] = {&c->bc_r, &c->bc_rhat, &c->bc_p0, &c->bc_p1, &c->bc_v0, &c->bc_v1, &c->bc_s, &c->bc_t, &c->bc_d,
                   &c->rs_k0, &c->rs_k1, &c->rs_k2, &c->rs_y, &c->rs_g, &c->rs_rhs};
   for (double** b : v) rc |= dev_alloc(c, b, n);
   rc |= dev_alloc(c, &c->rs_coef, n * ndir(c));
-  const int nb = cell_bands(c->d);
+  const int nb = bicg_blocks(c->d);
   rc |= dev_alloc(c, &c->bicg_parts, bicg_parts_words(nb));
   rc |= dev_alloc(c, &c->bicg, 1);
   if (rc) return EREM_ENOMEM;
@@ -86,7 +86,9 @@ int ensure_bicg(erem_ctx* c) {
   return EREM_OK;
 }
 
-BicgBufs bufs(erem_ctx* c) { return BicgBufs{c->bc_r, c->bc_rhat, {c->bc_p0, c->bc_p1}, {c->bc_v0, c->bc_v1}, c->bc_s, c->bc_t}; }
+BicgBufs bufs(erem_ctx* c) {
+  return BicgBufs{c->bc_r, c->bc_rhat, {c->bc_p0, c->bc_p1}, {c->bc_v0, c->bc_v1}, c->bc_s, c->bc_t, c->bc_d};
+}
 
 // (sigma I - J) x = b with the context's stencil, from x = 0, to
 // ||r|| <= rtol ||b|| (recursive residual).  Iterations after convergence
@@ -96,11 +98,11 @@ int bicg_solve(erem_ctx* c, double sigma, const double* b, double* x, double rto
   const Dims& d = c->d;
   const BicgBufs B = bufs(c);
   HIP_TRY(c, launch_bicg_reset(c->bicg, rtol * rtol, c->stream));
-  HIP_TRY(c, launch_bicg_start(d, b, x, B, c->bicg, c->stream));
+  HIP_TRY(c, launch_bicg_start(d, sigma, c->coef, b, x, B, c->bicg, c->stream));
   const int first = c->bicg_last > 0 ? c->bicg_last + 1 : 8;
   const int chunk = 4;
   if (c->prof) {
-    const int rc = ensure_events(c, 6 * static_cast<size_t>(std::max(first, chunk)));
+    const int rc = ensure_events(c, 4 * static_cast<size_t>(std::max(first, chunk)));
     if (rc) return rc;
   }
   int it = 0;
@@ -109,8 +111,8 @@ int bicg_solve(erem_ctx* c, double sigma, const double* b, double* x, double rto
     const int it0 = it;
     for (int j = 0; j < n; ++j, ++it) {
       const bool timed = c->prof && it % c->prof == 0;
-      HIP_TRY(c, launch_bicg_iteration(d, sigma, c->coef, x, B, c->bicg, it, c->stream,
-                                       timed ? &c->ev[6 * j] : nullptr));
+      HIP_TRY(c, launch_bicg_iteration(d, c->coef, x, B, c->bicg, it, c->stream,
+                                       timed ? &c->ev[4 * j] : nullptr));
     }
     HIP_TRY(c, hipMemcpyAsync(c->h_bicg, c->bicg, 4 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -120,8 +122,7 @@ int bicg_solve(erem_ctx* c, double sigma, const double* b, double* x, double rto
       for (int j = 0; j < n; ++j) {
         const int k = it0 + j;
         if (k % c->prof != 0 || k >= last) continue;
-        c->t_bicg += elapsed_ms(c->ev[6 * j], c->ev[6 * j + 1]) + elapsed_ms(c->ev[6 * j + 2], c->ev[6 * j + 3]) +
-                     elapsed_ms(c->ev[6 * j + 4], c->ev[6 * j + 5]);
+        c->t_bicg += elapsed_ms(c->ev[4 * j], c->ev[4 * j + 1]) + elapsed_ms(c->ev[4 * j + 2], c->ev[4 * j + 3]);
         c->n_bicg += 1;
       }
     }

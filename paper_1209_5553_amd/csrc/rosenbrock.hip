@@ -1,27 +1,34 @@
 // Shifted solves (sigma I - J) x = b for the Rosenbrock-type steps (Eq. ROS,
 // Eq. ROSMh) and the Newton iterations of theta-Euler (Eq. temscheme): the
 // paper solves these systems with BiCGSTAB; here BiCGSTAB runs with Jacobi
-// right preconditioning, M = diag(sigma - J_ii), three kernels per iteration,
-// every inner product reduced into a ring of slotted partial sums that the
-// next kernel folds with one wavefront (no host round trip per iteration).
+// right preconditioning, M = diag(sigma - J_ii), two kernels per iteration,
+// every inner product reduced into a ring of partial sums that the next kernel
+// adds up, a wavefront per sum (no host round trip per iteration).
 //
-// With y = M^{-1} p and z = M^{-1} s, one iteration `it` is
-//   K1: p = r + beta (p_old - omega_old v_old),  v = A y,  (rhat, v)
-//   K2: alpha = (rhat, r) / (rhat, v),  s = r - alpha v,  t = A z,  (t, s), (t, t)
-//   K3: omega = (t, s) / (t, t),  x += alpha y + omega z,  r = s - omega t,
-//       (rhat, r), (r, r)
-// where A = sigma I - J; a kernel that needs a neighbour's p (or s) forms it
-// from the neighbour's operands, so p and v alternate between two buffers.
+// With y = M^{-1} p and z = M^{-1} s, iteration `it` is
+//   K1: (it > 0) omega = (t, s) / (t, t),  x += alpha y + omega z,
+//       r = s - omega t of the iteration before,  (r, r);
+//       p = r + beta (p_old - omega v_old),  v = A y,  (rhat, v)
+//   K2: stop test on (r, r);  alpha = (rhat, r) / (rhat, v),  s = r - alpha v,
+//       t = A z,  (t, s), (t, t), (rhat, s), (rhat, t)
+// where A = sigma I - J.  beta needs (rhat, r) of the new r before K1 has formed
+// it: it is (rhat, s) - omega (rhat, t), which takes the place of a third kernel
+// and its pass; (r, r), which the stop test compares over many orders, is summed
+// from r itself.  A kernel that needs a neighbour's p (or s) forms it from the
+// neighbour's operands, so p and v alternate between two buffers.
+//
+// On 512 x 512 the kernels are chains of latencies (launch, loads, sums,
+// shuffles), 10 and 8 us; with three kernels per iteration, up to seven sums on
+// one wavefront and a division per neighbour an iteration took 27.6 us.
 #include <hip/hip_runtime.h>
 
 #include "rosenbrock.h"
 
+#include <algorithm>
+
 namespace erem {
 
 namespace {
-
-__device__ inline int rb_tid() { return threadIdx.x + threadIdx.y * kBX; }
-__device__ inline int rb_bid() { return blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z); }
 
 // Sum of NV values over the 256-thread block; valid in thread 0.
 template <int NV>
@@ -30,7 +37,7 @@ __device__ inline void rb_block_sum(double (&v)[NV]) {
 #pragma unroll
   for (int n = 0; n < NV; ++n)
     for (int off = 32; off > 0; off >>= 1) v[n] += __shfl_down(v[n], off, 64);
-  const int t = rb_tid();
+  const int t = threadIdx.x;
   if ((t & 63) == 0) {
 #pragma unroll
     for (int n = 0; n < NV; ++n) sh[t >> 6][n] = v[n];
@@ -63,228 +70,254 @@ struct Nbrs {
   }
 };
 
-// Scalars of a new solve (every producer overwrites the partial slots of
-// all bands, so they need no clearing).
+// Scalars of a new solve (every producer overwrites all partial slots, so they
+// need no clearing).
 __global__ void k_bicg_reset(BicgState* st, double tol2) {
   if (threadIdx.x == 0) {
     st->done = 0;
     st->it_done = 0;
     st->breakdown = 0;
+    st->bad = 0;
     st->tol2 = tol2;
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_bicg_start(Dims d, const double* __restrict__ b,
-                                               double* __restrict__ xv, double* __restrict__ r,
-                                               double* __restrict__ rhat, BicgState* st) {
-  const int x = blockIdx.x * kBX + threadIdx.x;
-  const int y = blockIdx.y * kBY + threadIdx.y;
-  const int z = blockIdx.z;
+// The cell bands (64 x 4 cells) of the grid, dealt to the workgroups in turn.
+struct Bands {
+  int gx, gy, n;
+  __device__ explicit Bands(const Dims& d) : gx((d.nx + kBX - 1) / kBX), gy((d.ny + kBY - 1) / kBY), n(gx * gy * d.nz) {}
+  __device__ void cell(int b, int& x, int& y, int& z) const {
+    x = (b % gx) * kBX + (threadIdx.x & 63);
+    y = ((b / gx) % gy) * kBY + (threadIdx.x >> 6);
+    z = b / (gx * gy);
+  }
+};
+
+__global__ __launch_bounds__(kThreads) void k_bicg_start(Dims d, double sigma, const double* __restrict__ coef,
+                                               const double* __restrict__ b, double* __restrict__ xv,
+                                               double* __restrict__ r, double* __restrict__ rhat,
+                                               double* __restrict__ dinv, BicgState* st) {
   double s[1] = {0.0};
-  if (x < d.nx && y < d.ny) {
-    const int i = x + d.nx * (y + d.ny * z);
+  for (int i = blockIdx.x * kThreads + threadIdx.x; i < d.N; i += gridDim.x * kThreads) {
     const double bi = b[i];
     r[i] = bi;
     rhat[i] = bi;
     xv[i] = 0.0;
-    s[0] = bi * bi;
+    dinv[i] = 1.0 / (sigma - coef[i]);
+    s[0] += bi * bi;
   }
   rb_block_sum<1>(s);
-  if (rb_tid() == 0) {
-    const int b = rb_bid();  // the block's band
-    st->bb_sl[b] = s[0];
-    st->rho[slot_of(st, 0) + b] = s[0];
-    st->rr[slot_of(st, 0) + b] = s[0];
-  }
+  if (threadIdx.x == 0) st->bb_sl[blockIdx.x] = s[0];  // also (rhat, r_0) and (r_0, r_0)
 }
 
-// K1 of iteration `it`: convergence test on (r_it, r_it), beta, p, v = A y.
+// Operands of one cell in K1 (the neighbours' loads go out with the cell's own).
 template <int NB>
-__global__ __launch_bounds__(kThreads) void k_bicg_pv(Dims d, double sigma, const double* __restrict__ coef,
-                                            const double* __restrict__ r, const double* __restrict__ pold,
+struct PvCell {
+  bool in;
+  int i;
+  double r, s, t, p, v, rh, dv, x;
+  double ns[NB], nt[NB], np[NB], nv[NB], nd[NB], ck[NB];
+};
+
+// K1 of iteration `it` (see above).
+template <int NB>
+__global__ __launch_bounds__(kThreads) void k_bicg_pv(Dims d, const double* __restrict__ coef,
+                                            double* __restrict__ r, const double* __restrict__ sv,
+                                            const double* __restrict__ tv, const double* __restrict__ pold,
                                             const double* __restrict__ vold, double* __restrict__ pnew,
                                             double* __restrict__ vnew, const double* __restrict__ rhat,
+                                            const double* __restrict__ dinv, double* __restrict__ xv,
                                             BicgState* st, int it) {
-  __shared__ double beta_sh, om_sh;
-  __shared__ int stop_sh;
-  const int t = rb_tid();
-  const int x = blockIdx.x * kBX + threadIdx.x;
-  const int y = blockIdx.y * kBY + threadIdx.y;
-  const int z = blockIdx.z;
-  const bool in = x < d.nx && y < d.ny;
-  const int N = d.N;
-  const int i = in ? x + d.nx * (y + d.ny * z) : 0;
-  const Nbrs<NB> nb(d, x, y, z, i);
-  // operands first, so that their loads overlap the scalar decision below
-  // (the diagonal of J is needed only at the neighbours: the preconditioned
-  // operator's own-cell term is p itself)
-  double rc = 0.0, pc = 0.0, vc = 0.0, rh = 0.0;
-  double rn[NB], pn[NB], vn[NB], cn0[NB], ck[NB];
-  if (in) {
-    rc = r[i]; pc = pold[i]; vc = vold[i]; rh = rhat[i];
+  __shared__ double sums[4];
+  const Bands B(d);
+  const int N = d.N, t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int stopped = *(volatile const int*)&st->done;  // only K2 writes it
+  auto load = [&](int b) {
+    PvCell<NB> c;
+    int x, y, z;
+    B.cell(b, x, y, z);
+    c.in = x < d.nx && y < d.ny;
+    c.i = c.in ? x + d.nx * (y + d.ny * z) : 0;
+    if (!c.in) x = y = z = 0;
+    const Nbrs<NB> nb(d, x, y, z, c.i);
+    c.rh = rhat[c.i];
+    c.dv = dinv[c.i];
+    if (it == 0) {
+      c.r = r[c.i];
+    } else {
+      c.s = sv[c.i];
+      c.t = tv[c.i];
+      c.p = pold[c.i];
+      c.v = vold[c.i];
+      c.x = xv[c.i];
+    }
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const int j = nb.idx[k];
-      rn[k] = r[j]; pn[k] = pold[j]; vn[k] = vold[j]; cn0[k] = coef[j];
-      ck[k] = coef[(k + 1) * N + i];
-    }
-  }
-  if (t < 64) {  // the first wavefront decides
-    int stop = *(volatile int*)&st->done;
-    double beta = 0.0, om = 0.0;
-    if (!stop) {
-      const double rr = wave_part_sum(st->rr + slot_of(st, it), st->nb);
-      const double bb = wave_part_sum(st->bb_sl, st->nb);
-      bool bad = !isfinite(rr);
-      if (!bad && rr <= st->tol2 * bb) {
-        stop = 1;
-        if (rb_bid() == 0 && t == 0) { st->it_done = it; st->done = 1; }
-      } else if (!bad && it > 0) {
-        const double rho = wave_part_sum(st->rho + slot_of(st, it), st->nb);
-        const double rho_p = wave_part_sum(st->rho + slot_of(st, it - 1), st->nb);
-        const double rv_p = wave_part_sum(st->rv + slot_of(st, it - 1), st->nb);
-        const double ts_p = wave_part_sum(st->ts + slot_of(st, it - 1), st->nb);
-        const double tt_p = wave_part_sum(st->tt + slot_of(st, it - 1), st->nb);
-        const double alpha_p = rho_p / rv_p;
-        om = tt_p > 0.0 ? ts_p / tt_p : 0.0;
-        beta = (rho / rho_p) * (alpha_p / om);
-        bad = rho == 0.0 || !isfinite(beta);
-      }
-      if (bad) {
-        stop = 1;
-        if (rb_bid() == 0 && t == 0) { st->breakdown = 1; st->it_done = it; st->done = 1; }
+      c.nd[k] = dinv[j];
+      c.ck[k] = coef[static_cast<size_t>(k + 1) * N + c.i];
+      if (it == 0) {
+        c.ns[k] = r[j];
+      } else {
+        c.ns[k] = sv[j];
+        c.nt[k] = tv[j];
+        c.np[k] = pold[j];
+        c.nv[k] = vold[j];
       }
     }
-    if (t == 0) { stop_sh = stop; beta_sh = beta; om_sh = om; }
-
+    return c;
+  };
+  int band = blockIdx.x;
+  PvCell<NB> c = load(band);  // in flight while the sums are added up
+  double om = 0.0, beta = 0.0, alpha = 0.0;
+  if (it > 0) {
+    const double* src[4] = {st->hs, st->ht, st->ts, st->tt};
+    const double v = wave_part_sum(src[wave] + slot_of(st, it - 1), st->nb);
+    if (lane == 0) sums[wave] = v;
+    const double rho_p = st->rho_v[(it - 1) & 3];
+    alpha = st->alpha[(it - 1) & 3];
+    __syncthreads();
+    om = sums[3] > 0.0 ? sums[2] / sums[3] : 0.0;
+    const double rho = sums[0] - om * sums[1];
+    beta = (rho / rho_p) * (alpha / om);
+    const bool bad = rho == 0.0 || !isfinite(beta);
+    if (bad) beta = 0.0;  // K2 decides: converged, or broken down
+    if (blockIdx.x == 0 && t == 0 && !stopped) {
+      st->rho_v[it & 3] = rho;
+      st->bad = bad ? 1 : 0;
+    }
   }
-  __syncthreads();
-  if (stop_sh) return;
-  const double beta = beta_sh, om = om_sh;
-  double s[1] = {0.0};
-  if (in) {
-    const double p = it == 0 ? rc : rc + beta * (pc - om * vc);
-    double v = p;
+  if (stopped) return;
+  double s[2] = {0.0, 0.0};
+  for (;;) {
+    if (c.in) {
+      double rc, p;
+      if (it == 0) {
+        rc = c.r;
+        p = rc;
+      } else {
+        rc = c.s - om * c.t;
+        p = rc + beta * (c.p - om * c.v);
+        xv[c.i] = c.x + (alpha * c.p + om * c.s) * c.dv;
+        r[c.i] = rc;
+      }
+      double v = p;  // the preconditioned operator's own-cell term
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
-      const double pk = it == 0 ? rn[k] : rn[k] + beta * (pn[k] - om * vn[k]);
-      v -= ck[k] * (pk / (sigma - cn0[k]));
+      for (int k = 0; k < NB; ++k) {
+        const double pk = it == 0 ? c.ns[k] : (c.ns[k] - om * c.nt[k]) + beta * (c.np[k] - om * c.nv[k]);
+        v -= c.ck[k] * (pk * c.nd[k]);
+      }
+      pnew[c.i] = p;
+      vnew[c.i] = v;
+      s[0] += c.rh * v;
+      s[1] += rc * rc;
     }
-    pnew[i] = p;
-    vnew[i] = v;
-    s[0] = rh * v;
+    band += gridDim.x;
+    if (band >= B.n) break;
+    c = load(band);
   }
-  rb_block_sum<1>(s);
-  if (t == 0) st->rv[slot_of(st, it) + rb_bid()] = s[0];
+  rb_block_sum<2>(s);
+  if (t == 0) {
+    st->rv[slot_of(st, it) + blockIdx.x] = s[0];
+    st->rr[slot_of(st, it) + blockIdx.x] = s[1];
+  }
 }
 
-// K2: alpha, s = r - alpha v, t = A z, (t, s), (t, t).
 template <int NB>
-__global__ __launch_bounds__(kThreads) void k_bicg_st(Dims d, double sigma, const double* __restrict__ coef,
+struct StCell {
+  bool in;
+  int i;
+  double r, v, rh;
+  double nr[NB], nv[NB], nd[NB], ck[NB];
+};
+
+// K2 of iteration `it` (see above).
+template <int NB>
+__global__ __launch_bounds__(kThreads) void k_bicg_st(Dims d, const double* __restrict__ coef,
                                             const double* __restrict__ r, const double* __restrict__ v,
+                                            const double* __restrict__ rhat, const double* __restrict__ dinv,
                                             double* __restrict__ sv, double* __restrict__ tv, BicgState* st,
                                             int it) {
-  __shared__ double alpha_sh;
+  __shared__ double sums[3];
   __shared__ int stop_sh;
-  const int t = rb_tid();
-  const int x = blockIdx.x * kBX + threadIdx.x;
-  const int y = blockIdx.y * kBY + threadIdx.y;
-  const int z = blockIdx.z;
-  const bool in = x < d.nx && y < d.ny;
-  const int N = d.N;
-  const int i = in ? x + d.nx * (y + d.ny * z) : 0;
-  const Nbrs<NB> nb(d, x, y, z, i);
-  double rc = 0.0, vc = 0.0;
-  double rn[NB], vn[NB], cn0[NB], ck[NB];
-  if (in) {
-    rc = r[i]; vc = v[i];
+  const Bands B(d);
+  const int N = d.N, t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  auto load = [&](int b) {
+    StCell<NB> c;
+    int x, y, z;
+    B.cell(b, x, y, z);
+    c.in = x < d.nx && y < d.ny;
+    c.i = c.in ? x + d.nx * (y + d.ny * z) : 0;
+    if (!c.in) x = y = z = 0;
+    const Nbrs<NB> nb(d, x, y, z, c.i);
+    c.r = r[c.i];
+    c.v = v[c.i];
+    c.rh = rhat[c.i];
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const int j = nb.idx[k];
-      rn[k] = r[j]; vn[k] = v[j]; cn0[k] = coef[j];
-      ck[k] = coef[(k + 1) * N + i];
+      c.nr[k] = r[j];
+      c.nv[k] = v[j];
+      c.nd[k] = dinv[j];
+      c.ck[k] = coef[static_cast<size_t>(k + 1) * N + c.i];
     }
+    return c;
+  };
+  int band = blockIdx.x;
+  StCell<NB> c = load(band);
+  if (wave < 3) {
+    const double* src[3] = {st->rr + slot_of(st, it), st->rv + slot_of(st, it), st->bb_sl};
+    const double w = wave_part_sum(src[wave], st->nb);
+    if (lane == 0) sums[wave] = w;
   }
-  if (t < 64) {
-    int stop = *(volatile int*)&st->done;
-    double alpha = 0.0;
-    if (!stop) {
-      alpha = wave_part_sum(st->rho + slot_of(st, it), st->nb) / wave_part_sum(st->rv + slot_of(st, it), st->nb);
-      if (!isfinite(alpha)) {
-        stop = 1;
-        if (rb_bid() == 0 && t == 0) { st->breakdown = 1; st->it_done = it; st->done = 1; }
-      }
-    }
-    if (t == 0) { stop_sh = stop; alpha_sh = alpha; }
-
-  }
+  // one reading of the flag for the whole workgroup: workgroup 0 may set it
+  if (t == 0) stop_sh = *(volatile const int*)&st->done;
+  const double rho_v = it > 0 ? st->rho_v[it & 3] : 0.0;
+  const int bad = st->bad;
   __syncthreads();
   if (stop_sh) return;
-  const double alpha = alpha_sh;
-  double s[2] = {0.0, 0.0};
-  if (in) {
-    const double si = rc - alpha * vc;
-    double ti = si;
+  const double rr = sums[0], bb = sums[2];
+  const double rho = it > 0 ? rho_v : bb;  // (rhat, r_0) = ||b||^2
+  const double alpha = rho / sums[1];
+  const bool conv = isfinite(rr) && rr <= st->tol2 * bb;
+  const bool fail = !conv && (!isfinite(rr) || (it > 0 && bad) || !isfinite(alpha));
+  if (conv || fail) {
+    if (blockIdx.x == 0 && t == 0) {
+      if (fail) st->breakdown = 1;
+      st->it_done = it;
+      st->done = 1;
+    }
+    return;
+  }
+  if (blockIdx.x == 0 && t == 0) {
+    st->alpha[it & 3] = alpha;
+    if (it == 0) st->rho_v[0] = rho;
+  }
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  for (;;) {
+    if (c.in) {
+      const double si = c.r - alpha * c.v;
+      double ti = si;
 #pragma unroll
-    for (int k = 0; k < NB; ++k) ti -= ck[k] * ((rn[k] - alpha * vn[k]) / (sigma - cn0[k]));
-    sv[i] = si;
-    tv[i] = ti;
-    s[0] = ti * si;
-    s[1] = ti * ti;
-  }
-  rb_block_sum<2>(s);
-  if (t == 0) {
-    const int b = rb_bid();
-    st->ts[slot_of(st, it) + b] = s[0];
-    st->tt[slot_of(st, it) + b] = s[1];
-  }
-}
-
-// K3: omega, x += alpha y + omega z, r = s - omega t, (rhat, r), (r, r).
-__global__ __launch_bounds__(kThreads) void k_bicg_xr(Dims d, double sigma, const double* __restrict__ coef,
-                                            double* __restrict__ xv, double* __restrict__ r,
-                                            const double* __restrict__ p, const double* __restrict__ sv,
-                                            const double* __restrict__ tv, const double* __restrict__ rhat,
-                                            BicgState* st, int it) {
-  __shared__ double alpha_sh, om_sh;
-  __shared__ int stop_sh;
-  const int t = rb_tid();
-  const int x = blockIdx.x * kBX + threadIdx.x;
-  const int y = blockIdx.y * kBY + threadIdx.y;
-  const int z = blockIdx.z;
-  const bool in = x < d.nx && y < d.ny;
-  const int i = in ? x + d.nx * (y + d.ny * z) : 0;
-  double xc = 0.0, pc = 0.0, sc = 0.0, tc = 0.0, c0 = 0.0, rh = 0.0;
-  if (in) {
-    xc = xv[i]; pc = p[i]; sc = sv[i]; tc = tv[i]; c0 = coef[i]; rh = rhat[i];
-  }
-  if (t < 64) {
-    const int stop = *(volatile int*)&st->done;
-    double alpha = 0.0, om = 0.0;
-    if (!stop) {
-      alpha = wave_part_sum(st->rho + slot_of(st, it), st->nb) / wave_part_sum(st->rv + slot_of(st, it), st->nb);
-      const double tt = wave_part_sum(st->tt + slot_of(st, it), st->nb);
-      om = tt > 0.0 ? wave_part_sum(st->ts + slot_of(st, it), st->nb) / tt : 0.0;
-
+      for (int k = 0; k < NB; ++k) ti -= c.ck[k] * ((c.nr[k] - alpha * c.nv[k]) * c.nd[k]);
+      sv[c.i] = si;
+      tv[c.i] = ti;
+      s[0] += ti * si;
+      s[1] += ti * ti;
+      s[2] += c.rh * si;
+      s[3] += c.rh * ti;
     }
-    if (t == 0) { stop_sh = stop; alpha_sh = alpha; om_sh = om; }
+    band += gridDim.x;
+    if (band >= B.n) break;
+    c = load(band);
   }
-  __syncthreads();
-  if (stop_sh) return;
-  const double alpha = alpha_sh, om = om_sh;
-  double s[2] = {0.0, 0.0};
-  if (in) {
-    xv[i] = xc + (alpha * pc + om * sc) / (sigma - c0);
-    const double rn = sc - om * tc;
-    r[i] = rn;
-    s[0] = rh * rn;
-    s[1] = rn * rn;
-  }
-  rb_block_sum<2>(s);
+  rb_block_sum<4>(s);
   if (t == 0) {
-    const int b = rb_bid();
-    st->rho[slot_of(st, it + 1) + b] = s[0];
-    st->rr[slot_of(st, it + 1) + b] = s[1];
+    const int o = slot_of(st, it) + blockIdx.x;
+    st->ts[o] = s[0];
+    st->tt[o] = s[1];
+    st->hs[o] = s[2];
+    st->ht[o] = s[3];
   }
 }
 
@@ -312,34 +345,34 @@ hipError_t launch_bicg_reset(BicgState* st, double tol2, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_bicg_start(const Dims& d, const double* b, double* x, const BicgBufs& B, BicgState* st,
-                             hipStream_t s) {
-  hipLaunchKernelGGL(k_bicg_start, cell_grid(d), cell_block(), 0, s, d, b, x, B.r, B.rhat, st);
+int bicg_blocks(const Dims& d) { return std::min(cell_bands(d), kBicgBlocks); }
+
+hipError_t launch_bicg_start(const Dims& d, double sigma, const double* coef, const double* b, double* x,
+                             const BicgBufs& B, BicgState* st, hipStream_t s) {
+  hipLaunchKernelGGL(k_bicg_start, dim3(bicg_blocks(d)), dim3(kThreads), 0, s, d, sigma, coef, b, x, B.r, B.rhat,
+                     B.dinv, st);
   return hipGetLastError();
 }
 
-hipError_t launch_bicg_iteration(const Dims& d, double sigma, const double* coef, double* x,
-                                 const BicgBufs& B, BicgState* st, int it, hipStream_t s, const hipEvent_t* e) {
+template <int NB>
+static hipError_t bicg_iteration(const Dims& d, const double* coef, double* x, const BicgBufs& B, BicgState* st,
+                                 int it, hipStream_t s, const hipEvent_t* e) {
+  const hipEvent_t n = nullptr;
   const double* pold = B.p[(it + 1) & 1];
   const double* vold = B.v[(it + 1) & 1];
-  double* pnew = B.p[it & 1];
-  double* vnew = B.v[it & 1];
-  const hipEvent_t n = nullptr;
-  if (d.dim == 3) {
-    launch_timed(k_bicg_pv<6>, cell_grid(d), cell_block(), 0, s, e ? e[0] : n, e ? e[1] : n, d, sigma, coef, B.r,
-                 pold, vold, pnew, vnew, B.rhat, st, it);
-    launch_timed(k_bicg_st<6>, cell_grid(d), cell_block(), 0, s, e ? e[2] : n, e ? e[3] : n, d, sigma, coef, B.r,
-                 static_cast<const double*>(vnew), B.s, B.t, st, it);
-  } else {
-    launch_timed(k_bicg_pv<4>, cell_grid(d), cell_block(), 0, s, e ? e[0] : n, e ? e[1] : n, d, sigma, coef, B.r,
-                 pold, vold, pnew, vnew, B.rhat, st, it);
-    launch_timed(k_bicg_st<4>, cell_grid(d), cell_block(), 0, s, e ? e[2] : n, e ? e[3] : n, d, sigma, coef, B.r,
-                 static_cast<const double*>(vnew), B.s, B.t, st, it);
-  }
-  launch_timed(k_bicg_xr, cell_grid(d), cell_block(), 0, s, e ? e[4] : n, e ? e[5] : n, d, sigma, coef, x, B.r,
-               static_cast<const double*>(pnew), static_cast<const double*>(B.s),
-               static_cast<const double*>(B.t), static_cast<const double*>(B.rhat), st, it);
+  const dim3 g(bicg_blocks(d)), b(kThreads);
+  launch_timed(k_bicg_pv<NB>, g, b, 0, s, e ? e[0] : n, e ? e[1] : n, d, coef, B.r,
+               static_cast<const double*>(B.s), static_cast<const double*>(B.t), pold, vold, B.p[it & 1], B.v[it & 1],
+               static_cast<const double*>(B.rhat), static_cast<const double*>(B.dinv), x, st, it);
+  launch_timed(k_bicg_st<NB>, g, b, 0, s, e ? e[2] : n, e ? e[3] : n, d, coef, static_cast<const double*>(B.r),
+               static_cast<const double*>(B.v[it & 1]), static_cast<const double*>(B.rhat),
+               static_cast<const double*>(B.dinv), B.s, B.t, st, it);
   return hipGetLastError();
+}
+
+hipError_t launch_bicg_iteration(const Dims& d, const double* coef, double* x, const BicgBufs& B, BicgState* st,
+                                 int it, hipStream_t s, const hipEvent_t* e) {
+  return d.dim == 3 ? bicg_iteration<6>(d, coef, x, B, st, it, s, e) : bicg_iteration<4>(d, coef, x, B, st, it, s, e);
 }
 
 hipError_t launch_lincomb(const Dims& d, double* out, const LinComb& lc, hipStream_t s) {

@@ -343,7 +343,8 @@ struct LejaPass {
   double* out;
   const double* g;   // source of substep j is v + (j delta) g + J u_j; null: v + J u_j
   const double* zt;  // added to out after every substep; null: nothing
-  hipEvent_t* ev;    // 2 K events per timed substep (the first nprof), or null
+  hipEvent_t* ev;    // 2 K events per timed substep (the first nprof), or null; on a small grid the
+                     // first two time the whole pass
   int nprof;
 };
 
@@ -351,6 +352,11 @@ template <class V>
 int leja_run(erem_ctx* c, const LejaVecs<V>& B, const LejaPass& P, const double* v, double delta, int s,
              int K) {
   const Dims& d = c->d;
+  if (leja_small_fits(d)) {
+    HIP_TRY(c, leja_small<V>(d, P.cf, c->coef, B.coef, v, P.g, P.zt, P.out, P.states, delta, s, K, c->stream,
+                             P.nprof > 0 ? P.ev[0] : nullptr, P.nprof > 0 ? P.ev[1] : nullptr));
+    return EREM_OK;
+  }
   for (int j = 0; j < s; ++j) {
     const double* src = v;
     if (j > 0) {
@@ -517,7 +523,16 @@ int leja_hphi1(erem_ctx* c, double h, const double* v, const double* g, double s
       last = std::max(last, hcf.estf[st.stopped] * std::sqrt(st.sums[st.stopped]));
     }
     const int timed_slot = j < s ? (j < nprof ? j : -1) : (c->prof ? nprof : -1);
-    if (timed_slot >= 0) {
+    if (leja_small_fits(c->d)) {
+      // one launch per pass, timed as a whole
+      if (c->prof) {
+        c->n_leja += applied;
+        if (j == 0 || j == s) {
+          const hipEvent_t* evj = &c->ev[static_cast<size_t>(timed_slot) * 2 * K];
+          c->t_leja += elapsed_ms(evj[0], evj[1]);
+        }
+      }
+    } else if (timed_slot >= 0) {
       const hipEvent_t* evj = &c->ev[static_cast<size_t>(timed_slot) * 2 * K];
       for (int k = 1, launch = 0; k <= applied; ++launch) {
         const int nt = leja_terms_per_launch(c->d, k, K);

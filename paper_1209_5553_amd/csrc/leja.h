@@ -69,6 +69,17 @@ template <class V>
 hipError_t leja_substep(const Dims& d, const LejaCoef* cf, const LejaVecs<V>& B, const double* src, LejaState* st,
                         double* part, int K, double* out, double delta, int first, const double* zt, hipStream_t s,
                         hipEvent_t* ev, int prof);
+// A whole evaluation of s substeps on a small grid in one
+// launch (leja_small.hip): out = sum of the substeps' increments, source v + t_j g
+// (g null: v), zt (or null) added per substep; the stop states st[0 .. s) as
+// leja_substep leaves them.  coef64: the stencil in FP64; coef: in the passes'
+// precision.
+constexpr int kSmallCells = 4096, kSmallCells3 = 2048;  // 2D, 3D
+bool leja_small_fits(const Dims& d);
+template <class V>
+hipError_t leja_small(const Dims& d, const LejaCoef* cf, const double* coef64, const V* coef, const double* v,
+                      const double* g, const double* zt, double* out, LejaState* st, double delta, int s, int K,
+                      hipStream_t q, hipEvent_t e0, hipEvent_t e1);
 // u = (first ? 0 : u) + delta p
 template <class V>
 hipError_t launch_substep_update(const Dims& d, double* u, const V* p, double delta, int first,

@@ -566,6 +566,9 @@ int krylov_hphi1(erem_ctx* c, double h, const double* v, double scal, const erem
     double** kbufs[] = {&c->kV, &c->kw, &c->kH, &c->kg, &c->kpart};
     for (double** b : kbufs)
       if (*b) { (void)hipFree(*b); *b = nullptr; }
+    if (c->h_kH) (void)hipHostFree(c->h_kH);
+    c->h_kH = nullptr;
+    c->kry_m = 0;
     int rc = EREM_OK;
     rc |= dev_alloc(c, &c->kV, N * m);
     rc |= dev_alloc(c, &c->kw, 2 * N);
@@ -582,9 +585,6 @@ int krylov_hphi1(erem_ctx* c, double h, const double* v, double scal, const erem
   const double thresh = std::pow(10.0, -o->p_order);
   const double rootN = std::sqrt(static_cast<double>(N));
   const int max_halvings = 60;
-    if (c->h_kH) (void)hipHostFree(c->h_kH);
-    c->h_kH = nullptr;
-    c->kry_m = 0;
   const size_t nH = static_cast<size_t>(m + 1) * m;
   const double* H = c->h_kH;
   double t = 0.0, delta = h;
@@ -599,6 +599,7 @@ int krylov_hphi1(erem_ctx* c, double h, const double* v, double scal, const erem
     HIP_TRY(c, arnoldi_cgs2(d, c->coef, c->kV, c->kw, c->kH, c->kH + nH, c->kg, c->kpart, m, c->stream));
     HIP_TRY(c, hipMemcpyAsync(c->h_kH, c->kH, sizeof(double) * (nH + 1), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    const double beta = H[nH];
     if (!std::isfinite(beta)) return fail(c, EREM_ENONFINITE, "non-finite Krylov vector norm");
     if (beta == 0.0) {
       // w = 0: u is a steady state of u' = J u + v, nothing changes any more
@@ -613,7 +614,6 @@ int krylov_hphi1(erem_ctx* c, double h, const double* v, double scal, const erem
     int me = m;
     bool exact = false;
     for (int j = 0; j < m; ++j) {
-    const double beta = H[nH];
       for (int i = 0; i <= j; ++i) {
         const double e = H[i * m + j];
         if (!std::isfinite(e)) return fail(c, EREM_ENONFINITE, "non-finite Hessenberg entry");

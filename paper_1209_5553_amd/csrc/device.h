@@ -203,9 +203,60 @@ inline void launch_timed(K kernel, dim3 grid, dim3 block, unsigned shmem, hipStr
     hipLaunchKernelGGL(kernel, grid, block, shmem, s, args...);
 }
 
+// v of another lane of the wavefront by a DPP control word (0 past its ends).
+template <int CTRL>
+__device__ inline double dpp(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
+}
+
+// v + v of the lane 16 (32) away: the two halves of a swapped pair of copies.
+__device__ inline double add_xor16(double v) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ inline double add_xor32(double v) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+// Sum over the lanes that agree in lane & 3; every such lane gets it.
+__device__ inline double sum_quads(double v) {
+  v += dpp<0x128>(v);  // row of 16 rotated by eight
+  v += dpp<0x124>(v);  // and by four
+  return add_xor32(add_xor16(v));
+}
+
+// v of lane l (the same for all lanes), in all lanes.
+__device__ inline double lane_of(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// Sum over the wavefront; every lane gets it.  Register moves only: a tree of
+// shuffles goes through the LDS pipe, a dozen dependent trips of some 100 cycles.
+// The halves are added from the widest distance down, as lane 0 of such a tree does.
+__device__ inline double wave_sum(double v) {
+  v = add_xor16(add_xor32(v));
+  v += dpp<0x128>(v);     // lane ^ 8
+  v += dpp<0x124>(v);     // lane ^ 4 (the sums repeat every 8 lanes)
+  v += dpp<0x4E>(v);      // lane ^ 2
+  return v + dpp<0xB1>(v);  // lane ^ 1
+}
+
+// Wavefront sums of four values at once: lane l gets that of value l & 3.
+__device__ inline double sum4(const double (&v)[4], int lane) {
+  const bool b0 = lane & 1, b1 = lane & 2;
+  const double lo = (b0 ? v[1] : v[0]) + dpp<0xB1>(b0 ? v[0] : v[1]);  // lane ^ 1
+  const double hi = (b0 ? v[3] : v[2]) + dpp<0xB1>(b0 ? v[2] : v[3]);
+  return sum_quads((b1 ? hi : lo) + dpp<0x4E>(b1 ? lo : hi));          // lane ^ 2
+}
+
 // Sum of n partials at base in a fixed order, by one wavefront: lane l adds
-// base[l], base[l + 64], ... in turn, a shuffle tree adds the lanes, and lane
-// 0's result is broadcast so that every lane takes the same decisions.  The
+// base[l], base[l + 64], ... in turn, a tree adds the lanes, and every lane gets
+// the result, so that all take the same decisions.  The
 // loads go sixteen at a time (a lane's share of 1024 partials is one memory
 // latency), and are added in order after they arrive.
 __device__ inline double wave_part_sum(const double* __restrict__ base, int n) {
@@ -219,31 +270,7 @@ __device__ inline double wave_part_sum(const double* __restrict__ base, int n) {
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) s += v[j];
   }
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-  return __shfl(s, 0, 64);
-}
-
-// v of another lane of the wavefront by a DPP control word (0 past its ends).
-template <int CTRL>
-__device__ inline double dpp(double v) {
-  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
-                          __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
-}
-
-// Sum over the lanes that agree in lane & 3; every such lane gets it.
-__device__ inline double sum_quads(double v) {
-  v += dpp<0x128>(v);  // row rotated by eight
-  v += dpp<0x124>(v);  // and by four
-  v += __shfl_xor(v, 16, 64);
-  return v + __shfl_xor(v, 32, 64);
-}
-
-// Wavefront sums of four values at once: lane l gets that of value l & 3.
-__device__ inline double sum4(const double (&v)[4], int lane) {
-  const bool b0 = lane & 1, b1 = lane & 2;
-  const double lo = (b0 ? v[1] : v[0]) + dpp<0xB1>(b0 ? v[0] : v[1]);  // lane ^ 1
-  const double hi = (b0 ? v[3] : v[2]) + dpp<0xB1>(b0 ? v[2] : v[3]);
-  return sum_quads((b1 ? hi : lo) + dpp<0x4E>(b1 ? lo : hi));          // lane ^ 2
+  return wave_sum(s);
 }
 
 // Ordered encoding of doubles for atomic min/max on 64-bit unsigned integers.

@@ -47,15 +47,8 @@ __device__ inline void take_sums(const double* __restrict__ part, int nb, int n,
         acc[u] += k < n ? part[static_cast<size_t>(k) * nb + b] : 0.0;
       }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) acc[u] += __shfl_down(acc[u], off, 64);
-    }
-    if (lane == 0) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (k0 + u * kKryWaves < n) gs[k0 + u * kKryWaves] = acc[u];
-    }
+    const double s = sum4(acc, lane);
+    if (lane < 4 && k0 + lane * kKryWaves < n) gs[k0 + lane * kKryWaves] = s;
   }
   __syncthreads();
 }
@@ -93,7 +86,7 @@ __device__ inline void wave_dots(const KryRow& row, const double* __restrict__ V
 }
 
 __device__ inline void wave_value(double v, double* sh, int k) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+  v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) sh[k * kKryWaves + (threadIdx.x >> 6)] = v;
 }
 

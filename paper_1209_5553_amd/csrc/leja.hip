@@ -33,7 +33,7 @@ __device__ inline V to_v(double x) { return static_cast<V>(x); }
 // Sum of one double over the 256-thread cell block; valid in thread 0.
 __device__ inline double block_sum256(double v) {
   __shared__ double sh[kThreads / 64];
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+  v = wave_sum(v);
   const int t = threadIdx.x + threadIdx.y * kBX;
   if ((t & 63) == 0) sh[t >> 6] = v;
   __syncthreads();
@@ -199,11 +199,9 @@ __global__ __launch_bounds__(kThreads) void k_leja_terms(Dims d, const LejaCoef*
   }
   if (stop) return;  // every wavefront of the workgroup alike
   __shared__ double red[NT][NW];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const double v = march_sum(sum[t]);
-    if (lane == 0) red[t][wave] = v;
-  }
+  static_assert(NT == 4, "the sums of a pass are reduced together");
+  const double s4 = sum4(sum, lane);
+  if (lane < 4) red[lane][wave] = s4;
   __syncthreads();
   if (threadIdx.x < NT) {
     const int t = threadIdx.x;
@@ -410,10 +408,8 @@ __global__ __launch_bounds__(NTH) void k_leja_zmarch(Dims d, const LejaCoef* __r
     qr = rin && z + 2 < nz ? qrn : V(0);
   }
   __shared__ double red[2][NW];
-  for (int off = 32; off > 0; off >>= 1) {
-    a0 += __shfl_down(a0, off, 64);
-    a1 += __shfl_down(a1, off, 64);
-  }
+  a0 = wave_sum(a0);
+  a1 = wave_sum(a1);
   if ((tid & 63) == 0) {
     red[0][tid >> 6] = a0;
     red[1][tid >> 6] = a1;

@@ -35,8 +35,7 @@ template <int NV>
 __device__ inline void rb_block_sum(double (&v)[NV]) {
   __shared__ double sh[kThreads / 64][NV];
 #pragma unroll
-  for (int n = 0; n < NV; ++n)
-    for (int off = 32; off > 0; off >>= 1) v[n] += __shfl_down(v[n], off, 64);
+  for (int n = 0; n < NV; ++n) v[n] = wave_sum(v[n]);
   const int t = threadIdx.x;
   if ((t & 63) == 0) {
 #pragma unroll

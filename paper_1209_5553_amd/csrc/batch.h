@@ -37,11 +37,12 @@ struct BProb {
 // Tile list entry: the problem, the strip of columns and the first row.
 struct BTile {
   int pid, strip, y0;
-  int done;  // set by the control kernel once the problem is done: the tile returns at entry
+  int done;           // set by the tile once its problem is done: it returns at entry
+  int tile0, ntiles;  // the problem's tiles
 };
 
-// Phases of a problem; every work launch advances each problem that is not
-// done by one phase, and the control kernel that follows picks the next.
+// Phases of a problem; every launch picks each unfinished problem's next phase
+// from what the launch before left, and advances it by that phase.
 enum BPhase : int {
   kPhInit = 0,    // start of a substep: q_0, p = d_0 q_0 (and the end of the previous substep or step)
   kPhTerms = 1,   // Newton terms k .. k + nt - 1
@@ -56,7 +57,7 @@ enum BInit : int {
   kInitStep = 2,   // next step: T += u + delta p of the last substep
 };
 
-// Dynamic state of one problem, written only by the control kernel.
+// Dynamic state of one problem (two copies, written by turns).
 struct BState {
   int phase, kind;
   int step;   // steps completed
@@ -67,17 +68,17 @@ struct BState {
   int tpar;   // buffer holding T^n: 0 the caller's array, 1 the internal copy
   int upar;   // buffer holding u (sum of the finished substeps' increments)
   int ppar;   // buffer holding p (the current substep's Newton sum)
-  int phases; // work passes taken
+  int phases; // work passes taken; -1: before the first
   int pad;
   double scal;     // error scale tol_a + tol_r max|T^n|
-  double ring[5];  // the last five scaled error estimates
+  double prev[4];  // the scaled error estimates of the four terms before term k
 };
 
 struct BatchArgs {
   const BProb* prob;
   BTile* tile;
-  BState* state;
-  int* ndone;            // problems done (control kernel counts them)
+  BState* state;         // two copies of nprob states
+  int* ndone;            // problems done
   const double* coef64;  // 5-point stencil, SoA with stride ntot (FP64)
   const void* coef;      // stencil of the Newton terms (FP64 or FP32)
   const double* g;       // G(T) = J T + g
@@ -89,7 +90,8 @@ struct BatchArgs {
   void *p0, *p1;         // Newton sums (ping-pong over substeps)
   const double* dk;      // divided differences, (m_max + 1) per problem
   const double* shift;   // c/gamma + xi_{k-1}, (m_max + 1) per problem
-  double* part;          // kBatchPartStride partials per tile
+  double* part;          // kBatchPartStride partials per tile, two copies of part_cap tiles
+  long long part_cap;
   long long ntot;
   int nprob, ntiles, nsteps, m_max;
   int nt, rows;          // Newton terms per pass and rows per tile of the tile shape
@@ -100,8 +102,8 @@ struct BatchArgs {
 hipError_t batch_pack(int nx, int ny, const double* coef, const double* F, const double* T0,
                       double* bcoef, double* g, long long ntot, long long off, hipStream_t s);
 hipError_t batch_reset(const BatchArgs& a, hipStream_t s);
-// One phase of every problem: work pass number `pass` over all tiles, then the
-// control kernel.  e0 / e1 (optional) time the work pass alone.
+// One phase of every problem: pass number `pass` over all tiles.  e0 / e1
+// (optional) time it.
 hipError_t batch_phase(BatchArgs a, long long pass, int fp32, hipStream_t s, hipEvent_t e0 = nullptr,
                        hipEvent_t e1 = nullptr);
 

@@ -23,10 +23,10 @@
 //               stay in registers;
 //   finish pass T += u + delta p of the last step.
 //
-// Each tile stores its partial sums (sum q_k^2 per term, in FP64); a
-// control kernel then reduces each problem's partials in a fixed order (one
-// wavefront per problem), applies the scaled-norm stop test of Sec. 4.2 to
-// the pass's NT estimates in order, and sets the problem's next phase.
+// Each tile stores its partial sums (sum q_k^2 per term, in FP64); at the start
+// of the next pass every tile's wavefront adds up its problem's partials in a
+// fixed order, applies the scaled-norm stop test of Sec. 4.2 to the pass's NT
+// estimates in order, and so knows the problem's next phase.
 // Problems of every size and substep count thus share every launch, the
 // work spreads over all CUs whatever the mix, and the whole run is a fixed
 // sequence of launches with no grid-wide synchronisation and no waiting
@@ -160,7 +160,7 @@ __device__ inline void batch_start(const BatchArgs& a, const BProb& P, const BSt
     }
   }
 done:
-  s0 = march_sum(out ? s0 : 0.0);
+  s0 = wave_sum(out ? s0 : 0.0);
   mx = march_max(out && !sub ? mx : 0.0);
   if (lane == 0) {
     part[0] = s0;
@@ -213,135 +213,38 @@ __device__ inline int batch_tile(int back) {
   return x * q + (x < r ? x : r) + (back ? size - 1 - k : k);
 }
 
-// One phase of every unfinished problem: a wavefront per tile (a strip of
-// columns by a chunk of rows).  While most problems are unfinished the pass is
-// bound by memory: eight FP64 terms of 7.2 M cells read 544 MB (5 stencil
-// words, q and p, plus the halos that missed L2) and write 115 MB in about
-// 145 us, 4.5 TB/s where a large copy reaches 4.8; taking every second pass
-// back to front finds the end of the pass before in the Infinity Cache (a run
-// of 50 steps 70.4 -> 65.9 ms).  The 64 x 16 LDS tiles on 512 threads that
-// this replaces took 215 us for the same pass (two workgroups' loads per CU in
-// flight, then eight barriered terms) and 92 ms for the run.  When only the
-// longest problems are left, a pass costs what one wavefront takes to issue
-// its rows (about 500 cycles a row of eight terms).
-template <int NT, class V>
-__global__ __launch_bounds__(kMarchLanes) __attribute__((amdgpu_waves_per_eu(2))) void k_bt_work(BatchArgs a) {
-  static_assert(NT <= kBatchPartStride, "terms per pass");
-  const int t = batch_tile(a.pass & 1);
-  const BTile tl = a.tile[t];
-  if (tl.done) return;  // the tiles of a finished problem stop here, before its state is read
-  const BState S = a.state[tl.pid];
-  if (S.phase == kPhDone) return;
-  const BProb P = a.prob[tl.pid];
-  const MarchStrip st = march_strip(P.nx, NT, tl.strip);
-  const int y0 = tl.y0, y1 = min(tl.y0 + a.rows, P.ny);
-  double* part = a.part + static_cast<long long>(kBatchPartStride) * t;
-  if (S.phase == kPhFinish) {
-    batch_finish<V>(a, P, S, st, y0, y1);
-    return;
-  }
-  if (S.phase == kPhInit) {
-    batch_start<V>(a, P, S, st, y0, y1, part);
-    return;
-  }
-  const int grp = (S.k - 1) / NT;
-  const V* qin = reinterpret_cast<const V*>((grp & 1) ? a.q1 : a.q0) + P.off;
-  V* qout = reinterpret_cast<V*>((grp & 1) ? a.q0 : a.q1) + P.off;
-  V* p = reinterpret_cast<V*>(S.ppar ? a.p1 : a.p0) + P.off;
-  V shift[NT], dk[NT];
-#pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    shift[j] = march_uniform(cv<V>(a.shift[P.coef_off + S.k + j]));
-    dk[j] = march_uniform(cv<V>(a.dk[P.coef_off + S.k + j]));
-  }
-  double sum[NT];
-  march_terms<NT, kBatchAhead, V>(reinterpret_cast<const V*>(a.coef) + P.off, a.ntot, qin, qout, p, P.nx, P.ny, st, y0, y1,
-                        cv<V>(P.inv_g), shift, dk, sum, [] { return false; });
-#pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    const double v = march_sum(sum[j]);
-    if ((threadIdx.x & 63) == 0) part[j] = v;
-  }
+// Reductions over the lanes that agree in lane & 7; every such lane gets them.
+__device__ inline void sum_max_octets(double& s, double& m) {
+  s += dpp<0x128>(s);
+  m = fmax(m, dpp<0x128>(m));
+  s = add_xor32(add_xor16(s));
+  const auto l16 = __builtin_amdgcn_permlane16_swap(__double2loint(m), __double2loint(m), false, false);
+  const auto h16 = __builtin_amdgcn_permlane16_swap(__double2hiint(m), __double2hiint(m), false, false);
+  m = fmax(__hiloint2double(h16[0], l16[0]), __hiloint2double(h16[1], l16[1]));
+  const auto l32 = __builtin_amdgcn_permlane32_swap(__double2loint(m), __double2loint(m), false, false);
+  const auto h32 = __builtin_amdgcn_permlane32_swap(__double2hiint(m), __double2hiint(m), false, false);
+  m = fmax(__hiloint2double(h32[0], l32[0]), __hiloint2double(h32[1], l32[1]));
 }
 
-// One wavefront per problem: reduce the problem's tile partials of the last
-// work pass in a fixed order, apply the stop test and pick the next phase.
-constexpr int kCtrlThreads = 64;  // one wavefront (one problem) per workgroup
 
-__global__ __launch_bounds__(kCtrlThreads) void k_bt_ctrl(BatchArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int pid = blockIdx.x * (kCtrlThreads / 64) + (threadIdx.x >> 6);
-  if (pid >= a.nprob) return;
-  // the state and the problem record are loaded together, then the partials
-  // with the stop test's coefficients: two memory round trips
-  BState S = a.state[pid];
-  const BProb P = a.prob[pid];
-  if (S.phase == kPhDone) return;
-  if (S.phase == kPhFinish) {
-    // the finish pass is done: from the next launch on the problem's tiles
-    // return at entry
-    for (int tt = lane; tt < P.ntiles; tt += 64) a.tile[P.tile0 + tt].done = 1;
-    if (lane == 0) {
-      S.phase = kPhDone;
-      ++S.phases;
-      a.state[pid] = S;
-      atomicAdd(a.ndone, 1);
-    }
-    return;
-  }
+// The problem's next phase, from the partials that its tiles left in the pass
+// before (lane l of every wavefront holds term k + (l & 7)'s sum in `s`, and in
+// `mx` the maximum of a start pass's second partial in the lanes of term 1; dk:
+// the lane's divided difference): the stop test of Sec. 4.2 on the pass's
+// estimates in order.  Every wavefront of the problem comes to the same state.
+__device__ inline void batch_next(const BatchArgs& a, const BProb& P, BState& S, double s, double mx, double dk) {
+  const int lane = threadIdx.x & 63, nt = a.nt;
   const bool init = S.phase == kPhInit;
-  const int nt = a.nt;
-  const double* dk = a.dk + P.coef_off;
-  double dkv[kBatchPartStride];
-#pragma unroll
-  for (int j = 0; j < kBatchPartStride; ++j) dkv[j] = init ? dk[0] : (j < nt ? dk[S.k + j] : 0.0);
-  const double* pp = a.part + static_cast<long long>(kBatchPartStride) * P.tile0;
-  double s[kBatchPartStride];
-#pragma unroll
-  for (int j = 0; j < kBatchPartStride; ++j) s[j] = 0.0;
-  double mx = 0.0;
-  for (int tt = lane; tt < P.ntiles; tt += 64) {
-    const double* pt = pp + kBatchPartStride * tt;
-    if (init) {
-      s[0] += pt[0];
-      mx = fmax(mx, pt[1]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < kBatchPartStride; ++j)
-        if (j < nt) s[j] += pt[j];
-    }
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-#pragma unroll
-    for (int j = 0; j < kBatchPartStride; ++j) s[j] += __shfl_down(s[j], off, 64);
-    mx = fmax(mx, __shfl_down(mx, off, 64));
-  }
-  // the pass's scaled estimates |delta d_k| ||q_k|| / (sqrt(N) scal), lane j
-  // forming term S.k + j's (each the expression a sequential loop would
-  // evaluate, so the same bits), then gathered in lane 0
-  mx = __shfl(mx, 0, 64);
-  if (init && S.kind != kInitSub) S.scal = a.tol_a + a.tol_r * mx;
-  double sj = 0.0, dj = 0.0;
-#pragma unroll
-  for (int j = 0; j < kBatchPartStride; ++j) {
-    const double v = __shfl(s[j], 0, 64);
-    if (lane == j) {
-      sj = v;
-      dj = dkv[j];
-    }
-  }
-  const double est = fabs(P.delta * dj) * sqrt(sj) / (P.rootN * S.scal);
-  double estv[kBatchPartStride];
-#pragma unroll
-  for (int j = 0; j < kBatchPartStride; ++j) estv[j] = __shfl(est, j, 64);
-  if (lane != 0) return;
   ++S.phases;
+  if (init && S.kind != kInitSub) S.scal = a.tol_a + a.tol_r * lane_of(mx, 1);
+  const double est = fabs(P.delta * dk) * sqrt(s) / (P.rootN * S.scal);
   bool stop = false;  // no further Newton work for this problem
   if (init) {
     if (S.kind == kInitStep) S.tpar ^= 1;
     if (S.kind == kInitSub) S.upar ^= 1;
     S.ppar ^= 1;
-    if (!isfinite(s[0]) || !isfinite(mx)) {
+    const double s0 = lane_of(s, 0), m0 = lane_of(mx, 1);
+    if (!isfinite(s0) || (S.kind != kInitSub && !isfinite(m0))) {
       S.flags |= 2;
       stop = true;
     } else if (!(S.scal > 0.0)) {
@@ -351,42 +254,35 @@ __global__ __launch_bounds__(kCtrlThreads) void k_bt_ctrl(BatchArgs a) {
       S.flags |= 1;  // not even one pass fits the term budget
       stop = true;
     } else {
-      S.ring[0] = estv[0];
+      S.prev[0] = S.prev[1] = S.prev[2] = 0.0;
+      S.prev[3] = lane_of(est, 0);
       S.k = 1;
       S.phase = kPhTerms;
     }
   } else {
-    // the terms in order until the test passes; every index below is a
-    // compile-time constant (the unrolled loops select the ring slot), so
-    // the state stays in registers
-    bool done = false, bad = false;
-    double ring[5];
-#pragma unroll
-    for (int q = 0; q < 5; ++q) ring[q] = S.ring[q];
-#pragma unroll
-    for (int j = 0; j < kBatchPartStride; ++j) {
-      if (j >= nt || done || bad) continue;
-      const int kk = S.k + j;
-      if (!isfinite(s[j])) {
-        bad = true;
-        continue;
-      }
-      const int slot = kk % 5;
-#pragma unroll
-      for (int q = 0; q < 5; ++q)
-        if (q == slot) ring[q] = estv[j];
-      if (kk >= 4) {
-        const double mean = 0.2 * (ring[0] + ring[1] + ring[2] + ring[3] + ring[4]);
-        done = mean < a.thresh;
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < 5; ++q) S.ring[q] = ring[q];
+    // lanes 0 .. 3: the four estimates before the pass; lanes 4 .. nt + 3: the
+    // pass's; each of the latter tests the mean of its own and the four below
+    const double p01 = lane == 0 ? S.prev[0] : S.prev[1], p23 = lane == 2 ? S.prev[2] : S.prev[3];
+    const double up = __shfl_up(est, 4, 64);
+    const double z = lane < 4 ? (lane < 2 ? p01 : p23) : up;
+    double mean = __shfl_up(z, 4, 64);
+    mean += __shfl_up(z, 3, 64);
+    mean += __shfl_up(z, 2, 64);
+    mean += __shfl_up(z, 1, 64);
+    mean = 0.2 * (mean + z);
+    const int j = lane - 4;
+    const bool mine = j >= 0 && j < nt;
+    const double sj = __shfl_up(s, 4, 64);
+    const unsigned long long bad = __ballot(mine && !isfinite(sj));
+    const unsigned long long hit = __ballot(mine && S.k + j >= 4 && mean < a.thresh);
+    const int fb = bad ? __ffsll(bad) : 65, fh = hit ? __ffsll(hit) : 65;
     S.terms += nt;  // all terms of the pass are kept
-    if (bad) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) S.prev[m] = lane_of(est, nt - 4 + m);
+    if (fb <= fh && fb < 65) {
       S.flags |= 2;
       stop = true;
-    } else if (done) {
+    } else if (fh < 65) {
       if (S.sub + 1 < P.s) {
         ++S.sub;
         S.kind = kInitSub;
@@ -411,7 +307,111 @@ __global__ __launch_bounds__(kCtrlThreads) void k_bt_ctrl(BatchArgs a) {
   // a failed problem still takes the finish pass, which copies the T of its
   // last completed step into the caller's array
   if (stop) S.phase = kPhFinish;
-  a.state[pid] = S;
+}
+
+// One phase of every unfinished problem: a wavefront per tile (a strip of
+// columns by a chunk of rows).  It first makes the problem's control step -
+// every tile's wavefront alike, from the state and the partials of the pass
+// before, which this pass does not overwrite (both alternate between two
+// buffers) - and then the phase that comes out of it; the problem's first tile
+// records the state.
+//
+// While most problems are unfinished the pass is bound by memory: eight FP64
+// terms of 7.2 M cells read 544 MB (5 stencil words, q and p, plus the halos that
+// missed L2) and write 115 MB in about 145 us, 4.5 TB/s where a large copy
+// reaches 4.8; taking every second pass back to front finds the end of the pass
+// before in the Infinity Cache (a run of 50 steps 70.4 -> 65.9 ms).  The 64 x 16
+// LDS tiles on 512 threads that this replaces took 215 us for the same pass (two
+// workgroups' loads per CU in flight, then eight barriered terms) and 92 ms for
+// the run.  When only the longest problems are left, a pass costs what one
+// wavefront takes to issue its rows (about 500 cycles a row of eight terms), and
+// a control launch of its own after every pass cost 6 us and a launch gap.
+template <int NT, class V>
+__global__ __launch_bounds__(kMarchLanes) __attribute__((amdgpu_waves_per_eu(2))) void k_bt_ctrl_work(BatchArgs a) {
+  static_assert(NT <= kBatchPartStride && NT % 4 == 0, "terms per pass");
+  const int t = batch_tile(a.pass & 1);
+  const int lane = threadIdx.x;
+  const BTile tl = a.tile[t];
+  if (tl.done) return;  // the tiles of a finished problem stop here, before its state is read
+  BState S = a.state[(a.pass & 1) * a.nprob + tl.pid];
+  const BProb P = a.prob[tl.pid];
+  const long long pcap = static_cast<long long>(kBatchPartStride) * a.part_cap;
+  {
+    // the partials of the pass before and the next coefficients' addresses need
+    // the tile record only: their loads go out beside the state's
+    const double* pp = a.part + (a.pass & 1) * pcap + static_cast<long long>(kBatchPartStride) * tl.tile0;
+    double s = 0.0, mx = 0.0;
+    if (S.phases >= 0) {
+      const int n = kBatchPartStride * tl.ntiles;
+      for (int b = lane; b < n; b += 4 * 64) {
+        double v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = b + 64 * u < n ? pp[b + 64 * u] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          s += v[u];
+          mx = fmax(mx, v[u]);
+        }
+      }
+    }
+    if (S.phase == kPhDone) {
+      if (lane == 0) a.tile[t].done = 1;
+      return;
+    }
+    if (S.phases < 0) {
+      S.phases = 0;  // the first pass: nothing to test yet
+    } else if (S.phase == kPhFinish) {
+      // the finish pass is done: the problem's tiles return at entry from now on.
+      // Both copies of the state say so: a wavefront of this pass that already
+      // reads it returns likewise.
+      S.phase = kPhDone;
+      ++S.phases;
+      if (lane == 0) {
+        a.tile[t].done = 1;
+        if (t == tl.tile0) {
+          a.state[tl.pid] = S;
+          a.state[a.nprob + tl.pid] = S;
+          atomicAdd(a.ndone, 1);
+        }
+      }
+      return;
+    } else {
+      const int k = S.phase == kPhInit ? 0 : S.k;
+      sum_max_octets(s, mx);
+      batch_next(a, P, S, s, mx, a.dk[P.coef_off + min(k + (lane & 7), a.m_max)]);
+    }
+    if (t == tl.tile0 && lane == 0) a.state[((a.pass & 1) ^ 1) * a.nprob + tl.pid] = S;
+  }
+  const MarchStrip st = march_strip(P.nx, NT, tl.strip);
+  const int y0 = tl.y0, y1 = min(tl.y0 + a.rows, P.ny);
+  double* part = a.part + ((a.pass & 1) ^ 1) * pcap + static_cast<long long>(kBatchPartStride) * t;
+  if (S.phase == kPhFinish) {
+    batch_finish<V>(a, P, S, st, y0, y1);
+    return;
+  }
+  if (S.phase == kPhInit) {
+    batch_start<V>(a, P, S, st, y0, y1, part);
+    return;
+  }
+  const int grp = (S.k - 1) / NT;
+  const V* qin = reinterpret_cast<const V*>((grp & 1) ? a.q1 : a.q0) + P.off;
+  V* qout = reinterpret_cast<V*>((grp & 1) ? a.q0 : a.q1) + P.off;
+  V* p = reinterpret_cast<V*>(S.ppar ? a.p1 : a.p0) + P.off;
+  V shift[NT], dk[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    shift[j] = march_uniform(cv<V>(a.shift[P.coef_off + S.k + j]));
+    dk[j] = march_uniform(cv<V>(a.dk[P.coef_off + S.k + j]));
+  }
+  double sum[NT];
+  march_terms<NT, kBatchAhead, V>(reinterpret_cast<const V*>(a.coef) + P.off, a.ntot, qin, qout, p, P.nx, P.ny, st, y0, y1,
+                        cv<V>(P.inv_g), shift, dk, sum, [] { return false; });
+#pragma unroll
+  for (int j = 0; j < NT; j += 4) {
+    const double s4[4] = {sum[j], sum[j + 1], sum[j + 2], sum[j + 3]};
+    const double v = sum4(s4, lane);
+    if (lane < 4) part[j + lane] = v;
+  }
 }
 
 __global__ void k_bt_reset(BatchArgs a) {
@@ -423,7 +423,9 @@ __global__ void k_bt_reset(BatchArgs a) {
   S.phase = kPhInit;
   S.kind = kInitFirst;
   S.k = 1;
+  S.phases = -1;
   a.state[pid] = S;
+  a.state[a.nprob + pid] = S;
 }
 
 // Pack one problem's stencil (SoA, stride N) into the batch layout (SoA,
@@ -448,9 +450,9 @@ __global__ __launch_bounds__(256) void k_batch_pack(int nx, int ny, const double
 template <class V>
 hipError_t launch_work(const BatchArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (a.nt == 8)
-    launch_timed(k_bt_work<8, V>, dim3(a.ntiles), dim3(kMarchLanes), 0, s, e0, e1, a);
+    launch_timed(k_bt_ctrl_work<8, V>, dim3(a.ntiles), dim3(kMarchLanes), 0, s, e0, e1, a);
   else
-    launch_timed(k_bt_work<4, V>, dim3(a.ntiles), dim3(kMarchLanes), 0, s, e0, e1, a);
+    launch_timed(k_bt_ctrl_work<4, V>, dim3(a.ntiles), dim3(kMarchLanes), 0, s, e0, e1, a);
   return hipGetLastError();
 }
 
@@ -473,11 +475,7 @@ hipError_t batch_reset(const BatchArgs& a, hipStream_t s) {
 
 hipError_t batch_phase(BatchArgs a, long long pass, int fp32, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   a.pass = static_cast<int>(pass & 1);
-  const hipError_t e = fp32 ? launch_work<float>(a, s, e0, e1) : launch_work<double>(a, s, e0, e1);
-  if (e != hipSuccess) return e;
-  const int per = kCtrlThreads / 64;
-  hipLaunchKernelGGL(k_bt_ctrl, dim3((a.nprob + per - 1) / per), dim3(kCtrlThreads), 0, s, a);
-  return hipGetLastError();
+  return fp32 ? launch_work<float>(a, s, e0, e1) : launch_work<double>(a, s, e0, e1);
 }
 
 }  // namespace erem

@@ -145,7 +145,7 @@ int build_tiles(erem_batch* b) {
     P.tile0 = static_cast<int>(tiles.size());
     P.ntiles = tx * ty;
     for (int y = 0; y < ty; ++y)
-      for (int x = 0; x < tx; ++x) tiles.push_back(BTile{i, x, y * rows, 0});
+      for (int x = 0; x < tx; ++x) tiles.push_back(BTile{i, x, y * rows, 0, P.tile0, P.ntiles});
   }
   if (tiles.size() > static_cast<size_t>(1 << 30)) return bfail(b, EREM_EINVAL, "too many tiles");
   b->ntiles = static_cast<int>(tiles.size());
@@ -164,7 +164,7 @@ int build_tiles(erem_batch* b) {
     if (b->part) (void)hipFree(b->part);
     b->tile = nullptr;
     b->part = nullptr;
-    if (balloc(b, &b->tile, cap) || balloc(b, &b->part, kBatchPartStride * static_cast<size_t>(cap)))
+    if (balloc(b, &b->tile, cap) || balloc(b, &b->part, 2 * kBatchPartStride * static_cast<size_t>(cap)))
       return EREM_ENOMEM;
     b->tile_cap = static_cast<int>(cap);
   }
@@ -194,6 +194,7 @@ BatchArgs make_args(erem_batch* b, double* T, int nsteps) {
   a.dk = b->dk;
   a.shift = b->shift;
   a.part = b->part;
+  a.part_cap = b->tile_cap;
   a.ntot = b->ntot;
   a.nprob = b->nprob;
   a.ntiles = b->ntiles;
@@ -207,13 +208,13 @@ BatchArgs make_args(erem_batch* b, double* T, int nsteps) {
   return a;
 }
 
-// Upper bound of the work passes a run can take: every problem needs, per
-// step and substep, one start pass and at most m_max / 4 term passes, and
-// one finish pass.
+// Upper bound of the passes a run can take: every problem needs, per step and
+// substep, one start pass and at most m_max / 4 term passes, one finish pass, and
+// the pass that finds it finished.
 long long max_phases(erem_batch* b, int nsteps) {
   int smax = 1;
   for (const BProb& P : b->hprob) smax = std::max(smax, P.s);
-  return static_cast<long long>(nsteps) * smax * (1 + b->m_max / 4) + 2;
+  return static_cast<long long>(nsteps) * smax * (1 + b->m_max / 4) + 3;
 }
 
 // Phases enqueued eagerly in chunks, the host reading the count of finished
@@ -455,7 +456,7 @@ int erem_batch_create(int32_t nprob, const erem_grid* grids, void* stream, erem_
   rc |= balloc(b, &b->p1, n);
   rc |= balloc(b, &b->tscratch, n);
   rc |= balloc(b, &b->prob, nprob);
-  rc |= balloc(b, &b->state, nprob);
+  rc |= balloc(b, &b->state, 2 * static_cast<size_t>(nprob));
   rc |= balloc(b, &b->ndone, 1);
   rc |= balloc(b, &b->red, 1);
   if (rc == EREM_OK && hipHostMalloc(reinterpret_cast<void**>(&b->h_red), sizeof(AsmReduce), hipHostMallocDefault) != hipSuccess)

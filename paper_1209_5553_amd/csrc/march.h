@@ -97,12 +97,6 @@ __device__ inline double march_mask(bool keep, double v) {
   return __hiloint2double(keep ? __double2hiint(v) : 0, __double2loint(v));
 }
 
-// Sum over the wavefront in a fixed order, valid in lane 0.
-__device__ inline double march_sum(double v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  return v;
-}
-
 // One strip's chunk of rows [y0, y1) by NT terms.  coef (five arrays, stride
 // cs), qin, qout and p start at the grid's first cell; shift[t], dk[t] belong
 // to term t + 1 of the pass.  sum[t] gets the lane's share of sum q^2 over the

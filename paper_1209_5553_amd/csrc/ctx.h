@@ -110,6 +110,7 @@ struct erem_ctx {
   // multigrid preconditioner of the pressure operator
   erem::MgHierarchy mg;
   bool use_mg = true;
+  bool mg_current = false;  // the hierarchy is that of the current transmissibilities
   std::vector<double*> mg_bufs;
   double alpha = 0.0, beta = 0.0, tmax = 0.0;
   std::vector<int> applied;  // Leja terms applied per substep by the last evaluation

@@ -903,7 +903,7 @@ int spd_solve(erem_ctx* c, const double* b, double* x, double rtol, int max_iter
   bool ok = false;
   // multigrid setup behind the first residual readback, as in the pressure
   // solve (the residual does not read the hierarchy)
-  bool setup_pending = c->use_mg;
+  bool setup_pending = c->use_mg && !c->mg_current;
   if (setup_pending && !c->ev_setup) HIP_TRY(c, hipEventCreateWithFlags(&c->ev_setup, hipEventDisableTiming));
   for (int outer = 0; outer < 12; ++outer) {
     HIP_TRY(c, launch_pcg_reset(c->pcg, 0.0, c->stream));
@@ -915,6 +915,7 @@ int spd_solve(erem_ctx* c, const double* b, double* x, double rtol, int max_iter
     if (setup_pending) {
       HIP_TRY(c, hipEventRecord(c->ev_setup, c->stream));
       HIP_TRY(c, mg_setup(c->mg, c->stream));
+      c->mg_current = true;
       setup_pending = false;
       HIP_TRY(c, hipEventSynchronize(c->ev_setup));
     } else {
@@ -1150,6 +1151,7 @@ int erem_set_bc(erem_ctx* c, double p_left, double p_right, double T_left, doubl
 int erem_assemble_transmissibilities(erem_ctx* c, const double* d_T) {
   if (!c) return EREM_EINVAL;
   if (!c->rock_set) return fail(c, EREM_EINVAL, "erem_set_rock must come first");
+  c->mg_current = false;
   HIP_TRY(c, launch_transmissibility(c->d, c->ph, c->logk, d_T, c->tx, c->ty, c->tz, c->stream));
   c->trans_set = true;
   return EREM_OK;
@@ -1184,7 +1186,7 @@ int erem_solve_pressure(erem_ctx* c, double rtol, int32_t max_iter, int32_t warm
   // only: the device builds the hierarchy while the host reads the residual
   // and enqueues the iterations, which queue behind it.  The residual does
   // not read the hierarchy.
-  bool setup_pending = c->use_mg;
+  bool setup_pending = c->use_mg && !c->mg_current;
   if (setup_pending && !c->ev_setup) HIP_TRY(c, hipEventCreateWithFlags(&c->ev_setup, hipEventDisableTiming));
   for (int outer = 0; outer < 8; ++outer) {
     HIP_TRY(c, launch_pcg_reset(c->pcg, 0.0, c->stream));
@@ -1196,6 +1198,7 @@ int erem_solve_pressure(erem_ctx* c, double rtol, int32_t max_iter, int32_t warm
     if (setup_pending) {
       HIP_TRY(c, hipEventRecord(c->ev_setup, c->stream));
       HIP_TRY(c, mg_setup(c->mg, c->stream));
+      c->mg_current = true;
       setup_pending = false;
       HIP_TRY(c, hipEventSynchronize(c->ev_setup));
     } else {

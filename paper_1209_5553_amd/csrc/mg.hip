@@ -51,11 +51,7 @@ __device__ inline bool pcg_done(const PcgState* st) { return st && *(volatile co
 // ---------------------------------------------------------------------------
 // Setup: coarse faces and diagonal from the fine faces.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void k_mg_coarsen(MgLevelDev F, MgLevelDev C) {
-  const int X = blockIdx.x * kBX + threadIdx.x;
-  const int Y = blockIdx.y * kBY + threadIdx.y;
-  const int Z = blockIdx.z;
-  if (X >= C.nx || Y >= C.ny) return;
+__device__ inline void coarsen_cell(const MgLevelDev& F, const MgLevelDev& C, int X, int Y, int Z) {
   const int fnx = F.nx, fny = F.ny, fnz = F.nz;
   const int y0 = 2 * Y, y1 = min(2 * Y + 1, fny - 1);
   const int x0 = 2 * X, x1 = min(2 * X + 1, fnx - 1);
@@ -98,65 +94,82 @@ __global__ __launch_bounds__(kThreads) void k_mg_coarsen(MgLevelDev F, MgLevelDe
   C.diag[X + cnx * (Y + cny * Z)] = w + e + s + n + b + t;
 }
 
-// Dense inverse of the bottom-level operator (SPD, diagonally dominant, so
-// Gauss-Jordan without pivoting is stable), one workgroup of 1024 threads
-// holding the matrix in registers (assembled in LDS).
+__global__ __launch_bounds__(kThreads) void k_mg_coarsen(MgLevelDev F, MgLevelDev C) {
+  const int X = blockIdx.x * kBX + threadIdx.x;
+  const int Y = blockIdx.y * kBY + threadIdx.y;
+  if (X < C.nx && Y < C.ny) coarsen_cell(F, C, X, Y, blockIdx.z);
+}
+
+// The tail of the setup in one workgroup of 1024 threads: the coarse levels of
+// the one-workgroup solve (a.lev[1] .. from a.lev[0] on; too small to be worth a
+// launch each), then the dense inverse of the bottom operator by Gauss-Jordan
+// (SPD, diagonally dominant, so it is stable without pivoting), the matrix in
+// registers: thread t keeps row t / 16, columns 4 (t % 16) .. + 3; the new pivot
+// row and the pivot column go through LDS, double buffered, a barrier per pivot.
+// The chain of pivots is what it costs, 0.5 us each.  Only the wavefront that owns
+// the pivot row divides and scales it.  Tail and inverse together take 41 us, what
+// the inverse alone took when all sixteen wavefronts divided, four to a SIMD; the
+// three launches of the tail are saved.  Rows and columns past n carry values that
+// are never stored.
 static_assert(kMgBottomCells <= 64, "the bottom inverse maps 64 rows x 16 column groups of 4 onto 1024 threads");
-__global__ __launch_bounds__(1024) void k_mg_bottom_inverse(MgLevelDev L, double* __restrict__ inv) {
-  __shared__ double M[kMgBottomCells * kMgBottomCells];
-  __shared__ double prow[2][kMgBottomCells];
-  __shared__ double pcol[2][kMgBottomCells];
+__global__ __launch_bounds__(1024) void k_mg_bottom_inverse(MgCoarseArgs a, double* __restrict__ inv) {
+  __shared__ double M[64 * 64];
+  __shared__ double prow[2][64];
+  __shared__ double pcol[2][64];
+  for (int l = 0; l + 1 < a.nlev; ++l) {
+    const MgLevelDev &F = a.lev[l], &C = a.lev[l + 1];
+    for (int c = threadIdx.x; c < C.nx * C.ny * C.nz; c += 1024)
+      coarsen_cell(F, C, c % C.nx, (c / C.nx) % C.ny, c / (C.nx * C.ny));
+    __syncthreads();
+  }
+  const MgLevelDev& L = a.lev[a.nlev - 1];
   const int n = L.nx * L.ny * L.nz;
-  for (int j = threadIdx.x; j < n * n; j += blockDim.x) M[j] = 0.0;
+  for (int j = threadIdx.x; j < 64 * 64; j += 1024) M[j] = 0.0;
   __syncthreads();
-  for (int c = threadIdx.x; c < n; c += blockDim.x) {
+  if (static_cast<int>(threadIdx.x) < n) {
+    const int c = threadIdx.x;
     const int x = c % L.nx, y = (c / L.nx) % L.ny, z = c / (L.nx * L.ny);
     // diagonal = sum of the cell's face transmissibilities (Dirichlet faces
     // included), formed here so that the finest level needs no other setup
     double dg = L.tx[fxi(L.nx, L.ny, x, y, z)] + L.tx[fxi(L.nx, L.ny, x + 1, y, z)] +
                 L.ty[fyi(L.nx, L.ny, x, y, z)] + L.ty[fyi(L.nx, L.ny, x, y + 1, z)];
     if (L.nz > 1) dg += L.tz[fzi(L.nx, L.ny, x, y, z)] + L.tz[fzi(L.nx, L.ny, x, y, z + 1)];
-    M[c * n + c] = dg;
-    if (x > 0) M[c * n + c - 1] = -L.tx[fxi(L.nx, L.ny, x, y, z)];
-    if (x + 1 < L.nx) M[c * n + c + 1] = -L.tx[fxi(L.nx, L.ny, x + 1, y, z)];
-    if (y > 0) M[c * n + c - L.nx] = -L.ty[fyi(L.nx, L.ny, x, y, z)];
-    if (y + 1 < L.ny) M[c * n + c + L.nx] = -L.ty[fyi(L.nx, L.ny, x, y + 1, z)];
-    if (z > 0) M[c * n + c - L.nx * L.ny] = -L.tz[fzi(L.nx, L.ny, x, y, z)];
-    if (z + 1 < L.nz) M[c * n + c + L.nx * L.ny] = -L.tz[fzi(L.nx, L.ny, x, y, z + 1)];
+    double* row = M + c * 64 + c;
+    row[0] = dg;
+    if (x > 0) row[-1] = -L.tx[fxi(L.nx, L.ny, x, y, z)];
+    if (x + 1 < L.nx) row[1] = -L.tx[fxi(L.nx, L.ny, x + 1, y, z)];
+    if (y > 0) row[-L.nx] = -L.ty[fyi(L.nx, L.ny, x, y, z)];
+    if (y + 1 < L.ny) row[L.nx] = -L.ty[fyi(L.nx, L.ny, x, y + 1, z)];
+    if (z > 0) row[-L.nx * L.ny] = -L.tz[fzi(L.nx, L.ny, x, y, z)];
+    if (z + 1 < L.nz) row[L.nx * L.ny] = -L.tz[fzi(L.nx, L.ny, x, y, z + 1)];
   }
   __syncthreads();
-  // Gauss-Jordan in place, no pivoting (the operator is SPD).  Thread t keeps
-  // row t / 16, columns 4 (t % 16) .. 4 (t % 16) + 3 in registers; the pivot
-  // row and column go through LDS, double-buffered so that one barrier per
-  // pivot suffices.  Rows and columns past n carry values that are never
-  // stored, so the update runs without branches (selects only).
   const int t = threadIdx.x;
-  const int i = t >> 4, j0 = (t & 15) * 4;
+  const int i = t >> 4, g = t & 15, j0 = 4 * g;
   double m[4];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) m[u] = (i < n && j0 + u < n) ? M[i * n + j0 + u] : 0.0;
+  for (int u = 0; u < 4; ++u) m[u] = M[i * 64 + j0 + u];
   for (int k = 0; k < n; ++k) {
-    const int b = k & 1;
-    if (i == k) {
+    const int b = k & 1, u = k & 3;
+    if (i >> 2 == k >> 2) {
+      // this wavefront has row k, its pivot in lane 16 (k % 4) + k / 4
+      const double piv = 1.0 / lane_of(u == 0 ? m[0] : u == 1 ? m[1] : u == 2 ? m[2] : m[3], 16 * u + (k >> 2));
+      if (i == k) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) prow[b][j0 + u] = m[u];
+        for (int v = 0; v < 4; ++v) {
+          m[v] = j0 + v == k ? piv : m[v] * piv;
+          prow[b][j0 + v] = m[v];
+        }
+      }
     }
-    if ((k >> 2) == (t & 15)) {
-      const int u = k & 3;
-      pcol[b][i] = u == 0 ? m[0] : u == 1 ? m[1] : u == 2 ? m[2] : m[3];
-    }
+    if (g == k >> 2) pcol[b][i] = u == 0 ? m[0] : u == 1 ? m[1] : u == 2 ? m[2] : m[3];
     __syncthreads();
-    const double piv = 1.0 / prow[b][k];
     const double ci = pcol[b][i];
-    double rj[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) rj[u] = prow[b][j0 + u];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int j = j0 + u;
-      const double pr = j == k ? piv : rj[u] * piv;  // new pivot row
-      const double upd = m[u] - ci * pr;
-      m[u] = i == k ? pr : (j == k ? -ci * piv : upd);
+    for (int v = 0; v < 4; ++v) {
+      const double pr = prow[b][j0 + v];
+      const double upd = j0 + v == k ? -ci * pr : m[v] - ci * pr;
+      m[v] = i == k ? m[v] : upd;
     }
   }
   if (i < n) {
@@ -416,7 +429,7 @@ __global__ __launch_bounds__(kBoxT) __attribute__((amdgpu_waves_per_eu(8))) void
       cg.x[j] = xo + alpha * pn;
       rr2 = bp * bp;
     }
-    for (int off = 32; off > 0; off >>= 1) rr2 += __shfl_down(rr2, off, 64);
+    rr2 = wave_sum(rr2);
     if (lane == 0) w = rr2;  // stored after the next barrier (rrs[0] is still being read)
   } else if (stop) {
     return;
@@ -502,10 +515,8 @@ __global__ __launch_bounds__(kBoxT) __attribute__((amdgpu_waves_per_eu(8))) void
     g = bi * x;
     dz = w * x;
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    g += __shfl_down(g, off, 64);
-    dz += __shfl_down(dz, off, 64);
-  }
+  g = wave_sum(g);
+  dz = wave_sum(dz);
   if (lane == 0) {
     sh[0][row] = g;
     sh[1][row] = dz;
@@ -1164,13 +1175,15 @@ __global__ __launch_bounds__(kMgLdsCells) void k_mg_coarse_2d(MgCoarseArgs a, Mg
 }  // namespace
 
 hipError_t mg_setup(const MgHierarchy& h, hipStream_t s) {
-  for (int l = 1; l <= h.lb; ++l) {
+  // the levels down to the first LDS level one by one, the rest with the bottom
+  // inverse
+  for (int l = 1; l <= h.lc; ++l) {
     const MgLevelDev& F = h.lev[l - 1];
     const MgLevelDev& C = h.lev[l];
     const dim3 grid((C.nx + kBX - 1) / kBX, (C.ny + kBY - 1) / kBY, C.nz);
     hipLaunchKernelGGL(k_mg_coarsen, grid, cell_block(), 0, s, F, C);
   }
-  hipLaunchKernelGGL(k_mg_bottom_inverse, dim3(1), dim3(1024), 0, s, h.lev[h.lb], h.binv);
+  hipLaunchKernelGGL(k_mg_bottom_inverse, dim3(1), dim3(1024), 0, s, h.coarse, h.binv);
   return hipGetLastError();
 }
 

@@ -622,6 +622,66 @@ def test_krylov_3d_matches_dense_oracle(torch_mod):
     assert err <= TOL
 
 
+def _diffusive_stencil(rng, nx, ny, nz):
+    """(ndir, N) stencil with zero couplings out of the grid and row sums <= 0."""
+    n = nx * ny * nz
+    shape = (nz, ny, nx)
+    coef = np.zeros((7 if nz > 1 else 5, n))
+    i = np.indices(shape)
+    edges = [i[2] > 0, i[2] < nx - 1, i[1] > 0, i[1] < ny - 1, i[0] > 0, i[0] < nz - 1]
+    for k in range(1, coef.shape[0]):
+        coef[k] = np.where(edges[k - 1].ravel(), 1.0 + 0.3 * rng.random(n), 0.0)
+    coef[0] = -coef[1:].sum(axis=0) - 0.1
+    return coef
+
+
+@pytest.mark.parametrize("shape", [(5, 3, 1), (1, 64, 1), (33, 31, 1), (32, 32, 1), (41, 25, 1), (64, 32, 1), (64, 64, 1),
+                                   (4096, 1, 1), (241, 17, 1), (3, 2, 2), (16, 16, 4), (5, 5, 41), (2, 512, 2),
+                                   (16, 16, 8), (683, 1, 3)])
+@pytest.mark.parametrize("opts", [{}, {"m_max": 13}, {"precision": 1, "tol_r": 1e-7}])
+def test_small_grid_phi1_edges_match_oracle(torch_mod, shape, opts):
+    """Grids at and beside the cell counts where the one-workgroup evaluation takes
+    another number of cells per thread (1024, 2048) or gives way to the passes (4096
+    cells in 2D, 2048 in 3D), with one and several substeps, and in FP32."""
+    torch = torch_mod
+    from paper_1209_5553_amd.api import EremContext, make_opts
+    nx, ny, nz = shape
+    n = nx * ny * nz
+    rng = np.random.default_rng(n + nx)
+    coef = _diffusive_stencil(rng, nx, ny, nz)
+    v = rng.standard_normal(n)
+    ctx = EremContext(nx, ny, nz, device="cuda:0") if nz > 1 else EremContext(nx, ny, device="cuda:0")
+    ctx.set_jacobian(_dev(torch, coef), torch.zeros(n, dtype=torch.float64, device="cuda:0"))
+    _say(f"small grid {shape} {opts}")
+    h = 2.0
+    out, st = ctx.phi1_apply(h, _dev(torch, v), opts=make_opts(**opts))
+    _say(f"  {st}")
+    ref = ophi.hphi1_action_taylor(stencil_to_sparse(coef, nx, ny, nz), v, h) / h
+    assert rel_inf(out.cpu().numpy(), ref) <= (1e-5 if "precision" in opts else TOL)
+
+
+@pytest.mark.parametrize("shape,m", [((1024, 256, 1), 12), ((1024, 257, 1), 13), ((67, 65, 61), 14)])
+def test_krylov_folded_sums_match_oracle(torch_mod, shape, m):
+    """1024 workgroups add up each other's partial sums, one more and a fold does;
+    and bases at and past the twelve vectors a cell holds in registers."""
+    torch = torch_mod
+    from paper_1209_5553_amd.api import EremContext
+    nx, ny, nz = shape
+    n = nx * ny * nz
+    rng = np.random.default_rng(n)
+    coef = _diffusive_stencil(rng, nx, ny, nz)
+    v = rng.standard_normal(n)
+    ctx = EremContext(nx, ny, nz, device="cuda:0") if nz > 1 else EremContext(nx, ny, device="cuda:0")
+    ctx.set_jacobian(_dev(torch, coef), torch.zeros(n, dtype=torch.float64, device="cuda:0"))
+    _say(f"krylov {shape} m={m}")
+    h = 2.0
+    out, st = ctx.phi1_apply(h, _dev(torch, v), opts=_krylov_opts(m))
+    ref = ophi.hphi1_action_taylor(stencil_to_sparse(coef, nx, ny, nz), v, h) / h
+    err = rel_inf(out.cpu().numpy(), ref)
+    _say(f"  arnoldi steps={st['m_total']} substeps={st['substeps']} err={err:.2e}")
+    assert err <= TOL
+
+
 # ------------------------------------------------------- mixed precision
 
 MIXED_TOL = 1e-5

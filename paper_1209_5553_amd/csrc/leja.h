@@ -10,11 +10,14 @@ namespace erem {
 constexpr int kLejaRing = 16;       // terms whose block partials are kept
 constexpr int kCheckEvery = 4;      // terms between stop tests
 constexpr int kTermsPerPass2 = 4;   // terms per pass on 2D grids: one stop-test group
-// Rows per wavefront of the 2D pass: four while that gives at most kTermFew
-// workgroups (333 x 77: 188 us a phi1 action against 203 with eight), else
-// eight (512 x 512: 1.16 times the time with four, 1.09 times with sixteen),
-// more once the workgroups would pass kGateMax.
-constexpr int kTermRowsFew = 4, kTermRows = 8, kTermFew = 64;
+// Most boxes of the 2D box pass with one and with two rows per thread: one box a
+// CU.  An FP64 phi1 action of 32 terms, one row / two rows / rows marched: 256 x 256
+// (155 / 55 boxes) 107 / 117 / 144 us; 512 x 512 (630 / 210) 185 / 129 / 154; 640 x
+// 640 (960 / 324) 226 / 175 / 161.
+constexpr int kBoxOne = 256, kBoxTwo = 256;
+// Rows per wavefront of the 2D marching pass, more once the workgroups would pass
+// kGateMax (512 x 512: four rows 1.16 times the time, sixteen 1.09 times).
+constexpr int kTermRows = 8;
 constexpr int kZmarchRows = 16;     // rows of the 3D pass's tile (64 wide)
 constexpr int kZmarchStrip = 2;     // cells per thread of its box
 constexpr int kZmarchThreads = 640;
@@ -69,8 +72,7 @@ template <class V>
 hipError_t leja_substep(const Dims& d, const LejaCoef* cf, const LejaVecs<V>& B, const double* src, LejaState* st,
                         double* part, int K, double* out, double delta, int first, const double* zt, hipStream_t s,
                         hipEvent_t* ev, int prof);
-// A whole evaluation of s substeps on a small grid in one
-// launch (leja_small.hip): out = sum of the substeps' increments, source v + t_j g
+// A whole evaluation of s substeps on a small grid in one launch (leja_small.hip): out = sum of the substeps' increments, source v + t_j g
 // (g null: v), zt (or null) added per substep; the stop states st[0 .. s) as
 // leja_substep leaves them.  coef64: the stencil in FP64; coef: in the passes'
 // precision.

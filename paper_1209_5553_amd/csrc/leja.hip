@@ -40,6 +40,17 @@ __device__ inline double block_sum256(double v) {
   return t == 0 ? sh[0] + sh[1] + sh[2] + sh[3] : 0.0;
 }
 
+// Rows of tile j of k_leja_box, H to a box: as march_strip's columns.
+template <int H>
+__host__ __device__ inline MarchStrip box_rows(int ny, int j) {
+  constexpr int inner = H - 2 * kTermsPerPass2;
+  MarchStrip s;
+  s.xs = j * inner;
+  s.x0 = j == 0 ? 0 : s.xs + kTermsPerPass2;
+  s.x1 = s.xs + H >= ny ? ny : s.xs + H - kTermsPerPass2;
+  return s;
+}
+
 __device__ inline int block_id() { return blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z); }
 
 __global__ void k_leja_reset(LejaState* st, int nslots, int nterms) {
@@ -165,12 +176,11 @@ __global__ __launch_bounds__(kThreads) void k_leja_term(Dims d, const LejaCoef* 
   if (threadIdx.x == 0 && threadIdx.y == 0) part[(k % kLejaRing) * nb + tile] = s;  // slot of the tile
 }
 
-// Four Newton terms in one pass on 2D grids (march.h): a workgroup's four
+// Four Newton terms in one pass on large 2D grids (march.h): a workgroup's four
 // wavefronts take four consecutive chunks of rows of one strip, and leave one
-// partial per term.  On grids of up to 512 x 512 the pass is a chain of
-// latencies: launch, first rows, stop test, some 16 rows; 10 us with its stop
-// test, where a pass with LDS tiles (9 us) and a stop-test launch (6.6 us) took
-// 16 and two launch gaps.
+// partial per term.  At 640 x 640 a pass is still half latencies (launch, first
+// rows, stop test, 16 rows): 10 us with its stop test, where a pass with LDS tiles
+// and a stop-test launch took 16 and two launch gaps.
 template <int NT, class V>
 __global__ __launch_bounds__(kThreads) void k_leja_terms(Dims d, const LejaCoef* __restrict__ cf,
                                                const V* __restrict__ coef, const V* __restrict__ qin,
@@ -206,6 +216,121 @@ __global__ __launch_bounds__(kThreads) void k_leja_terms(Dims d, const LejaCoef*
   if (threadIdx.x < NT) {
     const int t = threadIdx.x;
     part[((k + t) % kLejaRing) * stride + tile] = red[t][0] + red[t][1] + red[t][2] + red[t][3];
+  }
+}
+
+// Four Newton terms in one pass on small 2D grids: a workgroup of sixteen
+// wavefronts holds a box of 64 columns x 16 R rows, R cells of a column per thread,
+// and forms the four terms on a box that shrinks by a cell a side per term.  q's
+// east and west neighbours come from the neighbouring lanes, the rows above and
+// below from LDS (double buffered, a barrier per term).  The first pass of a
+// substep (FIRST) also sets q_0 = src and p_0 = d_0 q_0 and has a fifth partial, of
+// term 0.
+//
+// On a grid that does not fill the chip a pass is a chain of latencies.  All loads
+// of the box go out at once, ahead of the stop test, where k_leja_terms waits for
+// its rows in turn: 333 x 77 8.1 -> 5.5 us a pass and a phi1 action, with the start
+// pass gone, 168 -> 141 us; 512 x 512 9.1 -> 6.8 us.  Past one box per CU the rows
+// loaded twice (16 R for 16 R - 8) and the second round cost more than that.
+template <int R, bool FIRST, class V>
+__global__ __launch_bounds__(1024) void k_leja_box(Dims d, const LejaCoef* __restrict__ cf,
+                                         const V* __restrict__ coef, const double* __restrict__ src,
+                                         const V* __restrict__ qin, V* __restrict__ qout, V* __restrict__ p,
+                                         LejaState* st, double* __restrict__ part, LejaGate g, int stride, int k) {
+  constexpr int NT = kTermsPerPass2, NW = 16, H = NW * R;
+  __shared__ V sq[2][H + 2][kMarchLanes];  // a row of zeros below and above the box
+  __shared__ double red[NT + 1][NW];
+  const int tile = xcd_tile_id();
+  const int strips = march_strips(d.nx, NT);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const MarchStrip sx = march_strip(d.nx, NT, tile % strips), sy = box_rows<H>(d.ny, tile / strips);
+  const int gx = sx.xs + lane;
+  const bool xout = gx >= sx.x0 && gx < sx.x1;
+  V c[R][5], q[R], pv[R];
+  int cell[R];
+  bool in[R], out[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int gy = sy.xs + wave * R + r;
+    in[r] = gx < d.nx && gy < d.ny;
+    out[r] = xout && gy >= sy.x0 && gy < sy.x1;
+    cell[r] = min(gx, d.nx - 1) + d.nx * min(gy, d.ny - 1);  // every load is valid
+    q[r] = FIRST ? to_v<V>(src[cell[r]]) : qin[cell[r]];
+    if (!FIRST) pv[r] = p[cell[r]];
+#pragma unroll
+    for (int e = 0; e < 5; ++e) c[r][e] = coef[static_cast<long long>(e) * d.N + cell[r]];
+  }
+  const V ig = to_v<V>(cf->inv_g);
+  V shift[NT], dk[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    shift[t] = to_v<V>(cf->shift[k + t]);
+    dk[t] = to_v<V>(cf->dk[k + t]);
+  }
+  const V d0 = FIRST ? to_v<V>(cf->dk[0]) : V(0);
+  __builtin_amdgcn_sched_barrier(0);
+  if (wave == 0 || wave == NW - 1) {
+    sq[0][wave == 0 ? 0 : H + 1][lane] = V(0);
+    sq[1][wave == 0 ? 0 : H + 1][lane] = V(0);
+  }
+  if (leja_gate<NW>(cf, st, g, tile == 0)) return;
+  double sum[NT], s0 = 0.0;
+#pragma unroll
+  for (int t = 0; t < NT; ++t) sum[t] = 0.0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    q[r] = in[r] ? q[r] : V(0);
+#pragma unroll
+    for (int e = 0; e < 5; ++e) c[r][e] = in[r] ? c[r][e] : V(0);
+    if (FIRST) {
+      pv[r] = d0 * q[r];
+      const double v = out[r] ? static_cast<double>(q[r]) : 0.0;
+      s0 += v * v;
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int y = wave * R + 1;  // LDS row of the thread's first cell
+#pragma unroll
+    for (int r = 0; r < R; ++r) sq[t & 1][y + r][lane] = q[r];
+    __syncthreads();
+    V qo[R];
+    const V below = sq[t & 1][y - 1][lane], above = sq[t & 1][y + R][lane];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      V jq = c[r][1] * west(q[r]);
+      jq = fma(c[r][0], q[r], jq);
+      jq = fma(c[r][2], east(q[r]), jq);
+      jq = fma(c[r][3], r > 0 ? q[r > 0 ? r - 1 : 0] : below, jq);
+      jq = fma(c[r][4], r + 1 < R ? q[r + 1 < R ? r + 1 : 0] : above, jq);
+      qo[r] = fma(jq, ig, -(shift[t] * q[r]));
+      pv[r] = fma(dk[t], qo[r], pv[r]);
+      const double v = out[r] ? static_cast<double>(qo[r]) : 0.0;
+      sum[t] += v * v;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) q[r] = qo[r];
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (!out[r]) continue;
+    p[cell[r]] = pv[r];
+    qout[cell[r]] = q[r];
+  }
+  static_assert(NT == 4, "the sums of a pass are reduced together");
+  const double s4 = sum4(sum, lane);
+  if (lane < NT) red[lane][wave] = s4;
+  if (FIRST) {
+    s0 = wave_sum(s0);
+    if (lane == 0) red[NT][wave] = s0;
+  }
+  __syncthreads();
+  const int t = threadIdx.x;
+  if (t < NT + (FIRST ? 1 : 0)) {
+    double s = red[t][0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) s += red[t][w];
+    part[(t < NT ? (k + t) % kLejaRing : 0) * stride + tile] = s;
   }
 }
 
@@ -669,12 +794,10 @@ __global__ __launch_bounds__(kCoefThreads) void k_leja_coef(LejaCoefArgs a) {
 
 namespace {
 
-// Rows per chunk of the 2D pass: short chunks while the grid leaves wavefront
-// slots idle, longer ones once the workgroups (and so the partials that every
-// workgroup adds up) would pass kGateMax.
+// Rows per chunk of the 2D marching pass: longer chunks once the workgroups (and so
+// the partials that every workgroup adds up) would pass kGateMax.
 int terms_rows(const Dims& d) {
   const long long strips = march_strips(d.nx, kTermsPerPass2);
-  if (strips * ((d.ny + 4 * kTermRowsFew - 1) / (4 * kTermRowsFew)) <= kTermFew) return kTermRowsFew;
   int rows = kTermRows;
   while (strips * ((d.ny + 4ll * rows - 1) / (4ll * rows)) > kGateMax && rows < d.ny &&
          static_cast<long long>(d.nx) * (2 * rows + 2 * kTermsPerPass2) < (1ll << 27))
@@ -689,8 +812,21 @@ int zmarch_planes(const Dims& d) {
   return static_cast<int>((d.nz + chunks - 1) / chunks);
 }
 
+// Boxes of 16 R rows, and the rule: rows per thread of the box pass, 0 where a grid
+// has more boxes than CUs even with two.
+int box_blocks(const Dims& d, int R) {
+  const int H = 16 * R, inner = H - 2 * kTermsPerPass2;
+  const long long rows = d.ny <= H ? 1 : 1 + (d.ny - H + inner - 1) / inner;
+  return static_cast<int>(std::min<long long>(march_strips(d.nx, kTermsPerPass2) * rows, 1 << 30));
+}
+int box_cells(const Dims& d) {
+  if (d.dim != 2) return 0;
+  return box_blocks(d, 1) <= kBoxOne ? 1 : box_blocks(d, 2) <= kBoxTwo ? 2 : 0;
+}
+
 int terms_blocks(const Dims& d) {
   if (d.dim == 2) {
+    if (const int R = box_cells(d)) return box_blocks(d, R);
     const long long rows = terms_rows(d);
     return static_cast<int>(march_strips(d.nx, kTermsPerPass2) * ((d.ny + 4 * rows - 1) / (4 * rows)));
   }
@@ -740,16 +876,24 @@ hipError_t launch_leja_term(const Dims& d, const LejaCoef* cf, const V* coef, co
 
 namespace {
 
+// src (or null): the first pass of a substep, on a grid of the box pass.
 template <class V>
-hipError_t launch_terms(const Dims& d, const LejaCoef* cf, const V* coef, const V* qin, V* qout, V* p, LejaState* st,
-                        double* part, const LejaGate& g, int k, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+hipError_t launch_terms(const Dims& d, const LejaCoef* cf, const V* coef, const double* src, const V* qin, V* qout, V* p,
+                        LejaState* st, double* part, const LejaGate& g, int k, hipStream_t s, hipEvent_t e0,
+                        hipEvent_t e1) {
   const int nb = leja_slots(d);
-  if (d.dim == 2)
-    launch_timed(k_leja_terms<kTermsPerPass2, V>, dim3(terms_blocks(d)), dim3(kThreads), 0, s, e0, e1, d, cf, coef,
-                 qin, qout, p, st, part, g, nb, terms_rows(d), k);
-  else
-    launch_timed(k_leja_zmarch<kZmarchRows, kZmarchStrip, kZmarchThreads, V>, dim3(terms_blocks(d)),
-                 dim3(kZmarchThreads), 0, s, e0, e1, d, cf, coef, qin, qout, p, st, part, g, nb, zmarch_planes(d), k);
+  const dim3 grid(terms_blocks(d));
+  if (const int R = box_cells(d)) {
+    const auto kernel = src ? (R == 1 ? k_leja_box<1, true, V> : k_leja_box<2, true, V>)
+                            : (R == 1 ? k_leja_box<1, false, V> : k_leja_box<2, false, V>);
+    launch_timed(kernel, grid, dim3(1024), 0, s, e0, e1, d, cf, coef, src, qin, qout, p, st, part, g, nb, k);
+  } else if (d.dim == 2) {
+    launch_timed(k_leja_terms<kTermsPerPass2, V>, grid, dim3(kThreads), 0, s, e0, e1, d, cf, coef, qin, qout, p, st,
+                 part, g, nb, terms_rows(d), k);
+  } else {
+    launch_timed(k_leja_zmarch<kZmarchRows, kZmarchStrip, kZmarchThreads, V>, grid, dim3(kZmarchThreads), 0, s, e0,
+                 e1, d, cf, coef, qin, qout, p, st, part, g, nb, zmarch_planes(d), k);
+  }
   return hipGetLastError();
 }
 
@@ -783,11 +927,13 @@ template <class V>
 hipError_t leja_substep(const Dims& d, const LejaCoef* cf, const LejaVecs<V>& B, const double* src, LejaState* st,
                         double* part, int K, double* out, double delta, int first, const double* zt, hipStream_t s,
                         hipEvent_t* ev, int prof) {
-  hipError_t e = launch_leja_init<V>(d, cf, src, B.qa, B.p, part, s);
-  if (e != hipSuccess) return e;
-  int cnt[kLejaRing] = {};  // partials of the terms in the ring
-  cnt[0] = init_blocks(d);
   const int nterms = terms_blocks(d), nterm = cell_bands(d);
+  int cnt[kLejaRing] = {};  // partials of the terms in the ring
+  // the box pass makes the start vectors itself
+  const bool fused = box_cells(d) > 0 && leja_terms_per_launch(d, 1, K) > 1;
+  cnt[0] = fused ? nterms : init_blocks(d);
+  hipError_t e = fused ? hipSuccess : launch_leja_init<V>(d, cf, src, B.qa, B.p, part, s);
+  if (e != hipSuccess) return e;
   V* cur = B.qa;
   V* oth = B.qb;
   int prev = -1;  // last term already tested
@@ -804,7 +950,7 @@ hipError_t leja_substep(const Dims& d, const LejaCoef* cf, const LejaVecs<V>& B,
       prev = k - 1;
     }
     if (nt > 1) {
-      e = launch_terms<V>(d, cf, B.coef, cur, oth, B.p, st, part, g, k, s, e0, e1);
+      e = launch_terms<V>(d, cf, B.coef, fused && k == 1 ? src : nullptr, cur, oth, B.p, st, part, g, k, s, e0, e1);
     } else {
       // the one-term pass only reads the flag: the test is made before it
       if (g.k2 >= g.k1) {

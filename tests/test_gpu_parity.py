@@ -660,6 +660,16 @@ def test_small_grid_phi1_edges_match_oracle(torch_mod, shape, opts):
     assert rel_inf(out.cpu().numpy(), ref) <= (1e-5 if "precision" in opts else TOL)
 
 
+@pytest.mark.parametrize("shape", [(64, 80, 1), (65, 81, 1), (120, 72, 1), (121, 73, 1), (1366, 3, 1), (64, 2056, 1),
+                                   (64, 2057, 1), (65, 1111, 1), (64, 6152, 1), (64, 6153, 1)])
+@pytest.mark.parametrize("opts", [{}, {"m_max": 13}, {"precision": 1, "tol_r": 1e-7}])
+def test_box_pass_edges_match_oracle(torch_mod, shape, opts):
+    """Grids at and beside the edges of the 2D box pass (64 columns, 56 of them new, by
+    16 or 32 rows, 8 or 24 new) and at both its limits of 256 boxes, with a term budget
+    that is no multiple of a pass (13) and in FP32."""
+    test_small_grid_phi1_edges_match_oracle(torch_mod, shape, opts)
+
+
 @pytest.mark.parametrize("shape,m", [((1024, 256, 1), 12), ((1024, 257, 1), 13), ((67, 65, 61), 14)])
 def test_krylov_folded_sums_match_oracle(torch_mod, shape, m):
     """1024 workgroups add up each other's partial sums, one more and a fold does;

@@ -18,6 +18,11 @@ constexpr int kBoxOne = 256, kBoxTwo = 256;
 // Rows per wavefront of the 2D marching pass, more once the workgroups would pass
 // kGateMax (512 x 512: four rows 1.16 times the time, sixteen 1.09 times).
 constexpr int kTermRows = 8;
+// Box of the 3D box pass, planes of its output, and most boxes: one a CU.  An FP64
+// phi1 action of 36 terms, boxes / planes marched: 50^3 (200 boxes) 189 / 250 us,
+// 64^3 (480) 268 / 257, 80^3 (1120) 455 / 381.  On 50^3 one plane a box took 209 us,
+// three 200; boxes of 32 x 8 columns 215, of 64 x 16 246.
+constexpr int kCubeX = 32, kCubeY = 16, kCubeZ = 2, kCubeMax = 256;
 constexpr int kZmarchRows = 16;     // rows of the 3D pass's tile (64 wide)
 constexpr int kZmarchStrip = 2;     // cells per thread of its box
 constexpr int kZmarchThreads = 640;

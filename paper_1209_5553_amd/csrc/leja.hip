@@ -51,6 +51,16 @@ __host__ __device__ inline MarchStrip box_rows(int ny, int j) {
   return s;
 }
 
+// Tiles of k_leja_cube along a direction of n cells, W to a box, and tile j.
+__host__ __device__ inline int cube_tiles(int n, int W) { return n <= W ? 1 : 1 + (n - W + W - 5) / (W - 4); }
+__host__ __device__ inline MarchStrip cube_tile(int n, int W, int j) {
+  MarchStrip s;
+  s.xs = j * (W - 4);
+  s.x0 = j == 0 ? 0 : s.xs + 2;
+  s.x1 = s.xs + W >= n ? n : s.xs + W - 2;
+  return s;
+}
+
 __device__ inline int block_id() { return blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z); }
 
 __global__ void k_leja_reset(LejaState* st, int nslots, int nterms) {
@@ -348,8 +358,7 @@ __global__ __launch_bounds__(1024) void k_leja_box(Dims d, const LejaCoef* __res
 // Bound by memory: per cell and pair of terms the seven stencil words, q_{k-1},
 // p in and out and the last q, 88 B where two one-term passes move 176.  On
 // 256^3 (FP64, 1.5 GB a pass, six times the Infinity Cache) 248 -> 133 us per
-// term, 5.5 TB/s; on 128^3 28 -> 19 us; on 50^3, where a launch costs more than
-// its bytes, 4.4 us and a stop-test launch per four terms -> 3.7 us.
+// term, 5.5 TB/s; on 128^3 28 -> 19 us.
 template <int TY, int SH, int NTH, class V>
 __global__ __launch_bounds__(NTH) void k_leja_zmarch(Dims d, const LejaCoef* __restrict__ cf,
                                            const V* __restrict__ coef, const V* __restrict__ qin,
@@ -544,6 +553,127 @@ __global__ __launch_bounds__(NTH) void k_leja_zmarch(Dims d, const LejaCoef* __r
     double s = red[tid][0];
     for (int w = 1; w < NW; ++w) s += red[tid][w];
     part[((k + tid) % kLejaRing) * stride + tile] = s;
+  }
+}
+
+// Two Newton terms in one pass on small 3D grids: a workgroup of eight wavefronts
+// holds a box of 32 x 16 columns, a thread a column of ZC planes and two more on
+// either side, and forms term k on ZC + 2 planes and term k + 1 on the ZC of the
+// output, 28 x 12 columns.  East and west neighbours come from the neighbouring
+// lanes (a row's first and last take a wrong one, in the halo or against a
+// coefficient of 0), north and south ones from LDS, above and below are the
+// thread's own.  FIRST as in k_leja_box.
+template <int ZC, bool FIRST, class V>
+__global__ __launch_bounds__(kCubeX * kCubeY) void k_leja_cube(Dims d, const LejaCoef* __restrict__ cf,
+                                                     const V* __restrict__ coef, const double* __restrict__ src,
+                                                     const V* __restrict__ qin, V* __restrict__ qout,
+                                                     V* __restrict__ p, LejaState* st, double* __restrict__ part,
+                                                     LejaGate g, int stride, int k) {
+  constexpr int NW = kCubeX * kCubeY / 64, NZ = ZC + 2;  // planes of term k
+  __shared__ V sq[NZ][kCubeY + 2][kCubeX], s1[ZC][kCubeY + 2][kCubeX];
+  __shared__ double red[3][NW];
+  const int nx = d.nx, ny = d.ny, nz = d.nz, N = d.N;
+  const int tile = xcd_tile_id();
+  const int tx = cube_tiles(nx, kCubeX), ty = cube_tiles(ny, kCubeY);
+  const MarchStrip bx = cube_tile(nx, kCubeX, tile % tx), by = cube_tile(ny, kCubeY, (tile / tx) % ty);
+  const int z0 = tile / (tx * ty) * ZC;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lx = tid % kCubeX, ly = tid / kCubeX;
+  const int gx = bx.xs + lx, gy = by.xs + ly;
+  const bool in = gx < nx && gy < ny;
+  const bool out = gx >= bx.x0 && gx < bx.x1 && gy >= by.x0 && gy < by.x1;
+  const int cell = min(gx, nx - 1) + nx * min(gy, ny - 1);  // every load is valid
+  auto plane = [&](int z) { return nx * ny * min(max(z, 0), nz - 1); };
+  V c[NZ][7], q[ZC + 4], pv[ZC];
+#pragma unroll
+  for (int u = 0; u < ZC + 4; ++u) {
+    const int o = plane(z0 - 2 + u);
+    q[u] = FIRST ? to_v<V>((src + o)[cell]) : (qin + o)[cell];
+  }
+#pragma unroll
+  for (int u = 0; u < NZ; ++u) {
+    const int o = plane(z0 - 1 + u);
+#pragma unroll
+    for (int e = 0; e < 7; ++e) c[u][e] = (coef + e * N + o)[cell];
+  }
+  if (!FIRST) {
+#pragma unroll
+    for (int u = 0; u < ZC; ++u) pv[u] = (p + plane(z0 + u))[cell];
+  }
+  const V ig = to_v<V>(cf->inv_g);
+  const V sh0 = to_v<V>(cf->shift[k]), sh1 = to_v<V>(cf->shift[k + 1]);
+  const V d0 = to_v<V>(cf->dk[k]), d1 = to_v<V>(cf->dk[k + 1]);
+  const V dz = FIRST ? to_v<V>(cf->dk[0]) : V(0);
+  __builtin_amdgcn_sched_barrier(0);
+  if (ly == 0 || ly == kCubeY - 1) {  // rows of zeros below and above the box
+    const int y = ly == 0 ? 0 : kCubeY + 1;
+#pragma unroll
+    for (int u = 0; u < NZ; ++u) sq[u][y][lx] = V(0);
+#pragma unroll
+    for (int u = 0; u < ZC; ++u) s1[u][y][lx] = V(0);
+  }
+  if (leja_gate<NW>(cf, st, g, tile == 0)) return;
+  double a0 = 0.0, a1 = 0.0, s0 = 0.0;
+#pragma unroll
+  for (int u = 0; u < ZC + 4; ++u) {
+    const int z = z0 - 2 + u;
+    q[u] = in && z >= 0 && z < nz ? q[u] : V(0);
+    if (u >= 1 && u <= NZ) sq[u - 1][ly + 1][lx] = q[u];
+  }
+  if (FIRST) {
+#pragma unroll
+    for (int u = 0; u < ZC; ++u) {
+      pv[u] = dz * q[u + 2];
+      const double v = out && z0 + u < nz ? static_cast<double>(q[u + 2]) : 0.0;
+      s0 += v * v;
+    }
+  }
+  __syncthreads();
+  V t[NZ];
+#pragma unroll
+  for (int u = 0; u < NZ; ++u) {
+    const int z = z0 - 1 + u;
+    const V qc = q[u + 1];
+    V jq = c[u][0] * qc;
+    jq = fma(c[u][1], west(qc), jq);
+    jq = fma(c[u][2], east(qc), jq);
+    jq = fma(c[u][3], sq[u][ly][lx], jq);
+    jq = fma(c[u][4], sq[u][ly + 2][lx], jq);
+    jq = fma(c[u][5], q[u], jq);
+    jq = fma(c[u][6], q[u + 2], jq);
+    const V v = fma(jq, ig, -(sh0 * qc));
+    t[u] = in && z >= 0 && z < nz ? v : V(0);
+    if (u >= 1 && u <= ZC) s1[u - 1][ly + 1][lx] = t[u];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < ZC; ++u) {
+    const V qc = t[u + 1];
+    V jq = c[u + 1][0] * qc;
+    jq = fma(c[u + 1][1], west(qc), jq);
+    jq = fma(c[u + 1][2], east(qc), jq);
+    jq = fma(c[u + 1][3], s1[u][ly][lx], jq);
+    jq = fma(c[u + 1][4], s1[u][ly + 2][lx], jq);
+    jq = fma(c[u + 1][5], t[u], jq);
+    jq = fma(c[u + 1][6], t[u + 2], jq);
+    const V v = fma(jq, ig, -(sh1 * qc));
+    if (out && z0 + u < nz) {
+      const int o = plane(z0 + u);
+      (p + o)[cell] = fma(d1, v, fma(d0, qc, pv[u]));
+      (qout + o)[cell] = v;
+      a0 += static_cast<double>(qc) * static_cast<double>(qc);
+      a1 += static_cast<double>(v) * static_cast<double>(v);
+    }
+  }
+  const double s4[4] = {a0, a1, s0, 0.0};
+  const double s = sum4(s4, lane);
+  if (lane < 3) red[lane][wave] = s;
+  __syncthreads();
+  if (tid < (FIRST ? 3 : 2)) {
+    double v = red[tid][0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += red[tid][w];
+    part[(tid < 2 ? (k + tid) % kLejaRing : 0) * stride + tile] = v;
   }
 }
 
@@ -824,12 +954,21 @@ int box_cells(const Dims& d) {
   return box_blocks(d, 1) <= kBoxOne ? 1 : box_blocks(d, 2) <= kBoxTwo ? 2 : 0;
 }
 
+// Boxes of the 3D box pass; 0 where a grid has too many for it.
+int cube_blocks(const Dims& d) {
+  if (d.dim != 3) return 0;
+  const long long n = static_cast<long long>(cube_tiles(d.nx, kCubeX)) * cube_tiles(d.ny, kCubeY) *
+                      ((d.nz + kCubeZ - 1) / kCubeZ);
+  return n <= kCubeMax ? static_cast<int>(n) : 0;
+}
+
 int terms_blocks(const Dims& d) {
   if (d.dim == 2) {
     if (const int R = box_cells(d)) return box_blocks(d, R);
     const long long rows = terms_rows(d);
     return static_cast<int>(march_strips(d.nx, kTermsPerPass2) * ((d.ny + 4 * rows - 1) / (4 * rows)));
   }
+  if (const int n = cube_blocks(d)) return n;
   const int zc = zmarch_planes(d);
   return static_cast<int>(((d.nx + kBX - 1) / kBX) * ((d.ny + kZmarchRows - 1) / kZmarchRows) *
                           ((d.nz + zc - 1) / zc));
@@ -876,7 +1015,7 @@ hipError_t launch_leja_term(const Dims& d, const LejaCoef* cf, const V* coef, co
 
 namespace {
 
-// src (or null): the first pass of a substep, on a grid of the box pass.
+// src (or null): the first pass of a substep, on a grid of a box pass.
 template <class V>
 hipError_t launch_terms(const Dims& d, const LejaCoef* cf, const V* coef, const double* src, const V* qin, V* qout, V* p,
                         LejaState* st, double* part, const LejaGate& g, int k, hipStream_t s, hipEvent_t e0,
@@ -887,6 +1026,9 @@ hipError_t launch_terms(const Dims& d, const LejaCoef* cf, const V* coef, const 
     const auto kernel = src ? (R == 1 ? k_leja_box<1, true, V> : k_leja_box<2, true, V>)
                             : (R == 1 ? k_leja_box<1, false, V> : k_leja_box<2, false, V>);
     launch_timed(kernel, grid, dim3(1024), 0, s, e0, e1, d, cf, coef, src, qin, qout, p, st, part, g, nb, k);
+  } else if (cube_blocks(d)) {
+    launch_timed(src ? k_leja_cube<kCubeZ, true, V> : k_leja_cube<kCubeZ, false, V>, grid, dim3(kCubeX * kCubeY), 0, s,
+                 e0, e1, d, cf, coef, src, qin, qout, p, st, part, g, nb, k);
   } else if (d.dim == 2) {
     launch_timed(k_leja_terms<kTermsPerPass2, V>, grid, dim3(kThreads), 0, s, e0, e1, d, cf, coef, qin, qout, p, st,
                  part, g, nb, terms_rows(d), k);
@@ -929,8 +1071,8 @@ hipError_t leja_substep(const Dims& d, const LejaCoef* cf, const LejaVecs<V>& B,
                         hipEvent_t* ev, int prof) {
   const int nterms = terms_blocks(d), nterm = cell_bands(d);
   int cnt[kLejaRing] = {};  // partials of the terms in the ring
-  // the box pass makes the start vectors itself
-  const bool fused = box_cells(d) > 0 && leja_terms_per_launch(d, 1, K) > 1;
+  // the box passes make the start vectors themselves
+  const bool fused = (box_cells(d) || cube_blocks(d)) && leja_terms_per_launch(d, 1, K) > 1;
   cnt[0] = fused ? nterms : init_blocks(d);
   hipError_t e = fused ? hipSuccess : launch_leja_init<V>(d, cf, src, B.qa, B.p, part, s);
   if (e != hipSuccess) return e;

@@ -661,12 +661,15 @@ def test_small_grid_phi1_edges_match_oracle(torch_mod, shape, opts):
 
 
 @pytest.mark.parametrize("shape", [(64, 80, 1), (65, 81, 1), (120, 72, 1), (121, 73, 1), (1366, 3, 1), (64, 2056, 1),
-                                   (64, 2057, 1), (65, 1111, 1), (64, 6152, 1), (64, 6153, 1)])
+                                   (64, 2057, 1), (65, 1111, 1), (64, 6152, 1), (64, 6153, 1), (120, 3100, 1),
+                                   (121, 2200, 1), (32, 16, 5), (33, 17, 5), (60, 28, 3), (61, 29, 2), (32, 16, 512),
+                                   (32, 16, 513), (64, 16, 171), (65, 17, 131), (3, 33, 259)])
 @pytest.mark.parametrize("opts", [{}, {"m_max": 13}, {"precision": 1, "tol_r": 1e-7}])
 def test_box_pass_edges_match_oracle(torch_mod, shape, opts):
-    """Grids at and beside the edges of the 2D box pass (64 columns, 56 of them new, by
-    16 or 32 rows, 8 or 24 new) and at both its limits of 256 boxes, with a term budget
-    that is no multiple of a pass (13) and in FP32."""
+    """Grids at and beside the edges of the box passes (2D: 64 columns, 56 of them new,
+    by 16 or 32 rows, 8 or 24 new; 3D: 32 x 16 columns, 28 x 12 new, by two planes), at
+    their limits of 256 boxes and of the marching passes beyond, with a term budget that
+    is no multiple of a pass (13) and in FP32."""
     test_small_grid_phi1_edges_match_oracle(torch_mod, shape, opts)
 
 

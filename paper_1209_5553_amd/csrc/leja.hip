@@ -356,10 +356,11 @@ __global__ __launch_bounds__(1024) void k_leja_box(Dims d, const LejaCoef* __res
 // one-term pass whatever the compiler contracts.
 //
 // Bound by memory: per cell and pair of terms the seven stencil words, q_{k-1},
-// p in and out and the last q, 88 B where two one-term passes move 176.  On
+// p in and out and the last q, 88 B where two one-term passes move 176.  Turned
+// passes (zmarch_turns) find some of it in the Infinity Cache.  On
 // 256^3 (FP64, 1.5 GB a pass, six times the Infinity Cache) 248 -> 133 us per
 // term, 5.5 TB/s; on 128^3 28 -> 19 us.
-template <int TY, int SH, int NTH, class V>
+template <int TY, int SH, int NTH, bool FLIP, class V>
 __global__ __launch_bounds__(NTH) void k_leja_zmarch(Dims d, const LejaCoef* __restrict__ cf,
                                            const V* __restrict__ coef, const V* __restrict__ qin,
                                            V* __restrict__ qout, V* __restrict__ p, LejaState* st,
@@ -409,7 +410,10 @@ __global__ __launch_bounds__(NTH) void k_leja_zmarch(Dims d, const LejaCoef* __r
   const int rgx = x0 - 2 + rx, rgy = y0 - 2 + ry;
   const bool rin = ring && rgx >= 0 && rgx < nx && rgy >= 0 && rgy < ny;
   const int rcell = min(max(rgx, 0), nx - 1) + nx * min(max(rgy, 0), ny - 1);
-  auto plane = [&](int z) { return static_cast<long long>(min(max(z, 0), nz - 1)) * pl; };
+  auto plane = [&](int z) {  // FLIP: counted from the top
+    const int zz = min(max(z, 0), nz - 1);
+    return static_cast<long long>(FLIP ? nz - 1 - zz : zz) * pl;
+  };
 
   V c0[SH][7], c1[SH][7];              // stencil of planes z - 1 and z (then z + 1)
   V qm[SH], qc[SH], qp[SH], qr;        // q_{k-1} on planes z - 1, z, z + 1; the ring cell of z + 1
@@ -488,8 +492,8 @@ __global__ __launch_bounds__(NTH) void k_leja_zmarch(Dims d, const LejaCoef* __r
       jq = fma(c1[r][2], sq[par][ly][lx + 1], jq);
       jq = fma(c1[r][3], (r > 0 ? qc[r > 0 ? r - 1 : 0] : sq[par][ly - 1][lx]), jq);
       jq = fma(c1[r][4], (r + 1 < SH ? qc[r + 1 < SH ? r + 1 : 0] : sq[par][ly + 1][lx]), jq);
-      jq = fma(c1[r][5], qm[r], jq);
-      jq = fma(c1[r][6], qp[r], jq);
+      jq = fma(c1[r][5], FLIP ? qp[r] : qm[r], jq);
+      jq = fma(c1[r][6], FLIP ? qm[r] : qp[r], jq);
       const V v = fma(jq, ig, -(sh0 * qc[r]));
       t1[r] = in[r] && zin ? v : V(0);
     }
@@ -503,11 +507,11 @@ __global__ __launch_bounds__(NTH) void k_leja_zmarch(Dims d, const LejaCoef* __r
         jq = fma(c0[r][2], s1[par ^ 1][ly][lx + 1], jq);
         jq = fma(c0[r][3], (r > 0 ? tc[r > 0 ? r - 1 : 0] : s1[par ^ 1][ly - 1][lx]), jq);
         jq = fma(c0[r][4], (r + 1 < SH ? tc[r + 1 < SH ? r + 1 : 0] : s1[par ^ 1][ly + 1][lx]), jq);
-        jq = fma(c0[r][5], tm[r], jq);
-        jq = fma(c0[r][6], t1[r], jq);
+        jq = fma(c0[r][5], FLIP ? t1[r] : tm[r], jq);
+        jq = fma(c0[r][6], FLIP ? tm[r] : t1[r], jq);
         const V v = fma(jq, ig, -(sh1 * tc[r]));
         if (out[r]) {
-          const long long o = static_cast<long long>(z - 1) * pl + cell[r];
+          const long long o = plane(z - 1) + cell[r];
           p[o] = fma(d1, v, fma(d0, tc[r], pc[r]));
           qout[o] = v;
           a0 += static_cast<double>(tc[r]) * static_cast<double>(tc[r]);
@@ -962,6 +966,12 @@ int cube_blocks(const Dims& d) {
   return n <= kCubeMax ? static_cast<int>(n) : 0;
 }
 
+// Every second 3D pass marches from the top down when a pass moves more than the
+// Infinity Cache holds (ten words a cell): it then begins on what the pass before
+// touched last.  256^3, FP64 phi1 action of 36 terms 6.16 -> 5.73 ms, 256 x 256 x 128
+// 3.24 -> 2.94; on 150 x 131 x 97 in FP32 (76 MB) no difference.
+bool zmarch_turns(const Dims& d, size_t word) { return 10ll * d.N * static_cast<long long>(word) > (256ll << 20); }
+
 int terms_blocks(const Dims& d) {
   if (d.dim == 2) {
     if (const int R = box_cells(d)) return box_blocks(d, R);
@@ -1033,8 +1043,11 @@ hipError_t launch_terms(const Dims& d, const LejaCoef* cf, const V* coef, const 
     launch_timed(k_leja_terms<kTermsPerPass2, V>, grid, dim3(kThreads), 0, s, e0, e1, d, cf, coef, qin, qout, p, st,
                  part, g, nb, terms_rows(d), k);
   } else {
-    launch_timed(k_leja_zmarch<kZmarchRows, kZmarchStrip, kZmarchThreads, V>, grid, dim3(kZmarchThreads), 0, s, e0,
-                 e1, d, cf, coef, qin, qout, p, st, part, g, nb, zmarch_planes(d), k);
+    const bool flip = zmarch_turns(d, sizeof(V)) && (k >> 1) & 1;
+    launch_timed(flip ? k_leja_zmarch<kZmarchRows, kZmarchStrip, kZmarchThreads, true, V>
+                      : k_leja_zmarch<kZmarchRows, kZmarchStrip, kZmarchThreads, false, V>,
+                 grid, dim3(kZmarchThreads), 0, s, e0, e1, d, cf, coef, qin, qout, p, st, part, g, nb,
+                 zmarch_planes(d), k);
   }
   return hipGetLastError();
 }

@@ -673,6 +673,12 @@ def test_box_pass_edges_match_oracle(torch_mod, shape, opts):
     test_small_grid_phi1_edges_match_oracle(torch_mod, shape, opts)
 
 
+def test_turned_3d_passes_match_oracle(torch_mod):
+    """A pass over 3.4 M cells moves more than the Infinity Cache holds: every second
+    one marches from the top down."""
+    test_small_grid_phi1_edges_match_oracle(torch_mod, (150, 151, 150), {})
+
+
 @pytest.mark.parametrize("shape,m", [((1024, 256, 1), 12), ((1024, 257, 1), 13), ((67, 65, 61), 14)])
 def test_krylov_folded_sums_match_oracle(torch_mod, shape, m):
     """1024 workgroups add up each other's partial sums, one more and a fold does;

@@ -70,11 +70,12 @@ struct AsmReduce {
 
 // Conjugate-gradient scalars.  The inner products are kept as partial sums,
 // one per 64 x 4 cell band of the grid (the blocks of cell_grid), in a ring
-// of four iterations: each band's slot is written by the block that covers it
-// (the fused legs of the 2D multigrid keep one slot per workgroup instead), and
-// every consumer sums the slots in order (wave_part_sum), so the result does not
-// depend on the order in which the blocks ran.  The arrays live in one device
-// allocation of pcg_parts_words doubles.
+// of four iterations: each band's slot is written by the block or tile that
+// covers it (a tile of several bands writes its sum into its first band and
+// zeros into the others), and every consumer sums the slots in band order
+// (wave_part_sum), so the result does not depend on the order in which the
+// blocks ran.  The arrays live in one device allocation of
+// pcg_parts_words(nb) doubles.
 struct PcgState {
   int done;        // 1 once converged
   int it_done;     // iteration count at convergence
@@ -87,26 +88,17 @@ struct PcgState {
   double* rz;             // [4][nb]
   double* rr;             // [4][nb]
   double* pq;             // [4][nb]
-  // Chronopoulos-Gear form (2D multigrid): one partial per workgroup of the
-  // finest down leg (r.r of iterations past the first) and up leg (r.z, w.z)
-  int nd, nu;
-  double* frr;            // [4][nd]
-  double* frz;            // [4][nu]
-  double* fwz;            // [4][nu]
+  double* wz;             // [4][nb] w.z (Chronopoulos-Gear form)
 };
-inline size_t pcg_parts_words(int nb, int nd, int nu) { return static_cast<size_t>(13) * nb + 4 * nd + 8 * nu; }
-// The state's array pointers into a parts allocation of pcg_parts_words.
-inline void pcg_bind_parts(PcgState* st, double* parts, int nb, int nd, int nu) {
+inline size_t pcg_parts_words(int nb) { return static_cast<size_t>(17) * nb; }
+// The state's array pointers into a parts allocation of pcg_parts_words(nb).
+inline void pcg_bind_parts(PcgState* st, double* parts, int nb) {
   st->nb = nb;
   st->bb_sl = parts;
   st->rz = parts + nb;
   st->rr = parts + 5 * static_cast<size_t>(nb);
   st->pq = parts + 9 * static_cast<size_t>(nb);
-  st->nd = nd;
-  st->nu = nu;
-  st->frr = parts + 13 * static_cast<size_t>(nb);
-  st->frz = st->frr + 4 * static_cast<size_t>(nd);
-  st->fwz = st->frz + 4 * static_cast<size_t>(nu);
+  st->wz = parts + 13 * static_cast<size_t>(nb);
 }
 
 inline dim3 cell_grid(const Dims& d) {

@@ -250,17 +250,12 @@ int build_mg(erem_ctx* c) {
   h.lds_bytes = mg_lds_layout(h, lc, &a) * sizeof(double);
   for (int k = 0; k < a.nlev; ++k) a.lev[k] = h.lev[lc + k];
   h.coarse_threads = std::min(1024, ((a.n0 + 63) / 64) * 64);
-  // 2D hierarchies with two smoothed LDS levels keep them in registers, with
-  // the grid level above when it has at most kMgTopCells cells and is not the
-  // finest (whose legs carry the conjugate-gradient update)
-  h.lt = lc;
+  // 2D hierarchies with two smoothed LDS levels keep them in registers
   if (c->d.nz == 1 && a.nlev == 3) {
-    const bool top = lc >= 2 && static_cast<size_t>(h.lev[lc - 1].nx) * h.lev[lc - 1].ny <= kMgTopCells;
-    const size_t bytes = mg_coarse_2d_words(top) * sizeof(double);
-    if (bytes + 1024 <= static_cast<size_t>(max_lds) && mg_set_lds_limit(static_cast<int>(bytes), true) == hipSuccess) {
+    const size_t words = mg_coarse_2d_words() * sizeof(double);
+    if (words + 1024 <= static_cast<size_t>(max_lds) && mg_set_lds_limit(static_cast<int>(words), true) == hipSuccess) {
       h.reg2d = true;
-      h.lds_bytes = bytes;
-      if (top) h.lt = lc - 1;
+      h.lds_bytes = words;
     } else {
       (void)hipGetLastError();
     }
@@ -1028,10 +1023,7 @@ int erem_create(const erem_grid* g, void* stream, erem_ctx** out) {
   rc |= dev_alloc(c, &c->xi_dev, kMaxTerms + 1);
   rc |= dev_alloc(c, &c->ddc, 1);
   c->pcg_nb = cell_bands(c->d);
-  int nd = 0, nu = 0;
-  mg_cg_tiles(c->d.nx, c->d.ny, &nd, &nu);
-  if (c->d.nz != 1) nd = nu = 0;
-  rc |= dev_alloc(c, &c->pcg_parts, pcg_parts_words(c->pcg_nb, nd, nu));
+  rc |= dev_alloc(c, &c->pcg_parts, pcg_parts_words(c->pcg_nb));
   if (rc == EREM_OK) {
     if (hipHostMalloc(reinterpret_cast<void**>(&c->h_cf), 2 * sizeof(LejaCoef), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&c->h_states), sizeof(LejaState) * c->nstates, hipHostMallocDefault) != hipSuccess ||
@@ -1044,7 +1036,7 @@ int erem_create(const erem_grid* g, void* stream, erem_ctx** out) {
   if (rc == EREM_OK) {
     // the state's pointers into the partial slots, set once
     PcgState init{};
-    pcg_bind_parts(&init, c->pcg_parts, c->pcg_nb, nd, nu);
+    pcg_bind_parts(&init, c->pcg_parts, c->pcg_nb);
     if (hipMemcpy(c->pcg, &init, sizeof(PcgState), hipMemcpyHostToDevice) != hipSuccess) rc = EREM_EDEVICE;
   }
   if (rc != EREM_OK) {

@@ -9,7 +9,6 @@ namespace erem {
 
 constexpr int kMgMaxLevels = 16;
 constexpr int kMgLdsCells = 1024;   // levels at or below this size run in one workgroup
-constexpr int kMgTopCells = 4096;   // largest 2D grid level that joins them (four cells per thread)
 #ifndef EREM_MG_TOP_CYCLES
 #define EREM_MG_TOP_CYCLES 2
 #endif
@@ -53,7 +52,6 @@ struct MgCoarseArgs {
 struct MgHierarchy {
   int nlev = 0;            // levels built (finest first), the last is the bottom
   int lc = 0;              // first level handled in LDS
-  int lt = 0;              // first level of the one-workgroup solve: lc, or the grid level above it
   bool reg2d = false;      // 2D with two smoothed LDS levels: k_mg_coarse_2d
   int lb = 0;              // bottom level (= nlev - 1)
   int coarse_threads = 0;
@@ -85,22 +83,19 @@ struct CgFuse {
 };
 
 hipError_t mg_setup(const MgHierarchy& h, hipStream_t s);
-// Workgroups of the finest 2D legs (the partial slots of their sums).
-void mg_cg_tiles(int nx, int ny, int* nd, int* nu);
 // z = M^{-1} r.  With cg (only where mg_fuses_cg): see CgFuse; with
 // cg->update, r is the residual before the update and z = M^{-1} r_new.
 hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* st, int rz_slot,
                     hipStream_t s, const CgFuse* cg = nullptr);
 // True when the finest level is 2D and runs the global-memory legs.
-inline bool mg_fuses_cg(const MgHierarchy& h) { return h.lt > 0 && h.lev[0].nz == 1; }
+inline bool mg_fuses_cg(const MgHierarchy& h) { return h.lc > 0 && h.lev[0].nz == 1; }
 hipError_t mg_set_lds_limit(int bytes, bool reg2d);
 // k_mg_coarse_2d: padding of its LDS buffers (at least a row of the level plus
-// one: a bottom level of at most 64 columns has level-0 rows of at most 256 and
-// top rows of at most 512), and its LDS words.
-constexpr int kMgPad0 = 258, kMgPadTop = 514;
-inline size_t mg_coarse_2d_words(bool top) {
-  return 4 * (kMgLdsCells + 2 * kMgPad0) + (top ? 2 * (kMgTopCells + 2 * kMgPadTop) : 0) + kMgLdsCells +
-         2 * kMgBottomCells;
+// one: a bottom level of at most 64 columns has level-0 rows of at most 256), and
+// its LDS words.
+constexpr int kMgPad0 = 258;
+inline size_t mg_coarse_2d_words() {
+  return 4 * (kMgLdsCells + 2 * kMgPad0) + 2 * kMgLdsCells + 2 * kMgBottomCells + kMgBottomCells * kMgBottomCells;
 }
 
 }  // namespace erem

@@ -21,8 +21,6 @@
 #include "device.h"
 #include "mg.h"
 
-#include <mutex>
-
 namespace erem {
 
 namespace {
@@ -276,7 +274,7 @@ __global__ __launch_bounds__(kThreads) void k_mg_up_smooth(MgLevelDev F, MgLevel
     part = b[i] * v;
   }
   if (rz_slot < 0) return;
-  for (int off = 32; off > 0; off >>= 1) part += __shfl_down(part, off, 64);
+  part = wave_sum(part);
   __shared__ double sh[kThreads / 64];
   const int t = threadIdx.x + threadIdx.y * kBX;
   if ((t & 63) == 0) sh[t >> 6] = part;
@@ -287,80 +285,310 @@ __global__ __launch_bounds__(kThreads) void k_mg_up_smooth(MgLevelDev F, MgLevel
   }
 }
 
+constexpr int kTY = 8;  // tile rows of the finest 2D legs
+
+// A 64 x kTY tile covers the 64 x 4 bands (bx, 2 by) and (bx, 2 by + 1) of
+// the finest grid: its partial goes to the first, zero to the second.
+__device__ inline void tile_band_store(double* slots, int nx, int ny, double v) {
+  const int gx = (nx + kBX - 1) / kBX, gyb = (ny + kBY - 1) / kBY;
+  const int b0 = blockIdx.x + gx * (2 * blockIdx.y);
+  slots[b0] = v;
+  if (2 * static_cast<int>(blockIdx.y) + 1 < gyb) slots[b0 + gx] = 0.0;
+}
+
+// Operator of a cell: the transmissibilities to its neighbours (0 toward a missing
+// one) and the diagonal (1 outside the grid).
+struct BoxCell {
+  double tw, te, ts, tn, D;
+  __device__ inline void load(const MgLevelDev& L, int gx, int gy, bool in) {
+    const int nx = L.nx, ny = L.ny;
+    tw = in && gx > 0 ? L.tx[fxi(nx, ny, gx, gy, 0)] : 0.0;
+    te = in && gx + 1 < nx ? L.tx[fxi(nx, ny, gx + 1, gy, 0)] : 0.0;
+    ts = in && gy > 0 ? L.ty[fyi(nx, ny, gx, gy, 0)] : 0.0;
+    tn = in && gy + 1 < ny ? L.ty[fyi(nx, ny, gx, gy + 1, 0)] : 0.0;
+    D = in ? L.diag[gx + nx * gy] : 1.0;
+  }
+  __device__ inline double nb(double w, double e, double s, double n) const {
+    double v = tw * w;
+    v = fma(te, e, v);
+    v = fma(ts, s, v);
+    return fma(tn, n, v);
+  }
+};
+
 // ---------------------------------------------------------------------------
-// 2D forms of the two legs.  A workgroup of 1024 threads holds a box of 64 x 16
-// cells, one per thread, a wavefront per row; the box is the workgroup's tile
-// plus a halo of H cells, so that every sweep needs only what the box holds
-// (each sweep's outer ring goes wrong by one cell).  A thread keeps its cell's
-// four transmissibilities scaled by 1/D, D, the scaled right-hand side and the
-// iterate in registers; the x neighbours come from the next lanes by DPP, the y
-// neighbours from LDS (double buffered: a barrier per sweep).
+// The legs of the finest 2D level, with an iteration of conjugate gradients folded
+// in.  A workgroup owns a tile of 64 x 8 cells (one partial of each sum) and holds
+// it with a halo of H cells, K cells per thread: operands and iterates in
+// registers, the neighbours' iterates from LDS (with a ring of zeros around, double
+// buffered: a barrier per sweep; each sweep's outer ring goes wrong by one cell).
 //
-// On grids of up to 512 x 512 the legs are chains of latencies (launch, one
-// round of loads, a barrier per sweep), which is why a sweep is as short as this;
-// the loads of a halo come from L2.  A down / up leg of 256 x 256 and 128 x 128
-// takes 3.9 / 4.1 us (6.9 / 7.4 with tiles of 64 x 8 on 256 threads, four cells a
-// thread, operands in LDS), the finest legs of 512 x 512 with their CG work 9.6 /
-// 9.6 us (15.8 / 11.3, the five sums of the CG step on one wavefront).
+// On grids of up to 512 x 512 the legs are chains of latencies: launch, one round of
+// loads, the sums of the CG step (each on a wavefront of its own), a barrier and a
+// division per sweep.  Down / up on 512 x 512: 12.1 / 7.9 us; with four cells a thread on
+// 256 threads, the operands in LDS and all sums on one wavefront 15.8 / 11.3.
 // ---------------------------------------------------------------------------
-constexpr int kBoxR = 16;                 // box rows (64 columns wide)
-constexpr int kBoxT = kBX * kBoxR;        // threads
+template <int H, int NTH>
+struct CgBox {
+  static constexpr int W = kBX + 2 * H, R = kTY + 2 * H, N = W * R, K = (N + NTH - 1) / NTH;
+  typedef double Lds[R + 2][W + 2];
+  int lx[K], ly[K], j[K];
+  bool in[K], own[K];
+  BoxCell q[K];
+  __device__ inline void place(const MgLevelDev& F, int x0, int y0) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int c = threadIdx.x + k * NTH;
+      ly[k] = c / W;
+      lx[k] = c - ly[k] * W;
+      const int gx = x0 - H + lx[k], gy = y0 - H + ly[k];
+      in[k] = c < N && gx >= 0 && gx < F.nx && gy >= 0 && gy < F.ny;
+      own[k] = in[k] && lx[k] >= H && lx[k] < H + kBX && ly[k] >= H && ly[k] < H + kTY;
+      j[k] = gx + F.nx * gy;
+      q[k].load(F, gx, gy, in[k]);
+    }
+  }
+  __device__ inline bool cell(int k) const { return (k + 1) * NTH <= N || static_cast<int>(threadIdx.x) + k * NTH < N; }
+  __device__ static inline void ring(Lds& e) {
+    for (int i = threadIdx.x; i < W + 2; i += NTH) e[0][i] = e[R + 1][i] = 0.0;
+    for (int i = threadIdx.x; i < R + 2; i += NTH) e[i][0] = e[i][W + 1] = 0.0;
+  }
+  __device__ inline void put(Lds& e, int k, double v) const {
+    if (cell(k)) e[ly[k] + 1][lx[k] + 1] = v;
+  }
+  __device__ inline double nb(const Lds& e, int k) const {
+    const int y = cell(k) ? ly[k] + 1 : 1, x = cell(k) ? lx[k] + 1 : 1;
+    return q[k].nb(e[y][x - 1], e[y][x + 1], e[y - 1][x], e[y + 1][x]);
+  }
+  // one sweep: x + om (b - A x) / D
+  __device__ inline double sweep(const Lds& e, int k, double b, double x, double om) const {
+    return x + om * (fma(-q[k].D, x, b) + nb(e, k)) / q[k].D;
+  }
+};
+
+// Down leg: NU weighted Jacobi sweeps from zero (the first, x1 = w b / D, needs no
+// neighbours), then the restricted residual of the tile's aggregates.  In front,
+// iteration it of Chronopoulos-Gear conjugate gradients (one reduction phase per
+// iteration): from the slot sums of the previous leg pair the stop test on ||r_it||,
+// then beta = g_it / g_{it-1}, alpha = g_it / (d_it - beta g_it / alpha_{it-1}) with
+// g = r.z, d = w.z, w = A z (alpha = g_0 / d_0, beta = 0 at it = 0); s = w + beta
+// s_old and r_new = r - alpha s on the box (the halo values recomputed, the tile's
+// written); p = z + beta p and x += alpha p on the tile; the partial sum of
+// r_new . r_new.
+template <int NU>
+__global__ __launch_bounds__(1024) void k_mg_down_cg(MgLevelDev F, MgLevelDev C, const double* __restrict__ b,
+                                           double* __restrict__ xout, double* __restrict__ bc, PcgState* st,
+                                           CgFuse cg) {
+  static_assert(NU >= 2, "two sweeps at least");
+  typedef CgBox<NU, 1024> Box;
+  static_assert(Box::K == 1, "a cell per thread");
+  const bool stop = pcg_done(st);
+  __shared__ typename Box::Lds e[2];
+  __shared__ double srn[kTY][kBX];
+  __shared__ double sums[5], alpha_sh, beta_sh, sh[kTY / 2];
+  __shared__ int stop_sh;
+  const int nx = F.nx, ny = F.ny;
+  const int tile = xcd_tile_id();  // 2D grid: tile = bx + gridDim.x * by
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int it = cg.it;
+  // every load first
+  Box B;
+  B.place(F, (tile % gridDim.x) * kBX, (tile / gridDim.x) * kTY);
+  const int j = B.j[0];
+  const bool in = B.in[0], own = B.own[0];
+  const double rb = in ? b[j] : 0.0, rw = in ? cg.w[j] : 0.0, rs = in && it > 0 ? cg.s_old[j] : 0.0;
+  const double xo = own ? cg.x[j] : 0.0, zo = own ? cg.z[j] : 0.0, po = own && it > 0 ? cg.p[j] : 0.0;
+  Box::ring(e[0]);
+  Box::ring(e[1]);
+  if (wave < 5) {
+    const int nb = st->nb;
+    const double* src = wave == 0   ? st->rr + (it & 3) * nb
+                        : wave == 1 ? st->bb_sl
+                        : wave == 2 ? st->rz + (it & 3) * nb
+                        : wave == 3 ? st->wz + (it & 3) * nb
+                                    : st->rz + ((it - 1) & 3) * nb;
+    const double v = wave == 4 && it == 0 ? 1.0 : wave_part_sum(src, nb);
+    if (lane == 0) sums[wave] = v;
+  }
+  if (tid < kTY * kBX) srn[tid / kBX][tid % kBX] = 0.0;
+  __syncthreads();
+  if (tid < 64) {  // the first wavefront decides for the block
+    int halt = stop ? 1 : 0;
+    double alpha = 0.0, beta = 0.0;
+    const double rr = sums[0], bb = sums[1], g1 = sums[2], d1 = sums[3], g0 = sums[4];
+    const bool lead = tile == 0;
+    if (halt) {
+      // an earlier iteration converged
+    } else if (!isfinite(rr)) {
+      halt = 1;
+      if (lead && tid == 0) { st->nonfinite = 1; st->done = 1; st->it_done = it; }
+    } else if (rr <= st->tol2 * bb) {
+      halt = 1;
+      if (lead && tid == 0) { st->done = 1; st->it_done = it; st->bb = bb; }
+    } else if (it > 0) {
+      beta = g1 / g0;
+      alpha = g1 / (d1 - beta * g1 / st->alpha[(it - 1) & 3]);
+    } else {
+      alpha = g1 / d1;
+    }
+    if (tid == 0) {
+      stop_sh = halt;
+      alpha_sh = alpha;
+      beta_sh = beta;
+    }
+    if (!halt && lead && tid == 0) st->alpha[it & 3] = alpha;
+  }
+  // the first tile may set the stop flag while this kernel runs, so every
+  // wavefront follows the first one's decision, not its own read
+  __syncthreads();
+  if (stop_sh) return;
+  const double alpha = alpha_sh, beta = beta_sh;
+  const double sv = fma(beta, rs, rw);  // zero outside the grid stays zero
+  const double rn = fma(-alpha, sv, rb);
+  double x = sweep_weight<NU>(0) * rn / B.q[0].D;  // first sweep from zero
+  B.put(e[0], 0, x);
+  if (own) {
+    const double pn = fma(beta, po, zo);
+    cg.r_new[j] = rn;
+    cg.s_new[j] = sv;
+    cg.p[j] = pn;
+    cg.x[j] = fma(alpha, pn, xo);
+    srn[B.ly[0] - NU][B.lx[0] - NU] = rn;
+  }
+  __syncthreads();
+  if (wave < kTY / 2) {
+    const double r0 = srn[2 * wave][lane], r1 = srn[2 * wave + 1][lane];
+    const double v = wave_sum(fma(r1, r1, r0 * r0));
+    if (lane == 0) sh[wave] = v;
+  }
+#pragma unroll
+  for (int k = 2; k <= NU; ++k) {
+    x = B.sweep(e[k & 1], 0, rn, x, sweep_weight<NU>(k - 1));
+    B.put(e[(k - 1) & 1], 0, x);
+    __syncthreads();
+  }
+  if (tid == 0) tile_band_store(st->rr + ((it + 1) & 3) * st->nb, nx, ny, sh[0] + sh[1] + sh[2] + sh[3]);
+  const double res = fma(-B.q[0].D, x, rn) + B.nb(e[(NU - 1) & 1], 0);
+  if (own) xout[j] = x;
+  typename Box::Lds& er = e[NU & 1];
+  B.put(er, 0, own ? res : 0.0);
+  __syncthreads();
+  const int lx = B.lx[0], ly = B.ly[0];
+  if (own && ((lx - NU) & 1) == 0 && ((ly - NU) & 1) == 0) {
+    const int gx = (tile % gridDim.x) * kBX + lx - NU, gy = (tile / gridDim.x) * kTY + ly - NU;
+    bc[(gx >> 1) + C.nx * (gy >> 1)] =
+        (res + er[ly + 2][lx + 1]) + (er[ly + 1][lx + 2] + er[ly + 2][lx + 2]);
+  }
+}
+
+// Up leg: the coarse correction v = x + w_c e[parent] on the box, then NU weighted
+// Jacobi sweeps; the last covers the tile (out = z) and the ring around it, so that
+// w = A z follows on the tile (w_out); the partial sums of r.z and w.z go to the
+// ring slot.
+template <int NU>
+__global__ __launch_bounds__(576) void k_mg_up_cg(MgLevelDev F, MgLevelDev C, const double* __restrict__ b,
+                                        const double* __restrict__ xv, const double* __restrict__ ec,
+                                        double omega_c, double* __restrict__ out, double* __restrict__ w_out,
+                                        PcgState* st, int rz_slot) {
+  typedef CgBox<NU + 1, 576> Box;
+  constexpr int K = Box::K, H = NU + 1;
+  const bool stop = pcg_done(st);
+  __shared__ typename Box::Lds e[2];
+  __shared__ double sb[kTY][kBX], sz[kTY][kBX], sw[kTY][kBX], sh[2][kTY / 2];
+  const int nx = F.nx, ny = F.ny;
+  const int tile = xcd_tile_id();  // 2D grid: tile = bx + gridDim.x * by
+  const int x0 = (tile % gridDim.x) * kBX, y0 = (tile / gridDim.x) * kTY;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  Box B;
+  B.place(F, x0, y0);
+  double x[K], rb[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int gx = x0 - H + B.lx[k], gy = y0 - H + B.ly[k];
+    const double xi = B.in[k] ? xv[B.j[k]] : 0.0, ei = B.in[k] ? ec[(gx >> 1) + C.nx * (gy >> 1)] : 0.0;
+    rb[k] = B.in[k] ? b[B.j[k]] : 0.0;
+    x[k] = fma(omega_c, ei, xi);
+  }
+  Box::ring(e[0]);
+  Box::ring(e[1]);
+  for (int i = tid; i < kTY * kBX; i += 576) (&sb[0][0])[i] = (&sz[0][0])[i] = (&sw[0][0])[i] = 0.0;
+  if (stop) return;
+#pragma unroll
+  for (int k = 0; k < K; ++k) B.put(e[0], k, x[k]);
+  __syncthreads();
+#pragma unroll
+  for (int t = 1; t <= NU; ++t) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      x[k] = B.sweep(e[(t - 1) & 1], k, rb[k], x[k], sweep_weight<NU>(NU - t));
+      B.put(e[t & 1], k, x[k]);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const double w = fma(B.q[k].D, x[k], -B.nb(e[NU & 1], k));
+    if (!B.own[k]) continue;
+    out[B.j[k]] = x[k];
+    w_out[B.j[k]] = w;
+    const int y = B.ly[k] - H, c = B.lx[k] - H;
+    sb[y][c] = rb[k];
+    sz[y][c] = x[k];
+    sw[y][c] = w;
+  }
+  __syncthreads();
+  if (wave < kTY / 2) {
+    const int y = 2 * wave;
+    const double z0 = sz[y][lane], z1 = sz[y + 1][lane];
+    const double g = wave_sum(fma(sb[y + 1][lane], z1, sb[y][lane] * z0));
+    const double dz = wave_sum(fma(sw[y + 1][lane], z1, sw[y][lane] * z0));
+    if (lane == 0) {
+      sh[0][wave] = g;
+      sh[1][wave] = dz;
+    }
+  }
+  __syncthreads();
+  if (tid == 0) {
+    tile_band_store(st->rz + rz_slot * st->nb, nx, ny, sh[0][0] + sh[0][1] + sh[0][2] + sh[0][3]);
+    tile_band_store(st->wz + rz_slot * st->nb, nx, ny, sh[1][0] + sh[1][1] + sh[1][2] + sh[1][3]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The legs of 2D levels without conjugate-gradient work: a workgroup of 1024
+// threads holds a box of 64 x 16 cells, one per thread, a wavefront per row: its
+// tile plus a halo of H = NU cells, so that every sweep needs only what the box
+// holds (each sweep's outer ring goes wrong by one cell).  Operands and iterate
+// stay in registers, the x neighbours come from the next lanes by DPP, the y
+// neighbours from LDS (double buffered: a barrier per sweep).  The operations are
+// those of the finest legs, one by one and in their order.
+//
+// On such levels a leg is a chain of latencies (launch, one round of loads, a
+// barrier and a division per sweep): a down / up leg of 256 x 256 and 128 x 128
+// takes 4.0 / 4.2 us where tiles of 64 x 8 on 256 threads, four cells a thread with
+// their operands in LDS, took 6.7 / 7.1.
+// ---------------------------------------------------------------------------
+constexpr int kBoxR = 16;           // box rows (64 columns wide)
+constexpr int kBoxT = kBX * kBoxR;  // threads
 
 // West / east neighbour's value (0 past the wavefront's ends): wavefront shifts.
 __device__ inline double box_w(double v) { return dpp<0x138>(v); }
 __device__ inline double box_e(double v) { return dpp<0x130>(v); }
 
-// Operator of the thread's cell, scaled by 1/D; everything zero (D = 1) outside
-// the grid.  D is the sum of the cell's faces, as in the level's diagonal.
-struct BoxCell {
-  double tw, te, ts, tn, D, di;
-  __device__ inline void load(const MgLevelDev& L, int gx, int gy, bool in) {
-    const int nx = L.nx, ny = L.ny;
-    tw = in ? L.tx[fxi(nx, ny, gx, gy, 0)] : 0.0;
-    te = in ? L.tx[fxi(nx, ny, gx + 1, gy, 0)] : 0.0;
-    ts = in ? L.ty[fyi(nx, ny, gx, gy, 0)] : 0.0;
-    tn = in ? L.ty[fyi(nx, ny, gx, gy + 1, 0)] : 0.0;
-  }
-  __device__ inline void scale(const MgLevelDev& L, int gx, int gy, bool in) {
-    D = in ? tw + te + ts + tn : 1.0;
-    di = 1.0 / D;
-    tw = gx > 0 ? tw * di : 0.0;
-    te = gx + 1 < L.nx ? te * di : 0.0;
-    ts = gy > 0 ? ts * di : 0.0;
-    tn = gy + 1 < L.ny ? tn * di : 0.0;
-  }
-  // (b + sum t v_nb) / D for the scaled right-hand side bp; col: the thread's
-  // column of the LDS rows
-  __device__ inline double nb(double bp, double v, const double (*col)[kBX], int row, int lane) const {
-    double s = fma(tw, box_w(v), bp);
-    s = fma(te, box_e(v), s);
-    s = fma(ts, col[row][lane], s);         // rows are stored one down
-    return fma(tn, col[row + 2][lane], s);
-  }
-};
+// b - A v at the thread's cell; col: the LDS rows, stored one down.
+__device__ inline double box_residual(const BoxCell& q, double b, double v, const double (*col)[kBX], int row, int lane) {
+  return fma(-q.D, v, b) + q.nb(box_w(v), box_e(v), col[row][lane], col[row + 2][lane]);
+}
 
-// Down leg of a 2D level, fused: NU weighted Jacobi sweeps from zero (the first,
-// x1 = w b / D, needs no neighbours), then the restricted residual of the tile's
-// aggregates.
-//
-// With CG, iteration it of Chronopoulos-Gear conjugate gradients (one reduction
-// phase per iteration) is folded in front of the leg.  From the partial sums of
-// the previous leg pair (a wavefront per sum): the stop test on ||r_it||, then
-// beta = g_it / g_{it-1}, alpha = g_it / (d_it - beta g_it / alpha_{it-1}) with
-// g = r.z, d = w.z, w = A z (alpha = g_0 / d_0, beta = 0 at it = 0); s = w + beta
-// s_old and r_new = r - alpha s on the box (the halo values recomputed, the
-// tile's written); p = z + beta p and x += alpha p on the tile; the partial sum
-// of r_new . r_new.
-template <int NU, bool CG>
-__global__ __launch_bounds__(kBoxT) __attribute__((amdgpu_waves_per_eu(8))) void k_mg_down_restrict_2d(
-    MgLevelDev F, MgLevelDev C, const double* __restrict__ b, double* __restrict__ xout, double* __restrict__ bc,
-    PcgState* st, CgFuse cg) {
-  static_assert(NU >= 2, "two sweeps at least");
+// Down leg: NU weighted Jacobi sweeps from zero, then the restricted residual of
+// the tile's aggregates.
+template <int NU>
+__global__ __launch_bounds__(kBoxT) void k_mg_down_box(MgLevelDev F, MgLevelDev C, const double* __restrict__ b,
+                                            double* __restrict__ xout, double* __restrict__ bc, const PcgState* st) {
   constexpr int H = NU, TX = kBX - 2 * H, TR = kBoxR - 2 * H;
+  static_assert(TX % 2 == 0 && TR % 2 == 0, "whole aggregates");
   const bool stop = pcg_done(st);
   __shared__ double e[2][kBoxR + 2][kBX];
-  __shared__ double sums[5];
-  __shared__ double rrs[kBoxR];
   const int nx = F.nx, ny = F.ny;
   const int lane = threadIdx.x & 63, row = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tiles_x = (nx + TX - 1) / TX;
@@ -369,113 +597,43 @@ __global__ __launch_bounds__(kBoxT) __attribute__((amdgpu_waves_per_eu(8))) void
   const bool in = gx >= 0 && gx < nx && gy >= 0 && gy < ny;
   const bool own = in && lane >= H && lane < H + TX && row >= H && row < H + TR;
   const int j = gx + nx * gy;
-  const int it = cg.it;
-  // every load first
-  double bp = in ? b[j] : 0.0, w = 0.0, s = 0.0, xo = 0.0, zo = 0.0, po = 0.0;
-  if (CG) {
-    w = in ? cg.w[j] : 0.0;
-    s = in && it > 0 ? cg.s_old[j] : 0.0;
-    if (own) {
-      xo = cg.x[j];
-      zo = cg.z[j];
-      po = it > 0 ? cg.p[j] : 0.0;
-    }
-  }
+  const double bi = in ? b[j] : 0.0;
   BoxCell q;
   q.load(F, gx, gy, in);
   if (row == 0 || row == kBoxR - 1) {  // rows beside the box
     const int r = row == 0 ? 0 : kBoxR + 1;
     e[0][r][lane] = e[1][r][lane] = 0.0;
   }
-  if (CG) {
-    if (row < 5) {
-      const double* src = row == 0   ? (it > 0 ? st->frr + (it & 3) * st->nd : st->rr)
-                          : row == 1 ? st->bb_sl
-                          : row == 2 ? st->frz + (it & 3) * st->nu
-                          : row == 3 ? st->fwz + (it & 3) * st->nu
-                                     : st->frz + ((it - 1) & 3) * st->nu;
-      const int n = row == 0 ? (it > 0 ? st->nd : st->nb) : row == 1 ? st->nb : st->nu;
-      const double v = row == 4 && it == 0 ? 1.0 : wave_part_sum(src, n);
-      if (lane == 0) sums[row] = v;
-    }
-    // every wavefront must take the same decision, so none uses its own reading
-    // of the flag, which workgroup 0 may set meanwhile
-    const double alpha_old = it > 0 ? st->alpha[(it - 1) & 3] : 1.0;
-    if (threadIdx.x == 0) rrs[0] = stop ? 1.0 : 0.0;
-    __syncthreads();
-    const bool was = rrs[0] != 0.0;
-    const double rr = sums[0], bb = sums[1], g1 = sums[2], d1 = sums[3], g0 = sums[4];
-    const bool bad = !isfinite(rr), conv = rr <= st->tol2 * bb;
-    if (was || bad || conv) {
-      if (!was && tile == 0 && threadIdx.x == 0) {
-        if (bad) st->nonfinite = 1;
-        else st->bb = bb;
-        st->it_done = it;
-        st->done = 1;
-      }
-      return;
-    }
-    const double beta = it > 0 ? g1 / g0 : 0.0;
-    const double alpha = it > 0 ? g1 / (d1 - beta * g1 / alpha_old) : g1 / d1;
-    if (tile == 0 && threadIdx.x == 0) st->alpha[it & 3] = alpha;
-    s = w + beta * s;  // zero outside the grid
-    bp = bp - alpha * s;
-    double rr2 = 0.0;
-    if (own) {
-      const double pn = zo + beta * po;
-      cg.r_new[j] = bp;
-      cg.s_new[j] = s;
-      cg.p[j] = pn;
-      cg.x[j] = xo + alpha * pn;
-      rr2 = bp * bp;
-    }
-    rr2 = wave_sum(rr2);
-    if (lane == 0) w = rr2;  // stored after the next barrier (rrs[0] is still being read)
-  } else if (stop) {
-    return;
-  }
-  q.scale(F, gx, gy, in);
-  bp *= q.di;
-  double x = sweep_weight<NU>(0) * bp;  // first sweep from zero
+  if (stop) return;
+  double x = sweep_weight<NU>(0) * bi / q.D;  // first sweep from zero
   e[0][row + 1][lane] = x;
   __syncthreads();
-  if (CG && lane == 0) rrs[row] = w;
 #pragma unroll
   for (int k = 1; k < NU; ++k) {
-    x += sweep_weight<NU>(k) * (q.nb(bp, x, e[(k - 1) & 1], row, lane) - x);
+    x = x + sweep_weight<NU>(k) * box_residual(q, bi, x, e[(k - 1) & 1], row, lane) / q.D;
     e[k & 1][row + 1][lane] = x;
     __syncthreads();
   }
-  const double res = (q.nb(bp, x, e[(NU - 1) & 1], row, lane) - x) * q.D;
+  double res = box_residual(q, bi, x, e[(NU - 1) & 1], row, lane);
   if (own) xout[j] = x;
-  const double pair = (own ? res : 0.0) + box_e(own ? res : 0.0);
-  e[NU & 1][row + 1][lane] = pair;
+  else res = 0.0;
+  e[NU & 1][row + 1][lane] = res;
   __syncthreads();
   // aggregates start at even cells: lanes and rows at an even distance from H
-  if (own && ((lane - H) & 1) == 0 && ((row - H) & 1) == 0)
-    bc[(gx >> 1) + C.nx * (gy >> 1)] = pair + e[NU & 1][row + 2][lane];
-  if (CG && threadIdx.x == 0) {
-    double v = rrs[0];
-    for (int k = 1; k < kBoxR; ++k) v += rrs[k];
-    st->frr[((it + 1) & 3) * st->nd + tile] = v;
-  }
+  const double pair = res + e[NU & 1][row + 2][lane];
+  const double sum = pair + box_e(pair);
+  if (own && ((lane - H) & 1) == 0 && ((row - H) & 1) == 0) bc[(gx >> 1) + C.nx * (gy >> 1)] = sum;
 }
 
-// Up leg of a 2D level, fused: the coarse correction v = x + w_c e[parent] on
-// the box, then NU weighted Jacobi sweeps; the last lands on the tile (out = z).
-// With CG (the finest level of the Chronopoulos-Gear form) the halo is one
-// larger, so that the last sweep also covers the ring around the tile and w = A z
-// follows on the tile (w_out); the partial sums of r.z and w.z go to the ring
-// slot.
-template <int NU, bool CG>
-__global__ __launch_bounds__(kBoxT) __attribute__((amdgpu_waves_per_eu(8))) void k_mg_up_smooth_2d(
-    MgLevelDev F, MgLevelDev C, const double* __restrict__ b, const double* __restrict__ xv,
-    const double* __restrict__ ec, double omega_c, double* __restrict__ out, double* __restrict__ w_out, PcgState* st,
-    int rz_slot) {
-  constexpr int H = NU + (CG ? 1 : 0), TX = kBX - 2 * H, TR = kBoxR - 2 * H;
+// Up leg: the coarse correction v = x + w_c e[parent] on the box, then NU weighted
+// Jacobi sweeps.
+template <int NU>
+__global__ __launch_bounds__(kBoxT) void k_mg_up_box(MgLevelDev F, MgLevelDev C, const double* __restrict__ b,
+                                          const double* __restrict__ xv, const double* __restrict__ ec,
+                                          double omega_c, double* __restrict__ out, const PcgState* st) {
+  constexpr int H = NU, TX = kBX - 2 * H, TR = kBoxR - 2 * H;
   const bool stop = pcg_done(st);
   __shared__ double e[2][kBoxR + 2][kBX];
-  __shared__ double sh[2][kBoxR];
   const int nx = F.nx, ny = F.ny;
   const int lane = threadIdx.x & 63, row = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tiles_x = (nx + TX - 1) / TX;
@@ -492,48 +650,25 @@ __global__ __launch_bounds__(kBoxT) __attribute__((amdgpu_waves_per_eu(8))) void
     const int r = row == 0 ? 0 : kBoxR + 1;
     e[0][r][lane] = e[1][r][lane] = 0.0;
   }
-  double x = xi + omega_c * ei;
+  double x = fma(omega_c, ei, xi);
   e[0][row + 1][lane] = x;
   if (stop) return;
-  q.scale(F, gx, gy, in);
-  const double bp = bi * q.di;
   __syncthreads();
 #pragma unroll
   for (int k = 1; k <= NU; ++k) {
-    x += sweep_weight<NU>(NU - k) * (q.nb(bp, x, e[(k - 1) & 1], row, lane) - x);
-    if (k < NU || CG) {
+    x = x + sweep_weight<NU>(NU - k) * box_residual(q, bi, x, e[(k - 1) & 1], row, lane) / q.D;
+    if (k < NU) {
       e[k & 1][row + 1][lane] = x;
       __syncthreads();
     }
   }
   if (own) out[j] = x;
-  if (!CG) return;
-  double g = 0.0, dz = 0.0;
-  const double w = (x - q.nb(0.0, x, e[NU & 1], row, lane)) * q.D;
-  if (own) {
-    w_out[j] = w;
-    g = bi * x;
-    dz = w * x;
-  }
-  g = wave_sum(g);
-  dz = wave_sum(dz);
-  if (lane == 0) {
-    sh[0][row] = g;
-    sh[1][row] = dz;
-  }
-  __syncthreads();
-  if (threadIdx.x < 2) {
-    const int k = threadIdx.x;
-    double v = sh[k][0];
-    for (int r = 1; r < kBoxR; ++r) v += sh[k][r];
-    (k == 0 ? st->frz : st->fwz)[rz_slot * st->nu + tile] = v;
-  }
 }
 
-// Tiles of the legs on a level (the boxes less their halo).
-int leg_tiles(int nx, int ny, int halo) {
-  const int tx = kBX - 2 * halo, tr = kBoxR - 2 * halo;
-  return ((nx + tx - 1) / tx) * ((ny + tr - 1) / tr);
+// Workgroups of the box legs.
+dim3 box_grid(const MgLevelDev& L) {
+  const int tx = kBX - 2 * kMgSweeps, tr = kBoxR - 2 * kMgSweeps;
+  return dim3(((L.nx + tx - 1) / tx) * ((L.ny + tr - 1) / tr));
 }
 
 // ---------------------------------------------------------------------------
@@ -855,7 +990,7 @@ __global__ __launch_bounds__(1024) void k_mg_coarse_lds(MgCoarseArgs a, const do
     part = b0 * v;
   }
   if (rz_slot < 0) return;
-  for (int off = 32; off > 0; off >>= 1) part += __shfl_down(part, off, 64);
+  part = wave_sum(part);
   __shared__ double sh[16];
   if ((t & 63) == 0) sh[t >> 6] = part;
   __syncthreads();
@@ -872,24 +1007,19 @@ __global__ __launch_bounds__(1024) void k_mg_coarse_lds(MgCoarseArgs a, const do
 
 // ---------------------------------------------------------------------------
 // The coarse solve of 2D hierarchies with two smoothed LDS levels above the
-// bottom (every grid that is not a thin strip): the same cycles as
-// k_mg_coarse_lds with the operands in registers.  A thread owns cell t of
-// each level and keeps the four transmissibilities scaled by 1/D (zero toward a
-// missing neighbour), D, the scaled right-hand side and its iterate; only the
-// iterates that neighbours read go through LDS, so a sweep is four LDS reads,
-// four multiply-adds, one LDS write and a barrier.  With TOP the level above
-// (at most 4 x 1024 cells, four per thread, smoothed by the grid levels' NU
-// weighted sweeps) is handled here too, which spares its two launches.
+// bottom (every grid that is not a thin strip): the cycles of k_mg_coarse_lds, the
+// same operations in the same order, with the operands in registers.  A thread owns
+// cell t of each level; only the iterates that neighbours read go through LDS, so a
+// sweep is four LDS reads, some ten operations, one LDS write and a barrier, with no
+// division of the cell index.
 //
-// Bound by its chain of about 60 barriered phases, 0.2 us each, and 3 us of
-// launch and loads: 17.3 us with a 64 x 64 top level, where k_mg_coarse_lds
-// (operands from LDS and a division of the cell index in every phase) took 24.1
-// us for the levels below it and the top level's two legs 14 us and two launch
-// gaps more.
+// Bound by its chain of some 50 barriered phases: 11.8 us for 32 x 32 and two levels
+// below, where k_mg_coarse_lds takes 23.8.
 // ---------------------------------------------------------------------------
 struct CoarseCell {
-  double tw, te, ts, tn;   // transmissibility / D, zero toward a missing neighbour
-  double D, bp, e;         // diagonal, right-hand side / D, iterate
+  double tw, te, ts, tn;  // transmissibilities, zero toward a missing neighbour
+  double D, di;           // diagonal, its inverse
+  double B, e;            // right-hand side, iterate
 };
 
 // Cell c of a level (a cell past its end: all zero, D = 1).
@@ -906,7 +1036,7 @@ __device__ inline void coarse_load(const MgLevelDev& L, int c, CoarseCell& q) {
   q.te = in && x + 1 < nx ? te : 0.0;
   q.ts = in && y > 0 ? ts : 0.0;
   q.tn = in && y + 1 < ny ? tn : 0.0;
-  q.bp = q.e = 0.0;
+  q.B = q.e = 0.0;
 }
 
 __device__ inline int coarse_parent(const MgLevelDev& F, const MgLevelDev& C, int c) {
@@ -914,21 +1044,21 @@ __device__ inline int coarse_parent(const MgLevelDev& F, const MgLevelDev& C, in
   return (x >> 1) + C.nx * (y >> 1);
 }
 
-__device__ inline void coarse_scale(CoarseCell& q) {
-  const double di = 1.0 / q.D;
-  q.tw *= di;
-  q.te *= di;
-  q.ts *= di;
-  q.tn *= di;
+// sum t v_nb, v at the cell in a padded LDS array: a missing neighbour reads some
+// other entry or the padding and multiplies it by zero.  Each product is rounded
+// before the sum, as in lds_nb_sum.
+__device__ inline double coarse_nb(const CoarseCell& q, const double* v, int nx) {
+#pragma clang fp contract(off)
+  const double w = q.tw * v[-1], e = q.te * v[1], s = q.ts * v[-nx], n = q.tn * v[nx];
+  return w + e + s + n;
 }
 
-// (B + sum t v_nb) / D, v at the cell in a padded LDS array: a missing
-// neighbour reads some other entry or the padding and multiplies it by zero.
-__device__ inline double coarse_nb(const CoarseCell& q, const double* v, int nx) {
-  double s = fma(q.tw, v[-1], q.bp);
-  s = fma(q.te, v[1], s);
-  s = fma(q.ts, v[-nx], s);
-  return fma(q.tn, v[nx], s);
+// One sweep, and B - A v.
+__device__ inline double coarse_sweep(const CoarseCell& q, const double* v, int nx) {
+  return fma(kOmega, fma(q.B + coarse_nb(q, v, nx), q.di, -q.e), q.e);
+}
+__device__ inline double coarse_res(const CoarseCell& q, const double* v, int nx) {
+  return fma(-q.D, q.e, q.B) + coarse_nb(q, v, nx);
 }
 
 // Sum of the residuals of the (up to) 2 x 2 children of coarse cell (X, Y).
@@ -938,14 +1068,6 @@ __device__ inline double coarse_children(const double* r, int fnx, int fny, int 
   const int i = x0 + fnx * y0;
   const double r00 = r[i], r10 = r[hx ? i + 1 : i], r01 = r[hy ? i + fnx : i], r11 = r[hx && hy ? i + fnx + 1 : i];
   return r00 + (hx ? r10 : 0.0) + (hy ? r01 : 0.0) + (hx && hy ? r11 : 0.0);
-}
-
-// Sum over the 16 lanes of a DPP row; every lane gets it.
-__device__ inline double row_sum16(double v) {
-  v += dpp<0xB1>(v);            // quad_perm: lane ^ 1
-  v += dpp<0x4E>(v);            // quad_perm: lane ^ 2
-  v += dpp<0x141>(v);           // half mirror: the other quad of eight
-  return v + dpp<0x140>(v);     // mirror: the other eight of sixteen
 }
 
 // One double-buffered iterate of a level in LDS: a phase reads cur and writes
@@ -960,23 +1082,22 @@ struct CoarseBuf {
   }
 };
 
-template <int NU, bool TOP>
-__global__ __launch_bounds__(kMgLdsCells) void k_mg_coarse_2d(MgCoarseArgs a, MgLevelDev top,
-                                                              const double* __restrict__ bglob,
-                                                              const double* __restrict__ binv,
-                                                              double* __restrict__ out, PcgState* st, int rz_slot) {
-  constexpr int NT = TOP ? kMgTopCells / kMgLdsCells : 1;  // top cells per thread
+__global__ __launch_bounds__(kMgLdsCells) void k_mg_coarse_2d(MgCoarseArgs a, const double* __restrict__ bglob,
+                                                    const double* __restrict__ binv, double* __restrict__ out,
+                                                    PcgState* st, int rz_slot) {
   constexpr int S = kMgLdsCells;
+  static_assert(kMgLdsSweeps == 2, "two sweeps each way");
   const bool stop = pcg_done(st);
   extern __shared__ double smem[];
   const int t = threadIdx.x;
   const MgLevelDev &L0 = a.lev[0], &L1 = a.lev[1], &L2 = a.lev[2];
   const int n0 = L0.nx * L0.ny, n1 = L1.nx * L1.ny, n2 = L2.nx * L2.ny;
   const bool on0 = t < n0, on1 = t < n1, on2 = t < n2;
-  const int nxt = TOP ? top.nx : 0, nx0 = L0.nx, nx1 = L1.nx;
-  // LDS: the buffers (pointers to the thread's own cell), level 0's and then
-  // level 1's residuals, the bottom vectors
-  CoarseBuf b0, b1, bt;
+  const int nx0 = L0.nx, nx1 = L1.nx;
+  // LDS: the buffers (pointers to the thread's own cell), the residuals of level 0
+  // and then of level 1, the bottom's right-hand side, solution, partial products
+  // and inverse
+  CoarseBuf b0, b1;
   double* p = smem;
   auto take = [&](int cells, int pad) {
     double* r = p + pad + t;
@@ -987,118 +1108,81 @@ __global__ __launch_bounds__(kMgLdsCells) void k_mg_coarse_2d(MgCoarseArgs a, Mg
   b0.oth = take(S, kMgPad0);
   b1.cur = take(S, kMgPad0);
   b1.oth = take(S, kMgPad0);
-  bt.cur = bt.oth = nullptr;
-  if (TOP) {
-    bt.cur = take(kMgTopCells, kMgPadTop);
-    bt.oth = take(kMgTopCells, kMgPadTop);
-  }
   double* rc = take(S, 0) - t;
   double* bc = take(kMgBottomCells, 0) - t;
   double* ebot = take(kMgBottomCells, 0) - t;
-  // loads first; with TOP those of the levels below go out behind the top
-  // level's first sweep (the registers do not hold everything in flight)
-  CoarseCell ct[NT], c0, c1;
-  if (TOP) {
+  double* parts = take(S, 0) - t;
+  const double* zeroed = p;
+  double* inv = take(kMgBottomCells * kMgBottomCells, 0) - t;
+  // loads first
+  CoarseCell c0, c1;
+  coarse_load(L0, t, c0);
+  coarse_load(L1, t, c1);
+  constexpr int NI = kMgBottomCells * kMgBottomCells / S;
+  double vi[NI];
 #pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      coarse_load(top, t + k * S, ct[k]);
-      ct[k].bp = t + k * S < top.nx * top.ny ? bglob[t + k * S] : 0.0;
-    }
-  }
-  // bottom inverse: thread (row t / 16, columns 4 (t % 16) .. + 3)
-  const int br = t >> 4, bj = (t & 15) * 4;
-  double inv[4];
-  auto load_below = [&] {
-    coarse_load(L0, t, c0);
-    coarse_load(L1, t, c1);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) inv[k] = br < n2 && bj + k < n2 ? binv[br * n2 + bj + k] : 0.0;
-  };
-  if (!TOP) load_below();
-  const double bin = !TOP && on0 ? bglob[t] : 0.0;
+  for (int k = 0; k < NI; ++k) vi[k] = t + k * S < n2 * n2 ? binv[t + k * S] : 0.0;
+  const double bin = on0 ? bglob[t] : 0.0;
   const int par0 = on0 ? coarse_parent(L0, L1, t) : 0, par1 = on1 ? coarse_parent(L1, L2, t) : 0;
-  for (double* q = smem + t; q < p; q += S) *q = 0.0;  // padding and cells past a level's end
+  for (double* q = smem + t; q < zeroed; q += S) *q = 0.0;  // padding and cells past a level's end
+#pragma unroll
+  for (int k = 0; k < NI; ++k) inv[t + k * S] = vi[k];
+  c0.di = 1.0 / c0.D;
+  c1.di = 1.0 / c1.D;
+  c0.B = bin;
   if (stop) return;
   __syncthreads();
-  double B0 = bin;
-  if (TOP) {
-#pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      coarse_scale(ct[k]);
-      ct[k].bp /= ct[k].D;
-      ct[k].e = sweep_weight<NU>(0) * ct[k].bp;
-      bt.oth[k * S] = ct[k].e;
-    }
-    bt.turn();
-    load_below();
-#pragma unroll
-    for (int s = 1; s < NU; ++s) {
-      const double w = sweep_weight<NU>(s);
-#pragma unroll
-      for (int k = 0; k < NT; ++k) {
-        ct[k].e += w * (coarse_nb(ct[k], bt.cur + k * S, nxt) - ct[k].e);
-        bt.oth[k * S] = ct[k].e;
-      }
-      bt.turn();
-    }
-#pragma unroll
-    for (int k = 0; k < NT; ++k)
-      bt.oth[k * S] = (coarse_nb(ct[k], bt.cur + k * S, nxt) - ct[k].e) * ct[k].D;  // residuals
-    bt.turn();
-    B0 = on0 ? coarse_children(bt.cur - t, top.nx, top.ny, t % nx0, t / nx0) : 0.0;
-    __syncthreads();
-    // the top level's right-hand side waits in LDS (its iterate is in bt.oth)
-#pragma unroll
-    for (int k = 0; k < NT; ++k) bt.cur[k * S] = ct[k].bp;
-  }
-  coarse_scale(c0);
-  coarse_scale(c1);
-  c0.bp = B0 / c0.D;
+  // the bottom's columns go to as many wavefronts as level 0 fills
+  const int groups = (n0 + 63) >> 6, chunk = (n2 + groups - 1) / groups;
+  const int br = t & 63, bg = t >> 6, j0 = bg * chunk, j1 = min(n2, j0 + chunk);
   double x0 = 0.0;
 #pragma unroll 1
   for (int cyc = 0; cyc < a.ncyc; ++cyc) {
     if (cyc > 0) {  // continue from the residual the cycle before left
       x0 += c0.e;
-      c0.bp = coarse_nb(c0, b0.cur, nx0) - c0.e;
+      c0.B += fma(-c0.D, c0.e, coarse_nb(c0, b0.cur, nx0));
     }
-    c0.e = kOmega * c0.bp;
+    c0.e = kOmega * c0.B * c0.di;
     *b0.oth = c0.e;
     b0.turn();
-    c0.e += kOmega * (coarse_nb(c0, b0.cur, nx0) - c0.e);
+    c0.e = coarse_sweep(c0, b0.cur, nx0);
     *b0.oth = c0.e;
     b0.turn();
-    rc[t] = (coarse_nb(c0, b0.cur, nx0) - c0.e) * c0.D;
+    rc[t] = coarse_res(c0, b0.cur, nx0);
     __syncthreads();
     double x1 = 0.0;
 #pragma unroll 1
     for (int v = 0; v < a.ncyc1; ++v) {
       if (on1) {
         if (v == 0) {
-          c1.bp = coarse_children(rc, L0.nx, L0.ny, t % nx1, t / nx1) / c1.D;
+          c1.B = coarse_children(rc, L0.nx, L0.ny, t % nx1, t / nx1);
         } else {
           x1 += c1.e;
-          c1.bp = coarse_nb(c1, b1.cur, nx1) - c1.e;
+          c1.B += fma(-c1.D, c1.e, coarse_nb(c1, b1.cur, nx1));
         }
-        c1.e = kOmega * c1.bp;
+        c1.e = kOmega * c1.B * c1.di;
         *b1.oth = c1.e;
       }
       b1.turn();
       if (on1) {
-        c1.e += kOmega * (coarse_nb(c1, b1.cur, nx1) - c1.e);
+        c1.e = coarse_sweep(c1, b1.cur, nx1);
         *b1.oth = c1.e;
       }
       b1.turn();
-      if (on1) rc[t] = (coarse_nb(c1, b1.cur, nx1) - c1.e) * c1.D;
+      if (on1) rc[t] = coarse_res(c1, b1.cur, nx1);
       __syncthreads();
       if (on2) bc[t] = coarse_children(rc, L1.nx, L1.ny, t % L2.nx, t / L2.nx);
       __syncthreads();
-      {
-        double s = inv[0] * bc[bj];
-        s = fma(inv[1], bc[bj + 1], s);
-        s = fma(inv[2], bc[bj + 2], s);
-        s = fma(inv[3], bc[bj + 3], s);
-        s = row_sum16(s);
-        if ((t & 15) == 0) ebot[br] = s;
+      if (br < n2 && bg < groups) {
+        double s = 0.0;
+        for (int j = j0; j < j1; ++j) s += inv[j * n2 + br] * bc[j];
+        parts[bg * n2 + br] = s;
+      }
+      __syncthreads();
+      if (on2) {
+        double s = 0.0;
+        for (int k = 0; k < groups; ++k) s += parts[k * n2 + t];
+        ebot[t] = s;
       }
       __syncthreads();
       if (on1) {
@@ -1109,7 +1193,7 @@ __global__ __launch_bounds__(kMgLdsCells) void k_mg_coarse_2d(MgCoarseArgs a, Mg
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
         if (on1) {
-          c1.e += kOmega * (coarse_nb(c1, b1.cur, nx1) - c1.e);
+          c1.e = coarse_sweep(c1, b1.cur, nx1);
           // the last value is the level's whole correction, for level 0
           *b1.oth = s == 1 && v + 1 == a.ncyc1 ? c1.e + x1 : c1.e;
         }
@@ -1121,53 +1205,27 @@ __global__ __launch_bounds__(kMgLdsCells) void k_mg_coarse_2d(MgCoarseArgs a, Mg
     b0.turn();
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      c0.e += kOmega * (coarse_nb(c0, b0.cur, nx0) - c0.e);
-      *b0.oth = s == 1 && cyc + 1 == a.ncyc ? c0.e + x0 : c0.e;
+      c0.e = coarse_sweep(c0, b0.cur, nx0);
+      *b0.oth = c0.e;
       b0.turn();
     }
   }
-  if (TOP) {
-#pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      const int c = t + k * S;
-      const int pk = c < top.nx * top.ny ? coarse_parent(top, L0, c) : 0;
-      ct[k].bp = bt.cur[k * S];
-      ct[k].e = fma(a.omega_c, (b0.cur - t)[pk], bt.oth[k * S]);
-      bt.oth[k * S] = ct[k].e;
-    }
-    bt.turn();
-#pragma unroll
-    for (int s = 1; s <= NU; ++s) {
-      const double w = sweep_weight<NU>(NU - s);
-#pragma unroll
-      for (int k = 0; k < NT; ++k) {
-        const int c = t + k * S;
-        ct[k].e += w * (coarse_nb(ct[k], bt.cur + k * S, nxt) - ct[k].e);
-        if (s < NU)
-          bt.oth[k * S] = ct[k].e;
-        else if (c < top.nx * top.ny)
-          out[c] = ct[k].e;
-      }
-      if (s < NU) bt.turn();
-    }
-    return;
-  }
   double part = 0.0;
   if (on0) {
-    const double v = c0.e + x0;
+    const double v = x0 + c0.e;
     out[t] = v;
     part = bin * v;
   }
   if (rz_slot < 0) return;
-  for (int off = 32; off > 0; off >>= 1) part += __shfl_down(part, off, 64);
+  part = wave_sum(part);
   __shared__ double sh[kMgLdsCells / 64];
   if ((t & 63) == 0) sh[t >> 6] = part;
   __syncthreads();
   double* slots = st->rz + rz_slot * st->nb;
-  for (int k = t + 1; k < st->nb; k += kMgLdsCells) slots[k] = 0.0;
+  for (int k = t + 1; k < st->nb; k += S) slots[k] = 0.0;
   if (t == 0) {
     double s = 0.0;
-    for (int w = 0; w < kMgLdsCells / 64; ++w) s += sh[w];
+    for (int w = 0; w < groups; ++w) s += sh[w];
     slots[0] = s;
   }
 }
@@ -1187,17 +1245,12 @@ hipError_t mg_setup(const MgHierarchy& h, hipStream_t s) {
   return hipGetLastError();
 }
 
-void mg_cg_tiles(int nx, int ny, int* nd, int* nu) {
-  *nd = leg_tiles(nx, ny, kMgSweeps);
-  *nu = leg_tiles(nx, ny, kMgSweeps + 1);
-}
-
 // z = M^{-1} r on the finest level; with rz_slot >= 0 also accumulates r . z
 // into the CG ring.
 hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* st, int rz_slot, hipStream_t s,
                     const CgFuse* cg) {
   if (cg && !mg_fuses_cg(h)) return hipErrorInvalidValue;
-  const int lc = h.lt;  // the first level of the one-workgroup solve
+  const int lc = h.lc;
   auto grid_of = [](const MgLevelDev& L) {
     return dim3((L.nx + kBX - 1) / kBX, (L.ny + kBY - 1) / kBY, L.nz);
   };
@@ -1206,12 +1259,11 @@ hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* 
     const MgLevelDev& C = h.lev[l + 1];
     const double* b = l == 0 ? r : F.b;
     if (F.nz == 1) {
-      const dim3 g(leg_tiles(F.nx, F.ny, kMgSweeps));
+      const dim3 g((F.nx + kBX - 1) / kBX, (F.ny + kTY - 1) / kTY, 1);
       if (l == 0 && cg && cg->update)
-        hipLaunchKernelGGL((k_mg_down_restrict_2d<kMgSweeps, true>), g, dim3(kBoxT), 0, s, F, C, b, F.x, C.b, st, *cg);
+        hipLaunchKernelGGL(k_mg_down_cg<kMgSweeps>, g, dim3(1024), 0, s, F, C, b, F.x, C.b, st, *cg);
       else
-        hipLaunchKernelGGL((k_mg_down_restrict_2d<kMgSweeps, false>), g, dim3(kBoxT), 0, s, F, C, b, F.x, C.b, st,
-                           CgFuse{});
+        hipLaunchKernelGGL(k_mg_down_box<kMgSweeps>, box_grid(F), dim3(kBoxT), 0, s, F, C, b, F.x, C.b, st);
     } else {
       const dim3 g((F.nx + kBX - 1) / kBX, (F.ny + kBY - 1) / kBY, C.nz);
       hipLaunchKernelGGL(k_mg_down_restrict, g, cell_block(), 0, s, F, C, b, F.x, C.b, st);
@@ -1220,16 +1272,12 @@ hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* 
   {
     const double* b = lc == 0 ? r : h.lev[lc].b;
     double* out = lc == 0 ? z : h.lev[lc].x;
-    const int slot = lc == 0 ? rz_slot : -1;
-    if (h.reg2d && h.lt < h.lc)
-      hipLaunchKernelGGL((k_mg_coarse_2d<kMgSweeps, true>), dim3(1), dim3(kMgLdsCells), h.lds_bytes, s, h.coarse,
-                         h.lev[lc], b, h.binv, out, st, slot);
-    else if (h.reg2d)
-      hipLaunchKernelGGL((k_mg_coarse_2d<kMgSweeps, false>), dim3(1), dim3(kMgLdsCells), h.lds_bytes, s, h.coarse,
-                         h.lev[lc], b, h.binv, out, st, slot);
+    if (h.reg2d)
+      hipLaunchKernelGGL(k_mg_coarse_2d, dim3(1), dim3(kMgLdsCells), h.lds_bytes, s, h.coarse, b, h.binv, out, st,
+                         lc == 0 ? rz_slot : -1);
     else
       hipLaunchKernelGGL(k_mg_coarse_lds, dim3(1), dim3(h.coarse_threads), h.lds_bytes, s, h.coarse, b, h.binv,
-                         out, st, slot);
+                         out, st, lc == 0 ? rz_slot : -1);
   }
   // The up leg reads its level's x at the neighbours, so it writes its result
   // to y (z on the finest level); the LDS solve leaves its result in x.
@@ -1240,12 +1288,13 @@ hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* 
     const double* ec = l + 1 == lc ? C.x : C.y;
     double* out = l == 0 ? z : F.y;
     if (F.nz == 1) {
+      const dim3 g((F.nx + kBX - 1) / kBX, (F.ny + kTY - 1) / kTY, 1);
       if (l == 0 && cg)
-        hipLaunchKernelGGL((k_mg_up_smooth_2d<kMgSweeps, true>), dim3(leg_tiles(F.nx, F.ny, kMgSweeps + 1)),
-                           dim3(kBoxT), 0, s, F, C, b, F.x, ec, h.omega_c, out, cg->w_out, st, rz_slot);
+        hipLaunchKernelGGL(k_mg_up_cg<kMgSweeps>, g, dim3(576), 0, s, F, C, b, F.x, ec, h.omega_c, out, cg->w_out, st,
+                           rz_slot);
       else
-        hipLaunchKernelGGL((k_mg_up_smooth_2d<kMgSweeps, false>), dim3(leg_tiles(F.nx, F.ny, kMgSweeps)), dim3(kBoxT),
-                           0, s, F, C, b, F.x, ec, h.omega_c, out, nullptr, st, -1);
+        hipLaunchKernelGGL(k_mg_up_box<kMgSweeps>, box_grid(F), dim3(kBoxT), 0, s, F, C, b, F.x, ec, h.omega_c, out,
+                           st);
     } else {
       hipLaunchKernelGGL(k_mg_up_smooth, grid_of(F), cell_block(), 0, s, F, C, b, F.x, ec, h.omega_c, out, st,
                          l == 0 ? rz_slot : -1);
@@ -1257,20 +1306,13 @@ hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* 
 // The attribute belongs to the kernel, not to a context: keep the largest
 // size any context asked for.
 hipError_t mg_set_lds_limit(int bytes, bool reg2d) {
-  static std::mutex mu;
   static int granted[2] = {0, 0};
-  std::lock_guard<std::mutex> lock(mu);
   if (bytes <= granted[reg2d]) return hipSuccess;
-  const void* fn[2] = {reg2d ? reinterpret_cast<const void*>(&k_mg_coarse_2d<kMgSweeps, true>)
-                             : reinterpret_cast<const void*>(&k_mg_coarse_lds),
-                       reg2d ? reinterpret_cast<const void*>(&k_mg_coarse_2d<kMgSweeps, false>) : nullptr};
-  for (const void* f : fn) {
-    if (!f) continue;
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e != hipSuccess) return e;
-  }
-  granted[reg2d] = bytes;
-  return hipSuccess;
+  const void* kernel = reg2d ? reinterpret_cast<const void*>(&k_mg_coarse_2d)
+                             : reinterpret_cast<const void*>(&k_mg_coarse_lds);
+  const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) granted[reg2d] = bytes;
+  return e;
 }
 
 }  // namespace erem

@@ -365,10 +365,10 @@ int erem_coupled_step_adjoint(erem_ctx* ctx, double h, const double* d_T, double
  * most 64 columns by some rows) that form one list; a run is a sequence of phases, and each phase is one work
  * launch over the whole list - every problem that is not done takes one step
  * of its own schedule: a substep's start pass (q_0, p = d_0 q_0), four or
- * eight Newton terms (Eq. newt), or the last step's T update - followed by a
- * control launch that reduces each problem's tile partials in a fixed order
- * (so runs are bit-for-bit reproducible), applies the stop test of Sec. 4.2
- * and picks the problem's next phase.  With use_graph the whole sequence is
+ * eight Newton terms (Eq. newt), or the last step's T update.  The launch begins
+ * with the control step of the pass before: each problem's tile partials are added
+ * in a fixed order (so runs are bit-for-bit reproducible), and the stop test of
+ * Sec. 4.2 gives the problem's next phase.  With use_graph the whole sequence is
  * one hipGraph, captured on first use with the number of phases a
  * calibration run on a copy of T needed plus a margin; a run that needs more
  * continues with launches from the host.  Temperatures are packed: problem i
@@ -381,7 +381,7 @@ typedef struct {
     int32_t terms_min, terms_max;  /* per problem, over the run */
     int32_t failed;        /* problems that stopped on an error (see the return code) */
     int32_t tile_shape;    /* rows of a tile: 0: 16, 1: 8, 2: 32, 3: 64, 4: 128, all with
-                              four Newton terms per pass; 5: 32, 6: 16, 7: 64 with eight
+                              four Newton terms per pass; 5: 32, 6: 16, 7: 8 with eight
                               terms per pass; a tile is one wavefront's strip of at most
                               64 columns.  The stop test is
                               evaluated term by term after each pass and all terms of the
@@ -481,7 +481,7 @@ typedef struct {
     int64_t mg_cycles;
     double adj_rev_ms;          /* reverse Newton-Leja term kernel (adjoint) */
     int64_t adj_rev_launches;
-    double bicg_ms;             /* BiCGSTAB iteration (its three kernels) */
+    double bicg_ms;             /* BiCGSTAB iteration (its two kernels) */
     int64_t bicg_iterations;
 } erem_kernel_times;
 

@@ -12,12 +12,12 @@ namespace erem {
 // kBatchTileRows[shape] rows, advanced by kBatchPassTerms[shape] Newton terms
 // per pass by one wavefront.  Eight terms halve the bytes per term; short
 // tiles re-read more rows (2 NT per tile) but shorten a pass whose problems do
-// not fill the chip.  50 steps of 256 realisations (7.2 M cells, FP64): 95 ms
-// with 4 terms x 32 rows, 69.8 / 65.9 / 74.8 ms with 8 terms x 16 / 32 / 64
-// rows; 5 steps of 20 realisations (mixed): 2.60 ms with 4 x 8, 2.66 with
-// 4 x 16, 2.47 with 8 x 16, 2.99 with 8 x 32.
+// not fill the chip.  50 steps of 256 realisations (7.2 M cells, FP64): 87 ms
+// with 4 terms x 32 rows, 80.8 / 61.7 / 57.1 ms with 8 terms x 8 / 16 / 32 rows;
+// 4 steps of 30 realisations (mixed): 1.93 ms with 4 x 8, 1.98 with 4 x 16, 1.79
+// with 8 x 8, 1.87 with 8 x 16, 2.18 with 8 x 32.
 constexpr int kNumTileShapes = 8;
-constexpr int kBatchTileRows[kNumTileShapes] = {16, 8, 32, 64, 128, 32, 16, 64};
+constexpr int kBatchTileRows[kNumTileShapes] = {16, 8, 32, 64, 128, 32, 16, 8};
 constexpr int kBatchPassTerms[kNumTileShapes] = {4, 4, 4, 4, 4, 8, 8, 8};
 constexpr int kBatchPartStride = 8;  // partials per tile (one per term of a pass)
 

@@ -19,9 +19,9 @@
 // not sync inside the process and reads H once at the end.
 //
 // On small grids the passes are bound by latency (launch, one round of loads, the
-// sums, the shuffle trees): on 37 x 29 x 41, m = 10, a substep takes 33 launches
-// and 155 us of kernel time, where a reduction launch after every pass and the
-// basis read twice per pass took 62 launches and 237 us.
+// sums): on 37 x 29 x 41, m = 10, a substep takes 33 launches and 135 us of kernel
+// time, where a reduction launch after every pass and the basis read twice per pass
+// took 62 launches and 237 us.
 #include "device.h"
 #include "krylov.h"
 

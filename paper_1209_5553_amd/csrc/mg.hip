@@ -21,6 +21,8 @@
 #include "device.h"
 #include "mg.h"
 
+#include <mutex>
+
 namespace erem {
 
 namespace {
@@ -1306,7 +1308,9 @@ hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* 
 // The attribute belongs to the kernel, not to a context: keep the largest
 // size any context asked for.
 hipError_t mg_set_lds_limit(int bytes, bool reg2d) {
+  static std::mutex mu;  // contexts may be created on several threads
   static int granted[2] = {0, 0};
+  std::lock_guard<std::mutex> lock(mu);
   if (bytes <= granted[reg2d]) return hipSuccess;
   const void* kernel = reg2d ? reinterpret_cast<const void*>(&k_mg_coarse_2d)
                              : reinterpret_cast<const void*>(&k_mg_coarse_lds);

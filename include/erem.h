@@ -366,8 +366,8 @@ int erem_coupled_step_adjoint(erem_ctx* ctx, double h, const double* d_T, double
  * launch over the whole list - every problem that is not done takes one step
  * of its own schedule: a substep's start pass (q_0, p = d_0 q_0), four or
  * eight Newton terms (Eq. newt), or the last step's T update.  The launch begins
- * with the control step of the pass before: each problem's tile partials are added
- * in a fixed order (so runs are bit-for-bit reproducible), and the stop test of
+ * with the control step of the pass before: each problem's tile partials (of a
+ * problem of more than 384 tiles after a fold launch) are added in a fixed order (so runs are bit-for-bit reproducible), and the stop test of
  * Sec. 4.2 gives the problem's next phase.  With use_graph the whole sequence is
  * one hipGraph, captured on first use with the number of phases a
  * calibration run on a copy of T needed plus a margin; a run that needs more

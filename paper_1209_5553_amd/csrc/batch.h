@@ -20,6 +20,13 @@ constexpr int kNumTileShapes = 8;
 constexpr int kBatchTileRows[kNumTileShapes] = {16, 8, 32, 64, 128, 32, 16, 8};
 constexpr int kBatchPassTerms[kNumTileShapes] = {4, 4, 4, 4, 4, 8, 8, 8};
 constexpr int kBatchPartStride = 8;  // partials per tile (one per term of a pass)
+// Most tiles whose partials every wavefront of their problem adds up by itself,
+// and the slots that a larger problem's are folded into between two passes.  One
+// problem, every wavefront all of them / folded: 512 x 512 (288 tiles of 16 rows)
+// 397 / 421 us a run of two steps, 768 x 768 (384 of 32 rows) 408 / 405, 640 x 640
+// (480 of 16 rows) 473 / 445.
+constexpr int kBatchGate = 384;
+constexpr int kBatchFoldParts = 64;
 
 // Static description of one problem of the batch.
 struct BProb {
@@ -37,8 +44,15 @@ struct BProb {
 // Tile list entry: the problem, the strip of columns and the first row.
 struct BTile {
   int pid, strip, y0;
-  int done;           // set by the tile once its problem is done: it returns at entry
-  int tile0, ntiles;  // the problem's tiles
+  int done;       // set by the tile once its problem is done: it returns at entry
+  int tile0;      // the problem's first tile
+  int src, nsrc;  // partial slots that add up to the problem's: its tiles', or their fold
+  int pad;
+};
+
+// One wavefront of the fold: the partials of n tiles of problem pid into a slot.
+struct BFold {
+  int pid, tile0, n, slot;
 };
 
 // Phases of a problem; every launch picks each unfinished problem's next phase
@@ -90,8 +104,10 @@ struct BatchArgs {
   void *p0, *p1;         // Newton sums (ping-pong over substeps)
   const double* dk;      // divided differences, (m_max + 1) per problem
   const double* shift;   // c/gamma + xi_{k-1}, (m_max + 1) per problem
-  double* part;          // kBatchPartStride partials per tile, two copies of part_cap tiles
+  double* part;          // kBatchPartStride partials per slot, two copies of part_cap slots (tiles, then folds)
   long long part_cap;
+  const BFold* fold;
+  int nfold;
   long long ntot;
   int nprob, ntiles, nsteps, m_max;
   int nt, rows;          // Newton terms per pass and rows per tile of the tile shape
@@ -102,8 +118,8 @@ struct BatchArgs {
 hipError_t batch_pack(int nx, int ny, const double* coef, const double* F, const double* T0,
                       double* bcoef, double* g, long long ntot, long long off, hipStream_t s);
 hipError_t batch_reset(const BatchArgs& a, hipStream_t s);
-// One phase of every problem: pass number `pass` over all tiles.  e0 / e1
-// (optional) time it.
+// One phase of every problem: pass number `pass` over all tiles, then the fold of
+// its partials where a problem needs one.  e0 / e1 (optional) time the pass.
 hipError_t batch_phase(BatchArgs a, long long pass, int fp32, hipStream_t s, hipEvent_t e0 = nullptr,
                        hipEvent_t e1 = nullptr);
 

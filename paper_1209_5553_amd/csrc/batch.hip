@@ -24,8 +24,8 @@
 //   finish pass T += u + delta p of the last step.
 //
 // Each tile stores its partial sums (sum q_k^2 per term, in FP64); at the start
-// of the next pass every tile's wavefront adds up its problem's partials in a
-// fixed order, applies the scaled-norm stop test of Sec. 4.2 to the pass's NT
+// of the next pass every tile's wavefront adds up its problem's partials (those of
+// a problem of many tiles from a fold between the passes) in a fixed order, applies the scaled-norm stop test of Sec. 4.2 to the pass's NT
 // estimates in order, and so knows the problem's next phase.
 // Problems of every size and substep count thus share every launch, the
 // work spreads over all CUs whatever the mix, and the whole run is a fixed
@@ -226,6 +226,20 @@ __device__ inline void sum_max_octets(double& s, double& m) {
   m = fmax(__hiloint2double(h32[0], l32[0]), __hiloint2double(h32[1], l32[1]));
 }
 
+// Lane l's share of the sums and maxima of partial l & 7 over n slots.
+__device__ inline void batch_sums(const double* __restrict__ pp, int n, double& s, double& mx) {
+  n *= kBatchPartStride;
+  for (int b = threadIdx.x; b < n; b += 4 * 64) {
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = b + 64 * u < n ? pp[b + 64 * u] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      s += v[u];
+      mx = fmax(mx, v[u]);
+    }
+  }
+}
 
 // The problem's next phase, from the partials that its tiles left in the pass
 // before (lane l of every wavefront holds term k + (l & 7)'s sum in `s`, and in
@@ -339,21 +353,9 @@ __global__ __launch_bounds__(kMarchLanes) __attribute__((amdgpu_waves_per_eu(2))
   {
     // the partials of the pass before and the next coefficients' addresses need
     // the tile record only: their loads go out beside the state's
-    const double* pp = a.part + (a.pass & 1) * pcap + static_cast<long long>(kBatchPartStride) * tl.tile0;
     double s = 0.0, mx = 0.0;
-    if (S.phases >= 0) {
-      const int n = kBatchPartStride * tl.ntiles;
-      for (int b = lane; b < n; b += 4 * 64) {
-        double v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = b + 64 * u < n ? pp[b + 64 * u] : 0.0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          s += v[u];
-          mx = fmax(mx, v[u]);
-        }
-      }
-    }
+    if (S.phases >= 0)
+      batch_sums(a.part + (a.pass & 1) * pcap + static_cast<long long>(kBatchPartStride) * tl.src, tl.nsrc, s, mx);
     if (S.phase == kPhDone) {
       if (lane == 0) a.tile[t].done = 1;
       return;
@@ -412,6 +414,24 @@ __global__ __launch_bounds__(kMarchLanes) __attribute__((amdgpu_waves_per_eu(2))
     const double v = sum4(s4, lane);
     if (lane < 4) part[j + lane] = v;
   }
+}
+
+// Partials of the problems of more than kBatchGate tiles, folded after the pass
+// that left them: every tile of a problem adds up all of its partials, so without
+// a fold the reads grow with the square of the tiles.  Bound by its launch.  Two
+// steps of one 2048 x 2048 problem, 8 terms x 32 rows (1344 tiles): 1.22 -> 0.78
+// ms, 4096 x 4096 9.1 -> 2.65, with tiles of 8 rows 6.8 -> 1.12 and 90 -> 4.0.
+__global__ __launch_bounds__(kMarchLanes) void k_bt_fold(BatchArgs a) {
+  const BFold f = a.fold[blockIdx.x];
+  const int lane = threadIdx.x, copy = (a.pass & 1) ^ 1;  // the copy that the pass wrote
+  const int phase = a.state[copy * a.nprob + f.pid].phase;
+  if (phase >= kPhFinish) return;  // no next phase to find
+  double* part = a.part + static_cast<long long>(kBatchPartStride) * copy * a.part_cap;
+  double s = 0.0, mx = 0.0;
+  batch_sums(part + static_cast<long long>(kBatchPartStride) * f.tile0, f.n, s, mx);
+  sum_max_octets(s, mx);
+  if (lane < kBatchPartStride)
+    part[static_cast<long long>(kBatchPartStride) * f.slot + lane] = phase == kPhInit && lane == 1 ? mx : s;
 }
 
 __global__ void k_bt_reset(BatchArgs a) {
@@ -475,7 +495,10 @@ hipError_t batch_reset(const BatchArgs& a, hipStream_t s) {
 
 hipError_t batch_phase(BatchArgs a, long long pass, int fp32, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   a.pass = static_cast<int>(pass & 1);
-  return fp32 ? launch_work<float>(a, s, e0, e1) : launch_work<double>(a, s, e0, e1);
+  const hipError_t e = fp32 ? launch_work<float>(a, s, e0, e1) : launch_work<double>(a, s, e0, e1);
+  if (e != hipSuccess || a.nfold == 0) return e;
+  hipLaunchKernelGGL(k_bt_fold, dim3(a.nfold), dim3(kMarchLanes), 0, s, a);
+  return hipGetLastError();
 }
 
 }  // namespace erem

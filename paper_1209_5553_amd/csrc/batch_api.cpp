@@ -42,7 +42,9 @@ struct erem_batch {
   BState* state = nullptr;
   int* ndone = nullptr;
   int* h_ndone = nullptr;  // pinned
+  BFold* fold = nullptr;
   int ntiles = 0, tile_cap = 0;
+  int nfold = 0, fold_cap = 0;
   std::vector<BProb> hprob;
   // prepared state
   bool prepared = false;
@@ -101,6 +103,7 @@ void free_batch(erem_batch* b) {
   if (b->coef32) (void)hipFree(b->coef32);
   if (b->prob) (void)hipFree(b->prob);
   if (b->tile) (void)hipFree(b->tile);
+  if (b->fold) (void)hipFree(b->fold);
   if (b->state) (void)hipFree(b->state);
   if (b->ndone) (void)hipFree(b->ndone);
   if (b->h_ndone) (void)hipHostFree(b->h_ndone);
@@ -145,29 +148,56 @@ int build_tiles(erem_batch* b) {
     P.tile0 = static_cast<int>(tiles.size());
     P.ntiles = tx * ty;
     for (int y = 0; y < ty; ++y)
-      for (int x = 0; x < tx; ++x) tiles.push_back(BTile{i, x, y * rows, 0, P.tile0, P.ntiles});
+      for (int x = 0; x < tx; ++x) tiles.push_back(BTile{i, x, y * rows, 0, P.tile0, P.tile0, P.ntiles, 0});
   }
   if (tiles.size() > static_cast<size_t>(1 << 30)) return bfail(b, EREM_EINVAL, "too many tiles");
   b->ntiles = static_cast<int>(tiles.size());
   if (b->ntiles > b->tile_cap) {
     // sized once for the largest tile count of any shape, so that the arrays
     // the graphs hold are never reallocated
-    long long cap = b->ntiles;
+    long long cap = b->ntiles, fcap = 0;
     for (int k = 0; k < kNumTileShapes; ++k) {
-      long long n = 0;
-      for (const BProb& P : b->hprob)
-        n += static_cast<long long>(march_strips(P.nx, kBatchPassTerms[k])) *
-             ((P.ny + kBatchTileRows[k] - 1) / kBatchTileRows[k]);
+      long long n = 0, f = 0;
+      for (const BProb& P : b->hprob) {
+        const long long m = static_cast<long long>(march_strips(P.nx, kBatchPassTerms[k])) *
+                            ((P.ny + kBatchTileRows[k] - 1) / kBatchTileRows[k]);
+        n += m;
+        if (m > kBatchGate) f += kBatchFoldParts;
+      }
       cap = std::max(cap, n);
+      fcap = std::max(fcap, f);
     }
     if (b->tile) (void)hipFree(b->tile);
     if (b->part) (void)hipFree(b->part);
+    if (b->fold) (void)hipFree(b->fold);
     b->tile = nullptr;
     b->part = nullptr;
-    if (balloc(b, &b->tile, cap) || balloc(b, &b->part, 2 * kBatchPartStride * static_cast<size_t>(cap)))
+    b->fold = nullptr;
+    if (balloc(b, &b->tile, cap) || balloc(b, &b->part, 2 * kBatchPartStride * static_cast<size_t>(cap + fcap)) ||
+        balloc(b, &b->fold, fcap))
       return EREM_ENOMEM;
     b->tile_cap = static_cast<int>(cap);
+    b->fold_cap = static_cast<int>(fcap);
   }
+  // problems of many tiles: their partials go to kBatchFoldParts slots past the
+  // tiles' own
+  std::vector<BFold> folds;
+  for (int i = 0; i < b->nprob; ++i) {
+    const BProb& P = b->hprob[i];
+    if (P.ntiles <= kBatchGate) continue;
+    const int slot = b->tile_cap + static_cast<int>(folds.size());
+    for (int k = 0; k < kBatchFoldParts; ++k) {
+      const int t0 = static_cast<int>(static_cast<long long>(P.ntiles) * k / kBatchFoldParts);
+      const int t1 = static_cast<int>(static_cast<long long>(P.ntiles) * (k + 1) / kBatchFoldParts);
+      folds.push_back(BFold{i, P.tile0 + t0, t1 - t0, slot + k});
+    }
+    for (int t = P.tile0; t < P.tile0 + P.ntiles; ++t) {
+      tiles[t].src = slot;
+      tiles[t].nsrc = kBatchFoldParts;
+    }
+  }
+  b->nfold = static_cast<int>(folds.size());
+  if (b->nfold) BHIP(b, hipMemcpy(b->fold, folds.data(), sizeof(BFold) * folds.size(), hipMemcpyHostToDevice));
   BHIP(b, hipMemcpy(b->tile, tiles.data(), sizeof(BTile) * tiles.size(), hipMemcpyHostToDevice));
   BHIP(b, hipMemcpy(b->prob, b->hprob.data(), sizeof(BProb) * b->nprob, hipMemcpyHostToDevice));
   return EREM_OK;
@@ -194,7 +224,9 @@ BatchArgs make_args(erem_batch* b, double* T, int nsteps) {
   a.dk = b->dk;
   a.shift = b->shift;
   a.part = b->part;
-  a.part_cap = b->tile_cap;
+  a.part_cap = b->tile_cap + b->fold_cap;
+  a.fold = b->fold;
+  a.nfold = b->nfold;
   a.ntot = b->ntot;
   a.nprob = b->nprob;
   a.ntiles = b->ntiles;

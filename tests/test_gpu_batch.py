@@ -367,3 +367,61 @@ def test_batch_wide_substeps_match_oracle(torch_mod):
         err = rel_inf(Tg - p.T0, Tref - p.T0)
         _say(f"seed {s} (side {p.nx}): increment err {err:.2e}")
         assert err <= 1e-10, s
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("shape", [0, 1, 5, 7])
+def test_batch_folded_partials_match_oracle(torch_mod, shape, precision):
+    """Problems of more tiles than a wavefront adds up by itself (kBatchGate:
+    6 x 6400 cells are 400 tiles of 16 rows and 800 of 8) between small ones,
+    and one just below the edge (384 tiles of 8 rows, 385 with a row more),
+    replayed from a graph twice: FP64 1e-10, FP32 1e-5 of the increment."""
+    from paper_1209_5553_amd.api import EremBatch, make_opts
+    sides = [(33, 40), (6, 6400), (2, 1), (5, 3072), (5, 3073), (130, 17)]
+    probs = []
+    for i, (nx, ny) in enumerate(sides):
+        p = _rect_problem(nx, ny, seed=80 + i)
+        p.p_left = 1.0e4 * nx  # the pressure gradient of the 100-cell workload: no stiff column
+        probs.append(p)
+    b = EremBatch(probs, device="cuda:0")
+    b.prepare(probs[0].h, make_opts(m_max=256) if precision == 0 else
+              make_opts(m_max=256, precision=1, tol_r=1e-7))
+    b.set_tile_shape(shape)
+    T0 = b.pack([p.T0 for p in probs])
+    T, T2 = T0.clone(), T0.clone()
+    st = b.run(T, 2, use_graph=True)
+    _say(f"folded partials, shape {shape}, precision {precision}: {st}")
+    b.run(T2, 2, use_graph=False)
+    assert torch_mod.equal(T, T2)
+    T2.copy_(T0)
+    b.run(T2, 2, use_graph=True)
+    assert torch_mod.equal(T, T2)
+    for p, Tg in zip(probs, b.unpack(T)):
+        Tref, _ = oerem.run_linear(p, nsteps=2, tier="taylor")
+        assert rel_inf(Tg - p.T0, Tref - p.T0) <= (1e-10 if precision == 0 else 1e-5), (shape, p.name)
+
+
+def test_batch_pass_cost_grows_with_the_cells_of_a_problem(torch_mod):
+    """One 2048 x 2048 problem against 64 of 256 x 256, the same cells: a term
+    of the large one costs at most 1.5 times as much.  When every tile added up
+    all partials of its problem, it cost 3.5 times as much with tiles of 8 rows
+    (the reads grow with the square of the tiles)."""
+    from paper_1209_5553_amd.api import EremBatch, make_opts
+
+    def per_byte(sides):
+        probs = [_rect_problem(nx, ny, seed=90 + i) for i, (nx, ny) in enumerate(sides)]
+        b = EremBatch(probs, device="cuda:0")
+        b.prepare(probs[0].h, make_opts(m_max=128))
+        b.set_tile_shape(7)
+        T0 = b.pack([p.T0 for p in probs])
+        T = T0.clone()
+        best = np.inf
+        for _ in range(4):
+            T.copy_(T0)
+            st = b.run(T, 2, use_graph=True)
+            best = min(best, st["ms"] / st["leja_bytes"])
+        _say(f"{len(sides)} problems: {st}")
+        b.close()
+        return best
+
+    assert per_byte([(2048, 2048)]) <= 1.5 * per_byte([(256, 256)] * 64)

@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liberem.so")
 
 SOURCES = ["fields.hip", "leja.hip", "leja_small.hip", "krylov.hip", "mg.hip", "batch.hip", "adjoint.hip", "rosenbrock.hip", "noalloc.hip",
-           "erem_api.cpp", "batch_api.cpp", "adjoint_api.cpp", "ros_api.cpp", "host_numerics.cpp"]
+           "erem_api.cpp", "batch_api.cpp", "adjoint_api.cpp", "ros_api.cpp", "host_numerics.cpp", "lds_grant.cpp"]
 
 HIPCC_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared",

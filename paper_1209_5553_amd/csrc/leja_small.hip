@@ -12,9 +12,8 @@
 // (whose sums are formed in another order) passes at the same term.  One step on
 // 32 x 32: 718 -> 140 us.
 #include "device.h"
+#include "lds_grant.h"
 #include "leja.h"
-
-#include <mutex>
 
 namespace erem {
 
@@ -224,18 +223,10 @@ hipError_t launch_small(const Dims& d, const LejaCoef* cf, const double* coef64,
                         const double* g, const double* zt, double* out, LejaState* st, double delta, int s, int K,
                         hipStream_t q, hipEvent_t e0, hipEvent_t e1) {
   const size_t bytes = small_lds_bytes<C>(K);
-  {
-    static std::mutex mu;
-    static bool granted = false;  // the attribute belongs to the kernel; the largest size any K needs
-    std::lock_guard<std::mutex> lock(mu);
-    if (!granted) {
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_leja_small<DIM, C, V>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               static_cast<int>(small_lds_bytes<C>(kMaxTerms)));
-      if (e != hipSuccess) return e;
-      granted = true;
-    }
-  }
+  // the largest size any K needs
+  const hipError_t e = lds_grant(reinterpret_cast<const void*>(&k_leja_small<DIM, C, V>),
+                                 static_cast<int>(small_lds_bytes<C>(kMaxTerms)));
+  if (e != hipSuccess) return e;
   launch_timed(k_leja_small<DIM, C, V>, dim3(1), dim3(kSmallThreads), static_cast<unsigned>(bytes), q, e0, e1, d, cf,
                coef64, coef, v, g, zt, out, st, delta, s, K);
   return hipGetLastError();

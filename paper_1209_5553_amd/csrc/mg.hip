@@ -19,9 +19,8 @@
 // on shrinking halos instead of waiting for a grid-wide pass; the levels with
 // at most kMgLdsCells cells run inside one workgroup with everything in LDS.
 #include "device.h"
+#include "lds_grant.h"
 #include "mg.h"
-
-#include <mutex>
 
 namespace erem {
 
@@ -1305,18 +1304,9 @@ hipError_t mg_apply(const MgHierarchy& h, const double* r, double* z, PcgState* 
   return hipGetLastError();
 }
 
-// The attribute belongs to the kernel, not to a context: keep the largest
-// size any context asked for.
 hipError_t mg_set_lds_limit(int bytes, bool reg2d) {
-  static std::mutex mu;  // contexts may be created on several threads
-  static int granted[2] = {0, 0};
-  std::lock_guard<std::mutex> lock(mu);
-  if (bytes <= granted[reg2d]) return hipSuccess;
-  const void* kernel = reg2d ? reinterpret_cast<const void*>(&k_mg_coarse_2d)
-                             : reinterpret_cast<const void*>(&k_mg_coarse_lds);
-  const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e == hipSuccess) granted[reg2d] = bytes;
-  return e;
+  return lds_grant(reg2d ? reinterpret_cast<const void*>(&k_mg_coarse_2d)
+                         : reinterpret_cast<const void*>(&k_mg_coarse_lds), bytes);
 }
 
 }  // namespace erem

@@ -31,6 +31,12 @@ constexpr int kZmarchThreads = 640;
 // what they hide (128^3: 3.50 ms a step against 4.33 with 512 workgroups; 256^3
 // 38.2 against 40.7 ms).
 constexpr int kZmarchBlocks = 256;
+// Its tile on grids of at most four rows (a vertical slice), where sixteen would be
+// padding: a cell per thread, two workgroups a CU.  One FP64 step, tile of 16 / 4
+// rows: 512 x 1 x 512 2.24 / 1.18 ms, 512 x 4 x 512 2.61 / 1.53, 4 x 4 x 4000 89 / 47
+// (one term per pass on 64 x 4 tiles took 1.25, 2.43 and 77); two cells a thread
+// 1.30, 1.62 and 53; with 768 workgroups 1.44, 1.84 and 57.
+constexpr int kSliceRows = 4, kSliceStrip = 1, kSliceThreads = 448, kSliceBlocks = 512;
 constexpr int kInitBlocks = 2048;    // most workgroups of the start pass
 constexpr int kGateTerms = 5;       // most terms of one stop test (the first: terms 0 .. 4)
 constexpr int kGateMax = 2048;      // most partials per term that every workgroup adds up by itself

@@ -939,10 +939,13 @@ int terms_rows(const Dims& d) {
   return rows;
 }
 
-// Planes per chunk of the 3D pass: about kZmarchBlocks workgroups.
+// Rows of the 3D pass's tile, and planes per chunk: about kZmarchBlocks workgroups.
+int zmarch_rows(const Dims& d) { return d.ny <= kSliceRows ? kSliceRows : kZmarchRows; }
 int zmarch_planes(const Dims& d) {
-  const long long xy = static_cast<long long>((d.nx + kBX - 1) / kBX) * ((d.ny + kZmarchRows - 1) / kZmarchRows);
-  const long long chunks = std::max(1ll, std::min<long long>(d.nz, kZmarchBlocks / xy));
+  const int rows = zmarch_rows(d);
+  const long long xy = static_cast<long long>((d.nx + kBX - 1) / kBX) * ((d.ny + rows - 1) / rows);
+  const long long chunks =
+      std::max(1ll, std::min<long long>(d.nz, (rows == kSliceRows ? kSliceBlocks : kZmarchBlocks) / xy));
   return static_cast<int>((d.nz + chunks - 1) / chunks);
 }
 
@@ -979,8 +982,8 @@ int terms_blocks(const Dims& d) {
     return static_cast<int>(march_strips(d.nx, kTermsPerPass2) * ((d.ny + 4 * rows - 1) / (4 * rows)));
   }
   if (const int n = cube_blocks(d)) return n;
-  const int zc = zmarch_planes(d);
-  return static_cast<int>(((d.nx + kBX - 1) / kBX) * ((d.ny + kZmarchRows - 1) / kZmarchRows) *
+  const int zc = zmarch_planes(d), rows = zmarch_rows(d);
+  return static_cast<int>(((d.nx + kBX - 1) / kBX) * ((d.ny + rows - 1) / rows) *
                           ((d.nz + zc - 1) / zc));
 }
 
@@ -1043,11 +1046,13 @@ hipError_t launch_terms(const Dims& d, const LejaCoef* cf, const V* coef, const 
     launch_timed(k_leja_terms<kTermsPerPass2, V>, grid, dim3(kThreads), 0, s, e0, e1, d, cf, coef, qin, qout, p, st,
                  part, g, nb, terms_rows(d), k);
   } else {
-    const bool flip = zmarch_turns(d, sizeof(V)) && (k >> 1) & 1;
-    launch_timed(flip ? k_leja_zmarch<kZmarchRows, kZmarchStrip, kZmarchThreads, true, V>
-                      : k_leja_zmarch<kZmarchRows, kZmarchStrip, kZmarchThreads, false, V>,
-                 grid, dim3(kZmarchThreads), 0, s, e0, e1, d, cf, coef, qin, qout, p, st, part, g, nb,
-                 zmarch_planes(d), k);
+    const bool flip = zmarch_turns(d, sizeof(V)) && (k >> 1) & 1, slice = zmarch_rows(d) == kSliceRows;
+    const auto kernel = slice ? (flip ? k_leja_zmarch<kSliceRows, kSliceStrip, kSliceThreads, true, V>
+                                      : k_leja_zmarch<kSliceRows, kSliceStrip, kSliceThreads, false, V>)
+                              : (flip ? k_leja_zmarch<kZmarchRows, kZmarchStrip, kZmarchThreads, true, V>
+                                      : k_leja_zmarch<kZmarchRows, kZmarchStrip, kZmarchThreads, false, V>);
+    launch_timed(kernel, grid, dim3(slice ? kSliceThreads : kZmarchThreads), 0, s, e0, e1, d, cf, coef, qin, qout, p, st,
+                 part, g, nb, zmarch_planes(d), k);
   }
   return hipGetLastError();
 }

@@ -679,6 +679,50 @@ def test_turned_3d_passes_match_oracle(torch_mod):
     test_small_grid_phi1_edges_match_oracle(torch_mod, (150, 151, 150), {})
 
 
+@pytest.mark.parametrize("shape", [(2, 1, 1025), (64, 4, 257), (65, 3, 175), (130, 2, 603), (300, 4, 520), (65, 5, 175),
+                                   (2, 2, 4001)])
+@pytest.mark.parametrize("opts", [{}, {"m_max": 13}, {"precision": 1, "tol_r": 1e-7}])
+def test_slice_pass_edges_match_oracle(torch_mod, shape, opts):
+    """3D grids of at most four rows past the limit of the box pass (and one of
+    five): one tile of 64 columns and more, chunks of one plane, of several and
+    with a remainder, a budget that is no multiple of a pass (13) and FP32."""
+    test_small_grid_phi1_edges_match_oracle(torch_mod, shape, opts)
+
+
+def test_turned_slice_passes_match_oracle(torch_mod):
+    """A slice whose pass exceeds the Infinity Cache: every second one from the
+    top down."""
+    test_small_grid_phi1_edges_match_oracle(torch_mod, (1100, 3, 1100), {})
+
+
+def test_slice_terms_cost_like_those_of_full_tiles(torch_mod):
+    """A Newton term on 128 x 2 x 1024 takes at most 1.5 times the kernel time of
+    one on 512 x 16 x 32, the same cells in full tiles: with tiles of 16 rows for
+    its two it took 2.0 times."""
+    torch = torch_mod
+    from paper_1209_5553_amd.api import EremContext, make_opts
+
+    def per_term(nx, ny, nz):
+        n = nx * ny * nz
+        rng = np.random.default_rng(5)
+        ctx = EremContext(nx, ny, nz, device="cuda:0")
+        ctx.set_jacobian(_dev(torch, _diffusive_stencil(rng, nx, ny, nz)),
+                         torch.zeros(n, dtype=torch.float64, device="cuda:0"))
+        v, out = _dev(torch, rng.standard_normal(n)), torch.empty(n, dtype=torch.float64, device="cuda:0")
+        ctx.phi1_apply(20.0, v, out, make_opts())
+        best = np.inf
+        for _ in range(4):
+            ctx.profile(True)
+            ctx.phi1_apply(20.0, v, out, make_opts())
+            k = ctx.profile_read()
+            ctx.profile(False)
+            best = min(best, k["leja_term_ms"] / k["leja_term_launches"])
+        _say(f"{nx}x{ny}x{nz}: {1e3 * best:.2f} us a term")
+        return best
+
+    assert per_term(128, 2, 1024) <= 1.5 * per_term(512, 16, 32)
+
+
 @pytest.mark.parametrize("shape,m", [((1024, 256, 1), 12), ((1024, 257, 1), 13), ((67, 65, 61), 14)])
 def test_krylov_folded_sums_match_oracle(torch_mod, shape, m):
     """1024 workgroups add up each other's partial sums, one more and a fold does;

@@ -304,6 +304,35 @@ def test_batch_strip_and_chunk_edges_match_oracle(torch_mod, shape, precision):
         assert rel_inf(Tg - p.T0, Tref - p.T0) <= (1e-10 if precision == 0 else 1e-5), (shape, p.name)
 
 
+# rows and terms per pass of the tile shapes (include/erem.h, tile_shape)
+TILE_ROWS = (16, 8, 32, 64, 128, 32, 16, 8)
+PASS_TERMS = (4, 4, 4, 4, 4, 8, 8, 8)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("shape", list(range(8)))
+def test_batch_chunk_edges_of_every_shape_match_oracle(torch_mod, shape, precision):
+    """Heights one below, at and one above one and two of the shape's chunks, and
+    widths at the edge of its strips, in one batch: FP64 1e-10, FP32 1e-5 of the
+    increment."""
+    from paper_1209_5553_amd.api import EremBatch, make_opts
+    r, strip = TILE_ROWS[shape], 64 + 64 - 2 * PASS_TERMS[shape]
+    sides = [(20, r - 1), (21, r), (22, r + 1), (strip, 2 * r - 1), (strip + 1, 2 * r), (strip - 1, 2 * r + 1)]
+    probs = [_rect_problem(nx, ny, seed=70 + i) for i, (nx, ny) in enumerate(sides)]
+    b = EremBatch(probs, device="cuda:0")
+    b.prepare(probs[0].h, make_opts(m_max=256) if precision == 0 else
+              make_opts(m_max=256, precision=1, tol_r=1e-7))
+    b.set_tile_shape(shape)
+    T = b.pack([p.T0 for p in probs])
+    st = b.run(T, 2, use_graph=False)
+    _say(f"chunk edges, shape {shape}, precision {precision}: {st}")
+    # the shape has the chunks that the heights are chosen for
+    assert st["grid"] == sum((1 if nx <= 64 else 1 + -(-(nx - 64) // (strip - 64))) * -(-ny // r) for nx, ny in sides)
+    for p, Tg in zip(probs, b.unpack(T)):
+        Tref, _ = oerem.run_linear(p, nsteps=2, tier="taylor")
+        assert rel_inf(Tg - p.T0, Tref - p.T0) <= (1e-10 if precision == 0 else 1e-5), (shape, p.name)
+
+
 def test_batch_problem_over_the_term_budget_fails_alone(torch_mod):
     """Substeps capped at two: a stiff two-cell problem (h (beta - alpha)
     about 1200) cannot meet the tolerance within m_max terms of a substep of

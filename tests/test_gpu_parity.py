@@ -135,6 +135,14 @@ def test_multigrid_pressure_level_edges(torch_mod, shape):
     test_multigrid_pressure_ragged_shapes(torch_mod, shape)
 
 
+@pytest.mark.parametrize("shape", [(38, 25), (150, 100), (264, 232)])
+def test_multigrid_pressure_four_coarse_levels(torch_mod, shape):
+    """2D grids with three smoothed levels in the one-workgroup solve (38 x 25,
+    19 x 13, 10 x 7 above 5 x 4; 33 x 29, 17 x 15, 9 x 8 above 5 x 4), which keep
+    them in LDS, alone and under grid levels."""
+    test_multigrid_pressure_ragged_shapes(torch_mod, shape)
+
+
 def test_multigrid_pressure_3d_layered_is_analytic(torch_mod):
     torch = torch_mod
     prob = inputs.layered3d_problem(24, seed=3)

@@ -509,7 +509,21 @@ def bench_adjoint(args):
 # describe the kernels as measured: reset an entry to None when its kernel
 # changes.
 TRAFFIC = {
-    # adjoint workload (256 x 256): reverse Newton term
+    ("coupled512", "fp64", "mg_vcycle"): 55.70e6,
+    ("coupled512", "fp64", "leja_term"): 5.19e6,        # a working four-term launch moves 20.76 MB
+    ("injector512", "fp64", "leja_term"): 5.19e6,       # the same kernel on the same grid
+    ("layered128", "fp64", "leja_term"): 110.08e6,      # half of a two-term launch
+    ("layered128", "mixed", "leja_term"): 55.06e6,
+    ("layered256", "fp64", "leja_term"): 802.37e6,
+    ("layered256", "mixed", "leja_term"): 468.50e6,
+    ("compressible50", "fp64", "leja_term"): 7.03e6,
+    # batch256: whole-run totals of the work kernel (divided by its launches)
+    ("batch256", "fp64", "k_bt_ctrl_work/shape5"): 266.34e9,
+    ("batch256", "mixed", "k_bt_ctrl_work/shape5"): 212.14e9,
+    # one BiCGSTAB iteration (two kernels) of the comparison schemes
+    ("coupled512", "fp64", "bicg_iteration"): 58.30e6,
+    # adjoint workload (256 x 256): V-cycle + CG iteration, reverse Newton term
+    ("adjoint256", "fp64", "mg_vcycle"): 14.81e6,
     ("adjoint256", "fp64", "adj_rev_term"): 11.10e6,
 }
 

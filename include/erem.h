@@ -22,8 +22,10 @@
  * - Pointers named h_* or plain out/in are HOST pointers.
  * - Every call enqueues its device work on the stream given to erem_create
  *   (a hipStream_t passed as void*; NULL = the null stream).  Calls that fill
- *   an erem_stats or return host data synchronise that stream before
- *   returning.
+ *   an erem_stats or return host data have waited for the data behind them,
+ *   not always for the call's last update: results in device memory (the T of
+ *   a step) are ordered on that stream and may be pending at return, so work
+ *   on another stream, or a host timer, synchronises with it first.
  * - Return value: EREM_OK (0) or a negative error code; on error a message is
  *   available from erem_last_error(ctx) and, for erem_step, T is unmodified.
  *   No C++ exception crosses the ABI.
@@ -199,7 +201,8 @@ int erem_phi1_apply(erem_ctx* ctx, double h, const double* d_v, double* d_out,
  * a host synchronisation: the substep count is predicted from the previous
  * step's interval width and confirmed afterwards (a failed prediction runs
  * the step again on the interval read back); the result is the same bit for
- * bit.  The call returns after the step has completed on the stream. */
+ * bit.  At return the step is enqueued as a whole and confirmed; the update of
+ * d_T may be pending on the stream. */
 int erem_step(erem_ctx* ctx, double h, double* d_T, const erem_opts* opts, erem_stats* stats);
 
 /* As erem_step but with the J and F already held by the context (from
@@ -362,15 +365,16 @@ int erem_coupled_step_adjoint(erem_ctx* ctx, double h, const double* d_T, double
  * step (Eq. EERM) uses a fixed Gershgorin interval, substep count and set of
  * divided differences per problem (Sec. 4.2).  erem_batch_run advances all
  * problems by nsteps steps.  The problems are cut into tiles (a strip of at
- * most 64 columns by some rows) that form one list; a run is a sequence of phases, and each phase is one work
- * launch over the whole list - every problem that is not done takes one step
- * of its own schedule: a substep's start pass (q_0, p = d_0 q_0), four or
- * eight Newton terms (Eq. newt), or the last step's T update.  The launch begins
- * with the control step of the pass before: each problem's tile partials (of a
- * problem of more than 384 tiles after a fold launch) are added in a fixed order (so runs are bit-for-bit reproducible), and the stop test of
- * Sec. 4.2 gives the problem's next phase.  With use_graph the whole sequence is
- * one hipGraph, captured on first use with the number of phases a
- * calibration run on a copy of T needed plus a margin; a run that needs more
+ * most 64 columns by some rows) that form one list; a run is a sequence of
+ * phases, and each phase is one work launch over the whole list - every problem
+ * that is not done takes one step of its own schedule: a substep's start pass
+ * (q_0, p = d_0 q_0), four or eight Newton terms (Eq. newt), or the last step's
+ * T update.  The launch begins with the control step of the pass before: each
+ * problem's tile partials (of a problem of more than 384 tiles after a fold
+ * launch) are added in a fixed order (so runs are bit-for-bit reproducible), and
+ * the stop test of Sec. 4.2 gives the problem's next phase.  With use_graph the
+ * whole sequence is one hipGraph, captured on first use with the number of phases
+ * a calibration run on a copy of T needed plus a margin; a run that needs more
  * continues with launches from the host.  Temperatures are packed: problem i
  * owns cells [off_i, off_i + nx_i ny_i) of the caller's array
  * (erem_batch_offsets). */

@@ -12,10 +12,15 @@ namespace erem {
 // kBatchTileRows[shape] rows, advanced by kBatchPassTerms[shape] Newton terms
 // per pass by one wavefront.  Eight terms halve the bytes per term; short
 // tiles re-read more rows (2 NT per tile) but shorten a pass whose problems do
-// not fill the chip.  50 steps of 256 realisations (7.2 M cells, FP64): 87 ms
-// with 4 terms x 32 rows, 80.8 / 61.7 / 57.1 ms with 8 terms x 8 / 16 / 32 rows;
-// 4 steps of 30 realisations (mixed): 1.93 ms with 4 x 8, 1.98 with 4 x 16, 1.79
-// with 8 x 8, 1.87 with 8 x 16, 2.18 with 8 x 32.
+// not fill the chip.  Two FP64 steps, us, for the shapes 0 .. 7:
+//   one of 256 x 256          420   389   510   718  1117   471   381   343
+//   20 of 40 .. 256 a side    954   994  1183  1671  2688  1070   857   867
+//   64 of 256 x 256          2020  2395  1812  1772  1956  1315  1471  1943
+//   one of 4096 x 4096       3709  4168  3707  3858  4161  2645  2990  3958
+// Of 14 such sets in both precisions each ran fastest with eight terms (7: few
+// small problems, then 6, 5: the chip filled).  Four terms stay for the callers
+// that name such a shape, and shape 0 is what a batch has before one is chosen:
+// its applied degrees are multiples of four, as a single grid's.
 constexpr int kNumTileShapes = 8;
 constexpr int kBatchTileRows[kNumTileShapes] = {16, 8, 32, 64, 128, 32, 16, 8};
 constexpr int kBatchPassTerms[kNumTileShapes] = {4, 4, 4, 4, 4, 8, 8, 8};

@@ -24,9 +24,10 @@
 //   finish pass T += u + delta p of the last step.
 //
 // Each tile stores its partial sums (sum q_k^2 per term, in FP64); at the start
-// of the next pass every tile's wavefront adds up its problem's partials (those of
-// a problem of many tiles from a fold between the passes) in a fixed order, applies the scaled-norm stop test of Sec. 4.2 to the pass's NT
-// estimates in order, and so knows the problem's next phase.
+// of the next pass every tile's wavefront adds up its problem's partials (those
+// of a problem of many tiles from a fold between the passes) in a fixed order,
+// applies the scaled-norm stop test of Sec. 4.2 to the pass's NT estimates in
+// order, and so knows the problem's next phase.
 // Problems of every size and substep count thus share every launch, the
 // work spreads over all CUs whatever the mix, and the whole run is a fixed
 // sequence of launches with no grid-wide synchronisation and no waiting
@@ -331,15 +332,16 @@ __device__ inline void batch_next(const BatchArgs& a, const BProb& P, BState& S,
 // records the state.
 //
 // While most problems are unfinished the pass is bound by memory: eight FP64
-// terms of 7.2 M cells read 544 MB (5 stencil words, q and p, plus the halos that
-// missed L2) and write 115 MB in about 145 us, 4.5 TB/s where a large copy
-// reaches 4.8; taking every second pass back to front finds the end of the pass
+// terms of 7.2 M cells read 554 MB from beyond the L2s (5 stencil words, q and p,
+// plus halos) and write 115 MB in about 119 us, 5.6 TB/s where a large copy
+// reaches 4.8: taking every second pass back to front finds the end of the pass
 // before in the Infinity Cache (a run of 50 steps 70.4 -> 65.9 ms).  The 64 x 16
 // LDS tiles on 512 threads that this replaces took 215 us for the same pass (two
 // workgroups' loads per CU in flight, then eight barriered terms) and 92 ms for
 // the run.  When only the longest problems are left, a pass costs what one
-// wavefront takes to issue its rows (about 500 cycles a row of eight terms), and
-// a control launch of its own after every pass cost 6 us and a launch gap.
+// wavefront takes to issue its rows (about 500 cycles a row of eight terms).  A
+// control launch of its own after every pass cost 6 us and a launch gap (65.9 ->
+// 57.1 ms).
 template <int NT, class V>
 __global__ __launch_bounds__(kMarchLanes) __attribute__((amdgpu_waves_per_eu(2))) void k_bt_ctrl_work(BatchArgs a) {
   static_assert(NT <= kBatchPartStride && NT % 4 == 0, "terms per pass");

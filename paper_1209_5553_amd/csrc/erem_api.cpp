@@ -402,7 +402,7 @@ int substeps_for(double h, double width, double rho, int smax) {
 
 // Term budget of an evaluation's first attempt: the previous evaluation's
 // largest substep degree plus one stop-test group (the launches past the
-// stop return at entry), else m_max; a degree that outgrows it restarts the
+// stop write nothing, but each costs some 3 us and its first loads), else m_max; a degree that outgrows it restarts the
 // evaluation with the full budget.
 int first_budget(const erem_ctx* c, const erem_opts* o) {
   if (o->chunk > 0) return std::min(o->chunk, o->m_max);

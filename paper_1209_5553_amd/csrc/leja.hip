@@ -12,7 +12,9 @@
 // reproducible bit for bit), the scaled error estimates ||delta d_k q_k|| =
 // |delta d_k| ||q_k||_2 / (sqrt(N) scal) formed, and 10^p * mean(last five
 // estimates) < 1 tested (Sec. 4.2), after every kCheckEvery terms.  Once it
-// holds, the first workgroup records it and later passes return at entry.
+// holds, the first workgroup records it, and later passes write nothing: they
+// still issue their first loads (the box passes those of their whole box), which
+// are on their way before the flag is known, and add up the partials.
 //
 // Value type V is double (FP64 path) or float (mixed path: FP32 stencil,
 // vectors and accumulation; FP64 divided differences, norms and update).
@@ -357,9 +359,10 @@ __global__ __launch_bounds__(1024) void k_leja_box(Dims d, const LejaCoef* __res
 //
 // Bound by memory: per cell and pair of terms the seven stencil words, q_{k-1},
 // p in and out and the last q, 88 B where two one-term passes move 176.  Turned
-// passes (zmarch_turns) find some of it in the Infinity Cache.  On
-// 256^3 (FP64, 1.5 GB a pass, six times the Infinity Cache) 248 -> 133 us per
-// term, 5.5 TB/s; on 128^3 28 -> 19 us.
+// passes (zmarch_turns) find some of it in the Infinity Cache.  On 256^3 (FP64) a
+// pass reads 1.34 GB from beyond the L2s (planes at the ends of chunks and halos
+// twice) and writes 0.27 in 240 us, 6.7 TB/s: 248 -> 120 us per term; on 128^3 0.22
+// GB, and 28 -> 19 us per term.
 template <int TY, int SH, int NTH, bool FLIP, class V>
 __global__ __launch_bounds__(NTH) void k_leja_zmarch(Dims d, const LejaCoef* __restrict__ cf,
                                            const V* __restrict__ coef, const V* __restrict__ qin,

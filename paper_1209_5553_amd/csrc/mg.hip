@@ -1008,14 +1008,17 @@ __global__ __launch_bounds__(1024) void k_mg_coarse_lds(MgCoarseArgs a, const do
 
 // ---------------------------------------------------------------------------
 // The coarse solve of 2D hierarchies with two smoothed LDS levels above the
-// bottom (every grid that is not a thin strip): the cycles of k_mg_coarse_lds, the
+// bottom: the cycles of k_mg_coarse_lds, the
 // same operations in the same order, with the operands in registers.  A thread owns
 // cell t of each level; only the iterates that neighbours read go through LDS, so a
 // sweep is four LDS reads, some ten operations, one LDS write and a barrier, with no
 // division of the cell index.
 //
 // Bound by its chain of some 50 barriered phases: 11.8 us for 32 x 32 and two levels
-// below, where k_mg_coarse_lds takes 23.8.
+// below, where k_mg_coarse_lds takes 23.8.  Grids whose halving passes the 1024
+// cells high and the 64 low (33 x 29, 17 x 15, 9 x 8, 5 x 4: some 5% of the
+// rectangles of 48 to 512 cells a side, 300 x 200 and 600 x 400 among them) have
+// three smoothed levels and keep k_mg_coarse_lds, as thin strips do.
 // ---------------------------------------------------------------------------
 struct CoarseCell {
   double tw, te, ts, tn;  // transmissibilities, zero toward a missing neighbour

@@ -13,7 +13,11 @@
 //       t = A z,  (t, s), (t, t), (rhat, s), (rhat, t)
 // where A = sigma I - J.  beta needs (rhat, r) of the new r before K1 has formed
 // it: it is (rhat, s) - omega (rhat, t), which takes the place of a third kernel
-// and its pass; (r, r), which the stop test compares over many orders, is summed
+// and its pass.  The difference cancels where an iteration shortens r much (by a
+// factor f it loses log10 f digits of beta, which r and x do not inherit): over
+// four operators, sigma from 1e-3 to 1e-9 and rtol from 1e-6 to 1e-15 the
+// iterations were 0.88 .. 1.08 times those with (rhat, r) summed, the same up to
+// 40, and the residuals alike.  (r, r), which the stop test compares over many orders, is summed
 // from r itself.  A kernel that needs a neighbour's p (or s) forms it from the
 // neighbour's operands, so p and v alternate between two buffers.
 //

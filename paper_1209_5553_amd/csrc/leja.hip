@@ -361,8 +361,8 @@ __global__ __launch_bounds__(1024) void k_leja_box(Dims d, const LejaCoef* __res
 // p in and out and the last q, 88 B where two one-term passes move 176.  Turned
 // passes (zmarch_turns) find some of it in the Infinity Cache.  On 256^3 (FP64) a
 // pass reads 1.34 GB from beyond the L2s (planes at the ends of chunks and halos
-// twice) and writes 0.27 in 240 us, 6.7 TB/s: 248 -> 120 us per term; on 128^3 0.22
-// GB, and 28 -> 19 us per term.
+// twice) and writes 0.27 in 300 us, 5.4 TB/s: 248 -> 150 us per term; on 128^3 0.22
+// GB in 35.5 us, 28 -> 18 us per term.
 template <int TY, int SH, int NTH, bool FLIP, class V>
 __global__ __launch_bounds__(NTH) void k_leja_zmarch(Dims d, const LejaCoef* __restrict__ cf,
                                            const V* __restrict__ coef, const V* __restrict__ qin,
